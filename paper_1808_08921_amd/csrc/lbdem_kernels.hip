@@ -384,17 +384,18 @@ __device__ __forceinline__ C feq(int d, C rho, C ux, C uy, C uz, C uu)
 
 // f^eq_d(rho, u) - w_d rho_f with rho = rho_f + drho, Eq. (BGKequili) written for the
 // deviation from the rest state: w_d (drho + rho (c.u / c_s^2 + (c.u)^2 / (2 c_s^4) - u.u /
-// (2 c_s^2)))
+// (2 c_s^2))), with 1 / c_s^2 = 3 as exact factors 3, 9/2 and 3/2 and fused multiply-adds
+// (FP64 divisions by c_s^2, about a dozen instructions each and 57 per node, had cost the
+// FCC wave case's FP64 step 9 of 207 us and the FP64 adjoint a fifth of its time)
 template <typename C>
 __device__ __forceinline__ C feq_dev(int d, C drho, C rho, C ux, C uy, C uz, C uu)
 {
     const C cu = cdot(d, ux, uy, uz);
+    const C uu3 = C(1.5) * uu;
     if constexpr (sizeof(C) == 8) {
-        const double cs2 = kCS2;
-        return kWd[d] * (drho + rho * (cu / cs2 + (cu * cu) / (2.0 * cs2 * cs2) - uu / (2.0 * cs2)));
+        const C poly = __builtin_fma(C(4.5) * cu, cu, __builtin_fma(C(3), cu, -uu3));
+        return (C)kWd[d] * __builtin_fma(rho, poly, drho);
     } else {
-        // FP32 collision arithmetic with fused multiply-adds (uu3 = 1.5 u.u)
-        const C uu3 = C(1.5) * uu;
         const C poly = __builtin_fmaf(C(4.5) * cu, cu, __builtin_fmaf(C(3), cu, -uu3));
         return (C)kWd[d] * __builtin_fmaf(rho, poly, drho);
     }
