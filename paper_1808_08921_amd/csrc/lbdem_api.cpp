@@ -1499,45 +1499,63 @@ struct lbdem_adj {
     int64_t t0 = 0;
     double tau = 1.0;
     bool have_forward = false;
+    // the segment whose states (after its first, a checkpoint) seg holds, -1 for none
+    int seg_at = -1;
     AdjDev a{};
     hipStream_t stream = nullptr;
-    char *f0 = nullptr, *ckp = nullptr, *seg = nullptr, *lam0 = nullptr, *lam1 = nullptr, *mu = nullptr;
-    double *vdev = nullptr, *shape = nullptr, *P = nullptr, *dLdP = nullptr, *accw = nullptr, *acca = nullptr;
-    double *macc = nullptr, *gv = nullptr, *nfl = nullptr, *X = nullptr, *W = nullptr, *R = nullptr;
-    int *own = nullptr, *pz = nullptr;
+    char *f0 = nullptr, *ckp = nullptr, *seg = nullptr, *lam0 = nullptr, *lam1 = nullptr;
+    double *vdev = nullptr, *shape = nullptr, *gv = nullptr;
     std::vector<double> v_host;
+
+    size_t state_bytes() const { return (size_t)kQ * a.ns * es; }
+    // the state a segment starts from: the window's start, or a checkpoint
+    char *start_of(int s) const { return s == 0 ? f0 : ckp + state_bytes() * (size_t)(s - 1); }
 };
 
 extern "C" {
 
-static size_t adj_layout(lbdem_adj *J, int64_t ncell, int64_t np, int nprobe, int nblk, int64_t nsteps, int ck,
-                         size_t es, size_t cs, char *base)
+static size_t adj_layout(lbdem_adj *J, const MemberDev &M, int nprobe, int64_t nsteps, int ck, size_t es, size_t cs,
+                         char *base)
 {
     Carver c;
     c.base = base;
-    const size_t st = (size_t)kQ * ncell;
+    AdjDev a{};
+    // slots at most: every node fluid
+    const size_t wpp = (size_t)M.nx * M.ny / 64 + 2, cap = ((size_t)M.ncell + 63) / 64 * 64;
+    const size_t st = (size_t)kQ * cap, np1 = (size_t)std::max(M.np, 1), npr = (size_t)std::max(nprobe, 1);
     const int nck = (int)((nsteps + ck - 1) / ck);
     char *f0 = c.take<char>(es * st);
-    char *ckp = c.take<char>(es * st * (size_t)nck);
+    char *ckp = c.take<char>(es * st * (size_t)std::max(nck - 1, 1));
     char *seg = c.take<char>(es * st * (size_t)std::max(ck, 2));
-    char *lam0 = c.take<char>(cs * st), *lam1 = c.take<char>(cs * st), *mu = c.take<char>(cs * st);
-    double *macc = c.take<double>((size_t)(kQ - 1) * ncell);
-    int *own = c.take<int>((size_t)ncell);
-    double *X = c.take<double>(3 * (size_t)std::max<int64_t>(np, 1));
-    double *W = c.take<double>(3 * (size_t)std::max<int64_t>(np, 1));
-    double *R = c.take<double>((size_t)std::max<int64_t>(np, 1));
-    double *V = c.take<double>(3 * (size_t)std::max<int64_t>(np, 1));
-    double *gv = c.take<double>(3 * (size_t)std::max<int64_t>(np, 1));
+    char *lam0 = c.take<char>(cs * st), *lam1 = c.take<char>(cs * st);
+    a.wall = c.take<char>(cs * (size_t)(kQ - 1) * cap);
+    a.macc = c.take<double>((size_t)(kQ - 1) * cap);
+    a.own = c.take<int>((size_t)M.ncell);
+    a.rows = c.take<uint2>((size_t)M.nz * M.ny * M.nw);
+    a.pbase = c.take<int>((size_t)M.nz + 1);
+    a.node = c.take<int>(cap);
+    a.mask = c.take<uint2>(cap);
+    a.loff = c.take<int>(cap);
+    a.nlink = c.take<int>(1);
+    double *X = c.take<double>(3 * np1), *W = c.take<double>(3 * np1), *R = c.take<double>(np1);
+    double *V = c.take<double>(3 * np1), *gv = c.take<double>(3 * np1);
     double *shape = c.take<double>((size_t)std::max<int64_t>(nsteps, 1));
-    double *P = c.take<double>((size_t)std::max<int64_t>(nsteps * nprobe, 1));
-    double *dLdP = c.take<double>((size_t)std::max<int64_t>(nsteps * nprobe, 1));
-    double *accw = c.take<double>((size_t)nblk), *acca = c.take<double>((size_t)nblk);
-    double *nfl = c.take<double>((size_t)std::max(nprobe, 1));
-    int *pz = c.take<int>((size_t)std::max(nprobe, 1));
+    a.P = c.take<double>((size_t)nsteps * npr);
+    double *dLdP = c.take<double>((size_t)nsteps * npr);
+    const int64_t rows = std::min<int64_t>(ck, nsteps);
+    a.part = c.take<double>(wpp * npr * (size_t)rows);
+    const size_t nblk = (cap + 255) / 256;
+    a.acc_w = c.take<double>(nblk);
+    a.acc_a = c.take<double>(nblk);
+    double *nfl = c.take<double>(npr);
+    int *pz = c.take<int>(npr);
+    short *pzm = c.take<short>((size_t)M.nz);
     if (J) {
-        J->f0 = f0; J->ckp = ckp; J->seg = seg; J->lam0 = lam0; J->lam1 = lam1; J->mu = mu; J->macc = macc;
-        J->own = own; J->X = X; J->W = W; J->R = R; J->vdev = V; J->gv = gv; J->shape = shape; J->P = P;
-        J->dLdP = dLdP; J->accw = accw; J->acca = acca; J->nfl = nfl; J->pz = pz; J->nck = nck;
+        a.X = X; a.W = W; a.R = R; a.V = V; a.gv = gv; a.shape = shape; a.dLdP = dLdP; a.probe_nfl = nfl;
+        a.probe_z = pz; a.pzm = pzm; a.wpp = (int)wpp;
+        J->a = a;
+        J->f0 = f0; J->ckp = ckp; J->seg = seg; J->lam0 = lam0; J->lam1 = lam1; J->vdev = V; J->shape = shape;
+        J->gv = gv; J->nck = nck;
     }
     return (c.off + 255) & ~size_t(255);
 }
@@ -1550,8 +1568,7 @@ int lbdem_adj_workspace_size(lbdem_set *S, int32_t lattice, int64_t nsteps, int3
     if (nsteps < 1 || ckpt_every < 1) return fail(LBDEM_EINVAL, "nsteps and ckpt_every must be >= 1");
     const MemberDev &M = S->G.mem[lattice];
     const size_t es = elem_size(S->G.prec), cs = S->G.prec == PREC_FP64 ? 8 : 4;
-    const int nblk = (int)((M.ncell + 255) / 256);
-    *bytes = adj_layout(nullptr, M.ncell, M.np, S->params[lattice].n_probe, nblk, nsteps, ckpt_every, es, cs, nullptr);
+    *bytes = adj_layout(nullptr, M, S->params[lattice].n_probe, nsteps, ckpt_every, es, cs, nullptr);
     return LBDEM_OK;
 }
 
@@ -1577,29 +1594,34 @@ int lbdem_adj_create(lbdem_set *S, int32_t lattice, int64_t nsteps, int32_t ckpt
     J->nsteps = nsteps;
     J->ck = ckpt_every;
     J->stream = S->stream;
-    const int nblk = (int)((M.ncell + 255) / 256);
-    adj_layout(J.get(), M.ncell, M.np, p.n_probe, nblk, nsteps, ckpt_every, J->es, J->cs, (char *)workspace);
+    adj_layout(J.get(), M, p.n_probe, nsteps, ckpt_every, J->es, J->cs, (char *)workspace);
+    AdjDev &a = J->a;
+    a.M = M;
+    a.ncell = (int)M.ncell;
+    a.np = M.np;
+    a.rho_f = p.rho_f;
+    a.omega = 1.0 / p.tau;
+    a.amp = p.rho_amp;
+    a.n_probe = p.n_probe;
     rc = lbdem_time(S, &J->t0);
     if (rc) return rc;
     rc = node_layout(S);
     if (rc) return rc;
     rc = sync_set(S);
     if (rc) return rc;
-    // frozen geometry: node map (local particle indices), particle state, start populations
-    std::vector<int32_t> own((size_t)M.ncell);
-    rc = lbdem_owner_get(S, lattice, own.data());
-    if (rc) return rc;
-    const int np = M.np;
-    std::vector<double> x(3 * (size_t)std::max(np, 1)), v(x.size()), w(x.size()), fh(x.size()), th(x.size());
-    rc = lbdem_particles_get(S, lattice, np, x.data(), v.data(), w.data(), fh.data(), th.data());
-    if (rc) return rc;
-    J->v_host.assign(v.begin(), v.begin() + 3 * np);
-    HIPCHK(hipMemcpy(J->own, own.data(), sizeof(int32_t) * own.size(), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(J->X, x.data(), sizeof(double) * x.size(), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(J->W, w.data(), sizeof(double) * w.size(), hipMemcpyHostToDevice));
-    if (np > 0) HIPCHK(hipMemcpy(J->R, S->ds.R + M.p_off, sizeof(double) * np, hipMemcpyDeviceToDevice));
-    const char *src = (const char *)((J->t0 & 1) ? S->ds.popB : S->ds.popA) + J->es * M.pop_off;
-    HIPCHK(hipMemcpy(J->f0, src, J->es * kQ * M.ncell, hipMemcpyDeviceToDevice));
+    // frozen geometry: particle state, node map and the tables of its fluid nodes
+    const int np = M.np, par = (int)(J->t0 & 1);
+    hipStream_t st = J->stream;
+    J->v_host.assign(3 * (size_t)np, 0.0);
+    if (np > 0) {
+        const size_t o3 = 3 * (size_t)M.p_off, b3 = sizeof(double) * 3 * (size_t)np;
+        HIPCHK(hipMemcpyAsync((void *)a.X, S->ds.X[par] + o3, b3, hipMemcpyDeviceToDevice, st));
+        HIPCHK(hipMemcpyAsync((void *)a.W, S->ds.W[par] + o3, b3, hipMemcpyDeviceToDevice, st));
+        HIPCHK(hipMemcpyAsync((void *)a.R, S->ds.R + M.p_off, sizeof(double) * np, hipMemcpyDeviceToDevice, st));
+        HIPCHK(hipMemcpyAsync(J->v_host.data(), S->ds.V[par] + o3, b3, hipMemcpyDeviceToHost, st));
+    }
+    HIPCHK(launch_adj_geometry(a, S->ds.own[par] + M.cell_off, st));
+    HIPCHK(hipMemcpyAsync(&a.nf, a.pbase + M.nz, sizeof(int), hipMemcpyDeviceToHost, st));
     // unit-amplitude waveform at the time levels t0+1 .. t0+nsteps, Eq. (source)
     std::vector<double> shape((size_t)nsteps);
     for (int64_t n = 0; n < nsteps; ++n) {
@@ -1611,28 +1633,19 @@ int lbdem_adj_create(lbdem_set *S, int32_t lattice, int64_t nsteps, int32_t ckpt
         }
         shape[(size_t)n] = sv;
     }
-    HIPCHK(hipMemcpy(J->shape, shape.data(), sizeof(double) * shape.size(), hipMemcpyHostToDevice));
-    if (p.n_probe > 0) HIPCHK(hipMemcpy(J->pz, p.probe_z, sizeof(int) * p.n_probe, hipMemcpyHostToDevice));
-    AdjDev &a = J->a;
-    a.M = M;
-    a.ncell = (int)M.ncell;
-    a.own = J->own;
-    a.X = J->X; a.W = J->W; a.R = J->R; a.V = J->vdev;
-    a.np = np;
-    a.rho_f = p.rho_f;
-    a.omega = 1.0 / p.tau;
-    a.amp = p.rho_amp;
-    a.shape = J->shape;
-    a.n_probe = p.n_probe;
-    a.probe_z = J->pz;
-    a.probe_nfl = J->nfl;
-    a.P = J->P;
-    a.dLdP = J->dLdP;
-    a.acc_w = J->accw; a.acc_a = J->acca;
-    a.macc = J->macc;
-    a.gv = J->gv;
-    HIPCHK(launch_adj_nfl(a, J->nfl, J->stream));
-    HIPCHK(hipStreamSynchronize(J->stream));
+    HIPCHK(hipMemcpyAsync(J->shape, shape.data(), sizeof(double) * shape.size(), hipMemcpyHostToDevice, st));
+    std::vector<short> pzm((size_t)M.nz, (short)-1);
+    for (int k = 0; k < p.n_probe; ++k) pzm[(size_t)p.probe_z[k]] = (short)k;
+    HIPCHK(hipMemcpyAsync((void *)a.pzm, pzm.data(), sizeof(short) * pzm.size(), hipMemcpyHostToDevice, st));
+    if (p.n_probe > 0)
+        HIPCHK(hipMemcpyAsync((void *)a.probe_z, p.probe_z, sizeof(int) * p.n_probe, hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));
+    // (whole waves, unless the rounding would take an array past the 4 GiB of a 32-bit offset)
+    a.ns = (a.nf + 63) / 64 * 64;
+    if ((unsigned long long)kQ * (unsigned long long)a.ns * J->es >= (1ULL << 32)) a.ns = a.nf;
+    const char *src = (const char *)(par ? S->ds.popB : S->ds.popA) + J->es * M.pop_off;
+    HIPCHK(launch_adj_start(J->prec, a, src, J->f0, st));
+    HIPCHK(hipStreamSynchronize(st));
     *out = J.release();
     return LBDEM_OK;
 }
@@ -1642,24 +1655,33 @@ int lbdem_adj_forward(lbdem_adj *J, double tau, double amp, const double *v, dou
     if (!J) return fail(LBDEM_EINVAL, "null adjoint window");
     if (!(tau > 0.5)) return fail(LBDEM_EINVAL, "tau must exceed 1/2");
     AdjDev &a = J->a;
-    const size_t st = (size_t)kQ * a.ncell * J->es;
+    const size_t st = J->state_bytes();
     J->tau = tau;
+    J->have_forward = false;
+    J->seg_at = -1;
     a.omega = 1.0 / tau;
     a.amp = amp;
-    const std::vector<double> &vv = v ? std::vector<double>(v, v + 3 * a.np) : J->v_host;
-    if (a.np > 0) HIPCHK(hipMemcpyAsync(J->vdev, vv.data(), sizeof(double) * 3 * a.np, hipMemcpyHostToDevice, J->stream));
-    char *cur = J->seg, *nxt = J->seg + st;
-    HIPCHK(hipMemcpyAsync(cur, J->f0, st, hipMemcpyDeviceToDevice, J->stream));
+    if (a.np > 0) {
+        HIPCHK(hipMemcpyAsync(J->vdev, v ? v : J->v_host.data(), sizeof(double) * 3 * a.np, hipMemcpyHostToDevice,
+                              J->stream));
+        HIPCHK(launch_adj_wall(J->prec, a, J->stream));
+    }
+    // The states between checkpoints alternate between two buffers, which stay in the
+    // caches, but those of the last segment are kept for the backward pass.
+    const int64_t last = (int64_t)(J->nck - 1) * J->ck;
+    auto state = [&](int64_t n) {
+        if (n % J->ck == 0) return J->start_of((int)(n / J->ck));
+        return J->seg + st * (size_t)(n > last ? n - last : (n & 1));
+    };
     for (int64_t n = 0; n < J->nsteps; ++n) {
-        if (n % J->ck == 0)
-            HIPCHK(hipMemcpyAsync(J->ckp + st * (size_t)(n / J->ck), cur, st, hipMemcpyDeviceToDevice, J->stream));
-        if (a.n_probe > 0) HIPCHK(launch_adj_probe(J->prec, a, cur, (int)n, J->stream));
-        HIPCHK(launch_adj_step(J->prec, a, cur, nxt, (int)n, J->stream));
-        std::swap(cur, nxt);
+        const int m = (int)(n % J->ck);
+        HIPCHK(launch_adj_step(J->prec, a, state(n), n + 1 < J->nsteps ? state(n + 1) : nullptr, (int)n, m, J->stream));
+        if (m == J->ck - 1 || n + 1 == J->nsteps) HIPCHK(launch_adj_signal(a, (int)n - m, m + 1, J->stream));
     }
     if (probes && a.n_probe > 0)
-        HIPCHK(hipMemcpyAsync(probes, J->P, sizeof(double) * J->nsteps * a.n_probe, hipMemcpyDeviceToHost, J->stream));
+        HIPCHK(hipMemcpyAsync(probes, a.P, sizeof(double) * J->nsteps * a.n_probe, hipMemcpyDeviceToHost, J->stream));
     HIPCHK(hipStreamSynchronize(J->stream));
+    J->seg_at = J->nck - 1;
     J->have_forward = true;
     return LBDEM_OK;
 }
@@ -1669,35 +1691,47 @@ int lbdem_adj_backward(lbdem_adj *J, const double *dL_dP, double *dL_dtau, doubl
     if (!J) return fail(LBDEM_EINVAL, "null adjoint window");
     if (!J->have_forward) return fail(LBDEM_ESTATE, "lbdem_adj_forward must run first");
     AdjDev &a = J->a;
-    const size_t st = (size_t)kQ * a.ncell * J->es, sl = (size_t)kQ * a.ncell * J->cs;
+    const size_t st = J->state_bytes(), sl = (size_t)kQ * a.ns * J->cs;
     const int nblk = adj_blocks(a);
     if (a.n_probe > 0) {
         if (!dL_dP) return fail(LBDEM_EINVAL, "null loss gradient");
-        HIPCHK(hipMemcpyAsync(J->dLdP, dL_dP, sizeof(double) * J->nsteps * a.n_probe, hipMemcpyHostToDevice, J->stream));
+        HIPCHK(hipMemcpyAsync((void *)a.dLdP, dL_dP, sizeof(double) * J->nsteps * a.n_probe, hipMemcpyHostToDevice,
+                              J->stream));
     }
-    HIPCHK(hipMemsetAsync(J->lam0, 0, sl, J->stream));
-    HIPCHK(hipMemsetAsync(J->accw, 0, sizeof(double) * nblk, J->stream));
-    HIPCHK(hipMemsetAsync(J->acca, 0, sizeof(double) * nblk, J->stream));
-    HIPCHK(hipMemsetAsync(J->macc, 0, sizeof(double) * (kQ - 1) * (size_t)a.ncell, J->stream));
+    // (both adjoint fields: the elements that leave through a density face are never written)
+    if (nblk > 0) {
+        HIPCHK(hipMemsetAsync(J->lam0, 0, sl, J->stream));
+        HIPCHK(hipMemsetAsync(J->lam1, 0, sl, J->stream));
+        HIPCHK(hipMemsetAsync(a.acc_w, 0, sizeof(double) * nblk, J->stream));
+        HIPCHK(hipMemsetAsync(a.acc_a, 0, sizeof(double) * nblk, J->stream));
+    }
+    int nlink = 0;
+    HIPCHK(hipMemcpyAsync(&nlink, a.nlink, sizeof(int), hipMemcpyDeviceToHost, J->stream));
+    HIPCHK(hipStreamSynchronize(J->stream));
+    if (nlink > 0) HIPCHK(hipMemsetAsync(a.macc, 0, sizeof(double) * (size_t)nlink, J->stream));
     char *lam = J->lam0, *lam_next = J->lam1;
     for (int s = J->nck - 1; s >= 0; --s) {
         const int64_t start = (int64_t)s * J->ck;
         const int64_t len = std::min<int64_t>(J->ck, J->nsteps - start);
+        auto state = [&](int64_t m) { return m == 0 ? J->start_of(s) : J->seg + st * (size_t)m; };
         // recompute the segment's states from its checkpoint
-        HIPCHK(hipMemcpyAsync(J->seg, J->ckp + st * (size_t)s, st, hipMemcpyDeviceToDevice, J->stream));
-        for (int64_t m = 0; m + 1 < len; ++m)
-            HIPCHK(launch_adj_step(J->prec, a, J->seg + st * (size_t)m, J->seg + st * (size_t)(m + 1), (int)(start + m),
-                                   J->stream));
+        if (J->seg_at != s) {
+            J->seg_at = -1;
+            for (int64_t m = 0; m + 1 < len; ++m)
+                HIPCHK(launch_adj_step(J->prec, a, state(m), state(m + 1), (int)(start + m), (int)m, J->stream));
+            J->seg_at = s;
+        }
         for (int64_t m = len - 1; m >= 0; --m) {
-            HIPCHK(launch_adj_mu(J->prec, a, J->seg + st * (size_t)m, lam, J->mu, (int)(start + m), J->stream));
-            HIPCHK(launch_adj_pull(J->prec, a, J->mu, lam_next, J->stream));
+            HIPCHK(launch_adj_back(J->prec, a, state(m), lam, lam_next, (int)(start + m), J->stream));
             std::swap(lam, lam_next);
         }
     }
     HIPCHK(launch_adj_vgrad(a, J->stream));
     std::vector<double> aw(nblk), aa(nblk);
-    HIPCHK(hipMemcpyAsync(aw.data(), J->accw, sizeof(double) * nblk, hipMemcpyDeviceToHost, J->stream));
-    HIPCHK(hipMemcpyAsync(aa.data(), J->acca, sizeof(double) * nblk, hipMemcpyDeviceToHost, J->stream));
+    if (nblk > 0) {
+        HIPCHK(hipMemcpyAsync(aw.data(), a.acc_w, sizeof(double) * nblk, hipMemcpyDeviceToHost, J->stream));
+        HIPCHK(hipMemcpyAsync(aa.data(), a.acc_a, sizeof(double) * nblk, hipMemcpyDeviceToHost, J->stream));
+    }
     if (dL_dv && a.np > 0)
         HIPCHK(hipMemcpyAsync(dL_dv, J->gv, sizeof(double) * 3 * a.np, hipMemcpyDeviceToHost, J->stream));
     HIPCHK(hipStreamSynchronize(J->stream));

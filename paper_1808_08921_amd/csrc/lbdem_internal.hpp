@@ -181,11 +181,20 @@ struct DevSet {
     unsigned int *flags;
 };
 
-// Adjoint window over frozen geometry (one lattice): device view.
+// Adjoint window over frozen geometry (one lattice): device view.  Populations and adjoint
+// fields are [19][ns] over the window's slots (its fluid nodes, x fastest).
 struct AdjDev {
     MemberDev M;              // the lattice's constants (offsets relative to this lattice)
     int ncell;
-    const int *own;           // frozen node map, local particle indices [ncell]
+    int nf, ns;               // fluid nodes, and that rounded up to whole waves
+    int *own;                 // frozen node map, local particle indices [ncell]
+    uint2 *rows;              // per 32 nodes of a row: fluid bits, slot of the first fluid node [nz*ny*nw]
+    int *pbase;               // first slot of each plane, then the number of fluid nodes [nz + 1]
+    int *node;                // cell of each slot [nf]
+    uint2 *mask;              // per slot: bounce-back directions, link directions [nf]
+    int *loff;                // per slot: where its links are packed
+    int *nlink;               // links packed so far
+    void *wall;               // per link: moving-wall term of Eq. (mem) [nlink], collision precision
     const double *X, *W, *R;  // particle positions, angular velocities [np*3], radii [np]
     const double *V;          // particle velocities of the window [np*3]
     int np;
@@ -193,11 +202,14 @@ struct AdjDev {
     const double *shape;      // unit-amplitude waveform at time level t0+n+1 [nsteps]
     int n_probe;
     const int *probe_z;       // [n_probe]
+    const short *pzm;         // probe index of each plane, -1 for none [nz]
     const double *probe_nfl;  // fluid nodes per probe plane [n_probe]
+    int wpp;                  // most waves that hold nodes of one plane
+    double *part;             // waves' density sums of the probe planes [ckpt_every][n_probe][wpp]
     double *P;                // probe signals [nsteps][n_probe]
     const double *dLdP;       // loss gradient [nsteps][n_probe]
     double *acc_w, *acc_a;    // per-workgroup sums of dL/domega and dL/dA [nblk]
-    double *macc;             // summed dL/dg of every direction whose source is a particle [18][ncell]
+    double *macc;             // summed dL/dg of every link [nlink]
     double *gv;               // dL/dV [np*3]
 };
 
@@ -228,12 +240,13 @@ int links_block();
 int motion_grid(const DevSet &s);
 int remap_grid(const DevSet &s);
 // adjoint window kernels (lbdem_kernels.hip)
-hipError_t launch_adj_step(int prec, const AdjDev &a, const void *fin, void *fout, int n, hipStream_t st);
-hipError_t launch_adj_probe(int prec, const AdjDev &a, const void *fin, int n, hipStream_t st);
-hipError_t launch_adj_mu(int prec, const AdjDev &a, const void *fin, const void *lam, void *mu, int n, hipStream_t st);
-hipError_t launch_adj_pull(int prec, const AdjDev &a, const void *mu, void *lam, hipStream_t st);
+hipError_t launch_adj_geometry(const AdjDev &a, const int *own, hipStream_t st);
+hipError_t launch_adj_start(int prec, const AdjDev &a, const void *src, void *dst, hipStream_t st);
+hipError_t launch_adj_wall(int prec, const AdjDev &a, hipStream_t st);
+hipError_t launch_adj_step(int prec, const AdjDev &a, const void *fin, void *fout, int n, int m, hipStream_t st);
+hipError_t launch_adj_signal(const AdjDev &a, int n0, int count, hipStream_t st);
+hipError_t launch_adj_back(int prec, const AdjDev &a, const void *fin, const void *lam, void *out, int n, hipStream_t st);
 hipError_t launch_adj_vgrad(const AdjDev &a, hipStream_t st);
-hipError_t launch_adj_nfl(const AdjDev &a, double *nfl, hipStream_t st);
 int adj_blocks(const AdjDev &a);
 
 

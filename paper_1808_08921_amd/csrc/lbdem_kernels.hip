@@ -3088,51 +3088,32 @@ __global__ __launch_bounds__(256) void k_expand(DevSet s)
 // state as in the coupled fluid kernel.  Its discrete adjoint propagates a loss gradient
 // on the probe signals backwards: lambda^n = (dS/df^n)^T lambda^{n+1} + dL/df^n.
 
-// Pre-face populations g0 (deviation form) of fluid node (i, j, k) from the state fin,
-// and the unknown directions of a density face; the moving-wall term of Eq. (mem) uses
-// V_b . c_d = c_d . (V + Omega x (x - X)) of the source's particle.
-template <int P>
-__device__ __forceinline__ unsigned adj_gather(const AdjDev &a, const typename Prec<P>::S *fin, int i, int j, int k,
-                                               int cell, typename Prec<P>::C (&g)[kQ])
+//
+// The geometry is frozen, so the window works on its fluid nodes alone, numbered by slot
+// with x fastest, with one occupancy word and the slot of the word's first node per 32 nodes
+// of a row (the row table).  Along a row fluid nodes hold consecutive slots, so the
+// 18 sources of a node come from nine row words.  A slot carries the directions that bounce
+// back (mask.x) and those of them whose source lies in a particle (mask.y), the link
+// directions; per link, packed in slot order from loff, the term of the moving wall (wall,
+// filled once per forward) and the sum of dL/dg0 over the window (macc).
+// Bound by HBM: a forward step reads and writes 19 populations a fluid node, an adjoint step
+// reads 19 populations and 19 adjoint values and writes 19.  On the 64 x 64 x 256 packing of
+// 275 spheres (459 000 fluid nodes, FP64) a forward step takes 29 us (28 at the rate of a
+// device copy) and an adjoint step 65 us (48, of which 6 for the link sums); FP32 18 and
+// 52 us.  One thread per cell of the lattice with an owner lookup per direction, probe sums
+// by one workgroup per plane and mu and lambda in two kernels took 187 + 493 and 837 + 105
+// us.  (Holding the adjoint step to 168 VGPRs for a third wave per SIMD spills: 127 us.)
+
+__device__ __forceinline__ int adj_unknown(const AdjDev &a, int k)
 {
-    using C = typename Prec<P>::C;
-    const MemberDev &M = a.M;
-    const int nx = M.nx, ny = M.ny, nz = M.nz, nc = a.ncell;
-    const int dims[3] = {nx, ny, nz};
-    unsigned unk = 0u;
+    // the directions a density face leaves unknown: c_z = +1 at the lower face, -1 at the upper
+    int m = 0;
 #pragma unroll
     for (int e = 0; e < kQ - 1; ++e) {
-        int c[3] = {i - kCX[e], j - kCY[e], k - kCZ[e]};
-        int kind = 0; // 0 node, 1 wall, 2 unknown
-        for (int ax = 0; ax < 3; ++ax) {
-            if (c[ax] < 0 || c[ax] >= dims[ax]) {
-                const int f = M.bc[2 * ax + (c[ax] >= dims[ax] ? 1 : 0)];
-                if (f == BC_PRESSURE) kind = 2;
-                else if (f == BC_WALL) kind = max(kind, 1);
-                else c[ax] = c[ax] < 0 ? c[ax] + dims[ax] : c[ax] - dims[ax];
-            }
-        }
-        const int d = kOPP[e];
-        if (kind == 2) { g[e] = C(0); unk |= 1u << e; continue; }
-        if (kind == 1) { g[e] = decode_dev<P>(fin[d * nc + cell], d, a.rho_f); continue; }
-        const int sc = (c[2] * ny + c[1]) * nx + c[0];
-        const int q = a.own[sc];
-        if (q < 0) { g[e] = decode_dev<P>(fin[e * nc + sc], e, a.rho_f); continue; }
-        // (on a narrow lattice, from the link's midpoint, which fixes the image, as group_arm)
-        const double h0 = M.narrow ? 0.5 * kCX[e] : 0.0, h1 = M.narrow ? 0.5 * kCY[e] : 0.0,
-                     h2 = M.narrow ? 0.5 * kCZ[e] : 0.0;
-        const double r0 = mimg(((double)i - h0) - a.X[3 * q], M.per[0], M.box[0]) + h0;
-        const double r1 = mimg(((double)j - h1) - a.X[3 * q + 1], M.per[1], M.box[1]) + h1;
-        const double r2 = mimg(((double)k - h2) - a.X[3 * q + 2], M.per[2], M.box[2]) + h2;
-        const double *V = a.V + 3 * q, *W = a.W + 3 * q;
-        const double u0 = V[0] + (W[1] * r2 - W[2] * r1);
-        const double u1 = V[1] + (W[2] * r0 - W[0] * r2);
-        const double u2 = V[2] + (W[0] * r1 - W[1] * r0);
-        const double cu = (double)kCX[d] * u0 + (double)kCY[d] * u1 + (double)kCZ[d] * u2;
-        g[e] = decode_dev<P>(fin[d * nc + cell], d, a.rho_f) - (C)(kMW[d] * a.rho_f) * (C)cu;
+        if (kCZ[e] > 0 && k == 0 && a.M.bc[4] == BC_PRESSURE) m |= 1 << e;
+        if (kCZ[e] < 0 && k == a.M.nz - 1 && a.M.bc[5] == BC_PRESSURE) m |= 1 << e;
     }
-    g[18] = decode_dev<P>(fin[18 * nc + cell], 18, a.rho_f);
-    return unk;
+    return m;
 }
 
 __device__ __forceinline__ void adj_coords(const AdjDev &a, int cell, int &i, int &j, int &k)
@@ -3144,22 +3125,298 @@ __device__ __forceinline__ void adj_coords(const AdjDev &a, int cell, int &i, in
     i = rem - j * a.M.nx;
 }
 
-// One frozen forward step fin -> fout.
-template <int P>
-__global__ __launch_bounds__(256) void k_adj_step(AdjDev a, const typename Prec<P>::S *fin, typename Prec<P>::S *fout, int n)
+// The source of direction e of cell (i, j, k): its cell index, or -1 for a wall, -2 for a
+// source outside a density face.
+__device__ __forceinline__ int adj_source_cell(const AdjDev &a, int e, int i, int j, int k)
 {
-    const double drho_in = a.amp * a.shape[n];
+    const MemberDev &M = a.M;
+    const int dims[3] = {M.nx, M.ny, M.nz};
+    int c[3] = {i - kCXd[e], j - kCYd[e], k - kCZd[e]};
+    int kind = 0;
+    for (int ax = 0; ax < 3; ++ax) {
+        if (c[ax] < 0 || c[ax] >= dims[ax]) {
+            const int f = M.bc[2 * ax + (c[ax] >= dims[ax] ? 1 : 0)];
+            if (f == BC_PRESSURE) kind = 2;
+            else if (f == BC_WALL) kind = max(kind, 1);
+            else c[ax] = c[ax] < 0 ? c[ax] + dims[ax] : c[ax] - dims[ax];
+        }
+    }
+    if (kind != 0) return -kind;
+    return (c[2] * dims[1] + c[1]) * dims[0] + c[0];
+}
+
+// Sum of v over the threads before this one in the workgroup (256 threads) and the total.
+__device__ __forceinline__ int block_scan(int v, int &total, int *cnt4)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int inc = v;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+    }
+    if (lane == 63) cnt4[wv] = inc;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < wv; ++w) before += cnt4[w];
+    total = cnt4[0] + cnt4[1] + cnt4[2] + cnt4[3];
+    __syncthreads();
+    return before + inc - v;
+}
+
+// Window set-up (1): frozen node map with local particle indices, occupancy words, and the
+// number of fluid nodes of each plane; one workgroup per plane.
+__global__ __launch_bounds__(256) void k_adj_rows(AdjDev a, const int *own)
+{
+    __shared__ int cnt4[4];
+    const int z = blockIdx.x, nx = a.M.nx, ny = a.M.ny, nxy = nx * ny, nw = a.M.nw;
+    for (int c = threadIdx.x; c < nxy; c += 256) {
+        const int o = own[z * nxy + c];
+        a.own[z * nxy + c] = o < 0 ? -1 : o - a.M.p_off;
+    }
+    int count = 0;
+    for (int w = threadIdx.x; w < ny * nw; w += 256) {
+        const int j = w / nw, x0 = (w - j * nw) * 32;
+        unsigned bits = 0u;
+        for (int b = 0; b < min(32, nx - x0); ++b)
+            if (own[z * nxy + j * nx + x0 + b] < 0) bits |= 1u << b;
+        a.rows[z * ny * nw + w] = make_uint2(bits, 0u);
+        count += __popc(bits);
+    }
+    int total;
+    (void)block_scan(count, total, cnt4);
+    if (threadIdx.x == 0) a.pbase[z] = total;
+}
+
+// (2) first slot of each plane; pbase[nz] the number of fluid nodes, nlink cleared.
+__global__ __launch_bounds__(256) void k_adj_planes(AdjDev a)
+{
+    __shared__ int cnt4[4];
+    int run = 0;
+    for (int z0 = 0; z0 < a.M.nz; z0 += 256) {
+        const int z = z0 + (int)threadIdx.x;
+        int total;
+        const int before = block_scan(z < a.M.nz ? a.pbase[z] : 0, total, cnt4);
+        if (z < a.M.nz) a.pbase[z] = run + before;
+        run += total;
+    }
+    if (threadIdx.x == 0) {
+        a.pbase[a.M.nz] = run;
+        *a.nlink = 0;
+    }
+}
+
+// (3) slots of the row words and the node of each slot; one workgroup per plane.
+__global__ __launch_bounds__(256) void k_adj_slots(AdjDev a)
+{
+    __shared__ int cnt4[4];
+    const int z = blockIdx.x, nx = a.M.nx, ny = a.M.ny, nxy = nx * ny, nw = a.M.nw;
+    int run = a.pbase[z];
+    for (int w0 = 0; w0 < ny * nw; w0 += 256) {
+        const int w = w0 + (int)threadIdx.x;
+        const unsigned bits = w < ny * nw ? a.rows[z * ny * nw + w].x : 0u;
+        int total;
+        int at = run + block_scan(__popc(bits), total, cnt4);
+        if (w < ny * nw) {
+            a.rows[z * ny * nw + w].y = (unsigned)at;
+            const int j = w / nw, x0 = (w - j * nw) * 32;
+            for (unsigned m = bits; m; m &= m - 1u) a.node[at++] = z * nxy + j * nx + x0 + __ffs(m) - 1;
+        }
+        run += total;
+    }
+}
+
+// (4) bounce-back and link directions of each slot, and where its links are packed (the
+// waves take their ranges in any order: only sums of a link's own values depend on it).
+__global__ __launch_bounds__(256) void k_adj_masks(AdjDev a)
+{
+    const int r = blockIdx.x * 256 + (int)threadIdx.x, lane = threadIdx.x & 63;
+    unsigned back = 0u, link = 0u;
+    if (r < a.nf) {
+        int i, j, k;
+        adj_coords(a, a.node[r], i, j, k);
+        for (int e = 0; e < kQ - 1; ++e) {
+            const int sc = adj_source_cell(a, e, i, j, k);
+            if (sc == -1) back |= 1u << e;
+            else if (sc >= 0 && a.own[sc] >= 0) { back |= 1u << e; link |= 1u << e; }
+        }
+    }
+    const int n = __popc(link);
+    int inc = n;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+    }
+    int base = 0;
+    if (lane == 63) base = atomicAdd(a.nlink, inc);
+    base = __shfl(base, 63, 64);
+    if (r >= a.nf) return;
+    a.mask[r] = make_uint2(back, link);
+    a.loff[r] = base + inc - n;
+}
+
+// (5) the start populations (node layout, stride ncell) at their slots.
+template <typename T>
+__global__ __launch_bounds__(256) void k_adj_start(AdjDev a, const T *src, T *dst)
+{
+    const int r = blockIdx.x * 256 + (int)threadIdx.x;
+    if (r >= a.nf) return;
+    const int cell = a.node[r];
+    for (int d = 0; d < kQ; ++d) dst[(size_t)d * a.ns + r] = src[(size_t)d * a.ncell + cell];
+}
+
+// Per forward: the moving-wall term of Eq. (mem) of every link, 2 (w_d / c_s^2) rho_f V_b . c_d
+// with V_b . c_d = c_d . (V + Omega x (x - X)) of the source's particle.
+template <int P>
+__global__ __launch_bounds__(256) void k_adj_wall(AdjDev a)
+{
     using C = typename Prec<P>::C;
-    const int cell = blockIdx.x * blockDim.x + threadIdx.x;
-    if (cell >= a.ncell || a.own[cell] >= 0) return;
+    const int r = blockIdx.x * 256 + (int)threadIdx.x;
+    if (r >= a.nf) return;
+    const unsigned link = a.mask[r].y;
+    if (link == 0u) return;
+    const MemberDev &M = a.M;
     int i, j, k;
-    adj_coords(a, cell, i, j, k);
+    adj_coords(a, a.node[r], i, j, k);
+    C *w = static_cast<C *>(a.wall) + a.loff[r];
+    for (unsigned m = link; m; m &= m - 1u) {
+        const int e = __ffs(m) - 1;
+        const int q = a.own[adj_source_cell(a, e, i, j, k)];
+        // (on a narrow lattice, from the link's midpoint, which fixes the image, as group_arm)
+        const double h0 = M.narrow ? 0.5 * kCXd[e] : 0.0, h1 = M.narrow ? 0.5 * kCYd[e] : 0.0,
+                     h2 = M.narrow ? 0.5 * kCZd[e] : 0.0;
+        const double r0 = mimg(((double)i - h0) - a.X[3 * q], M.per[0], M.box[0]) + h0;
+        const double r1 = mimg(((double)j - h1) - a.X[3 * q + 1], M.per[1], M.box[1]) + h1;
+        const double r2 = mimg(((double)k - h2) - a.X[3 * q + 2], M.per[2], M.box[2]) + h2;
+        const double *V = a.V + 3 * q, *W = a.W + 3 * q;
+        const double u0 = V[0] + (W[1] * r2 - W[2] * r1);
+        const double u1 = V[1] + (W[2] * r0 - W[0] * r2);
+        const double u2 = V[2] + (W[0] * r1 - W[1] * r0);
+        // c_d = -c_e
+        const double cu = -(double)kCXd[e] * u0 - (double)kCYd[e] * u1 - (double)kCZd[e] * u2;
+        *w++ = (C)((e < 6 ? kMW[0] : kMW[6]) * a.rho_f) * (C)cu;
+    }
+}
+
+// Element of the population arrays each direction of slot r is pulled from: f~_e at the
+// source, or f~_{e*} at r itself from a wall or a particle (for an unknown direction of a
+// density face: its own element, whose value is not used).
+__device__ __forceinline__ void adj_sources(const AdjDev &a, int i, int j, int k, unsigned r, unsigned back, unsigned unk,
+                                            unsigned (&idx)[kQ - 1])
+{
+    const int nx = a.M.nx, ny = a.M.ny, nz = a.M.nz, nw = a.M.nw, per_x = a.M.per[0];
+    const unsigned ns = (unsigned)a.ns, b = 1u << (i & 31);
+    const int wx = (i == 0) ? nx - 1 : 0; // the x neighbour across a periodic face
+    const unsigned bw = 1u << (wx & 31);
+    uint2 wv[9], ww[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const int row = (wrapc(k + q % 3 - 1, nz) * ny + wrapc(j + q / 3 - 1, ny)) * nw;
+        wv[q] = a.rows[row + (i >> 5)];
+        ww[q] = per_x ? a.rows[row + (wx >> 5)] : make_uint2(0u, 0u);
+    }
+#pragma unroll
+    for (int e = 0; e < kQ - 1; ++e) {
+        const int q = (1 - kCY[e]) * 3 + (1 - kCZ[e]);
+        const unsigned rk = wv[q].y + (unsigned)__popc(wv[q].x & (b - 1u));
+        unsigned v;
+        if (kCX[e] == 0) {
+            v = rk;
+        } else {
+            const unsigned rwr = ww[q].y + (unsigned)__popc(ww[q].x & (bw - 1u));
+            if (kCX[e] < 0) v = (i < nx - 1) ? rk + ((wv[q].x & b) ? 1u : 0u) : rwr;
+            else v = (i > 0) ? rk - 1u : rwr;
+        }
+        const unsigned far = (unsigned)e * ns + v;
+        idx[e] = ((back >> e) & 1u) ? (unsigned)kOPP[e] * ns + r : (((unk >> e) & 1u) ? (unsigned)e * ns + r : far);
+    }
+}
+
+// Element idx of a window's [19][ns] array.  FP64 and FP32 arrays stay below 4 GiB (as the
+// set's), so a 32-bit byte offset from a scalar base reaches them.  A 16-bit set's FP32
+// adjoint fields can be larger.
+template <int P, typename T>
+__device__ __forceinline__ T adj_ld(const T *base, unsigned idx)
+{
+    if constexpr (P == PREC_FP64 || P == PREC_FP32) return ldo(base, idx);
+    else return base[idx];
+}
+template <int P, typename T>
+__device__ __forceinline__ void adj_st(T *base, unsigned idx, T v)
+{
+    if constexpr (P == PREC_FP64 || P == PREC_FP32) sto(base, idx, v);
+    else base[idx] = v;
+}
+
+// Pre-collision populations (deviations from the rest state) of slot r, density faces
+// included, pulled from the state fin.  ALL: the moving-wall terms are loaded for every
+// direction at once instead of behind a branch per direction; the adjoint step, whose waves
+// are few (212 VGPRs), gains by it (72.6 -> 65.3 us), the forward step does not (29.3 -> 30.8).
+template <int P, bool ALL>
+__device__ __forceinline__ void adj_gather(const AdjDev &a, const typename Prec<P>::S *fin, int k, unsigned r,
+                                           const unsigned (&idx)[kQ - 1], unsigned link, unsigned unk, int n,
+                                           typename Prec<P>::C (&g)[kQ])
+{
+    using C = typename Prec<P>::C;
+    using S = typename Prec<P>::S;
+    S raw[kQ];
+#pragma unroll
+    for (int e = 0; e < kQ - 1; ++e) raw[e] = adj_ld<P>(fin, idx[e]);
+    raw[kQ - 1] = adj_ld<P>(fin, (unsigned)(kQ - 1) * (unsigned)a.ns + r);
+#pragma unroll
+    for (int e = 0; e < kQ; ++e) g[e] = ((unk >> e) & 1u) ? C(0) : decode_dev<P>(raw[e], e, a.rho_f);
+    if (link) {
+        const C *w = static_cast<const C *>(a.wall) + a.loff[r];
+        if constexpr (ALL) {
+            // (a lane without a link at e reads the next link's term, or past the last one
+            // within the array's capacity)
+            C t[kQ - 1];
+#pragma unroll
+            for (int e = 0; e < kQ - 1; ++e) t[e] = w[__popc(link & ((1u << e) - 1u))];
+#pragma unroll
+            for (int e = 0; e < kQ - 1; ++e) g[e] -= ((link >> e) & 1u) ? t[e] : C(0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < kQ - 1; ++e)
+                if ((link >> e) & 1u) g[e] -= w[__popc(link & ((1u << e) - 1u))];
+        }
+    }
+    if (k == 0 && a.M.bc[4] == BC_PRESSURE) zou_he<C>(g, (C)(a.amp * a.shape[n]), false);
+    if (k == a.M.nz - 1 && a.M.bc[5] == BC_PRESSURE) zou_he<C>(g, C(0), true);
+}
+
+// One frozen forward step fin -> fout (no store after the window's last step, whose end
+// state nothing reads), and per wave of a probe plane its sum of rho - rho_f before the
+// collision, at row m of the partial sums.
+template <int P>
+__global__ __launch_bounds__(256) void k_adj_step(AdjDev a, const typename Prec<P>::S *fin, typename Prec<P>::S *fout,
+                                                  int n, int m)
+{
+    using C = typename Prec<P>::C;
+    const int blk = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
+    const unsigned r = (unsigned)blk * 256 + threadIdx.x;
+    const bool on = (int)r < a.nf;
+    int i = 0, j = 0, k = 0;
+    if (on) adj_coords(a, a.node[r], i, j, k);
+    const int pidx = on ? a.pzm[k] : -1;
+    if (!fout && __ballot(pidx >= 0) == 0ull) return;
+    const uint2 mk = on ? a.mask[r] : make_uint2(0x3ffffu, 0u);
+    const unsigned unk = (unsigned)adj_unknown(a, k);
+    unsigned idx[kQ - 1];
+    adj_sources(a, i, j, k, on ? r : 0u, mk.x, unk, idx);
     C f[kQ];
-    adj_gather<P>(a, fin, i, j, k, cell, f);
-    if (k == 0 && a.M.bc[4] == BC_PRESSURE) zou_he<C>(f, (C)drho_in, false);
-    if (k == a.M.nz - 1 && a.M.bc[5] == BC_PRESSURE) zou_he<C>(f, C(0), true);
+    adj_gather<P, false>(a, fin, k, on ? r : 0u, idx, mk.y, unk, n, f);
     C drho, jx, jy, jz;
     moments<C>(f, drho, jx, jy, jz);
+    // the wave's sum for each probe plane it holds nodes of
+    for (unsigned long long left = __ballot(pidx >= 0); left != 0ull;) {
+        const int lead = __ffsll((long long)left) - 1, kk = __shfl(k, lead, 64), pp = __shfl(pidx, lead, 64);
+        const bool mine = pidx == pp;
+        const double sum = wave_sum(mine ? (double)drho : 0.0);
+        if ((int)(threadIdx.x & 63) == lead)
+            a.part[((size_t)m * a.n_probe + pp) * a.wpp + ((int)(r >> 6) - (a.pbase[kk] >> 6))] = sum;
+        left &= ~__ballot(mine);
+    }
+    if (!fout || !on) return;
     const C rho = (C)a.rho_f + drho;
     const C ux = jx / rho, uy = jy / rho, uz = jz / rho;
     const C uu = ux * ux + uy * uy + uz * uz;
@@ -3167,36 +3424,21 @@ __global__ __launch_bounds__(256) void k_adj_step(AdjDev a, const typename Prec<
 #pragma unroll
     for (int d = 0; d < kQ; ++d) {
         const C fe = feq_dev<C>(d, drho, rho, ux, uy, uz, uu);
-        store_dev<P>(fout, (unsigned)(d * a.ncell + cell), d, f[d] + om * (fe - f[d]), a.rho_f);
+        store_dev<P>(fout + (size_t)d * a.ns, r, d, f[d] + om * (fe - f[d]), a.rho_f);
     }
 }
 
-// Probe signals of step n from the state f^n: one workgroup per probe plane, the plane
-// average of rho - rho_f over its fluid nodes (pre-collision, after the density faces).
-template <int P>
-__global__ __launch_bounds__(256) void k_adj_probe(AdjDev a, const typename Prec<P>::S *fin, int n)
+// Probe signals of steps n0 + m, m from m0 on: the waves' sums of each plane in order, over
+// the plane's fluid nodes; one wave per (plane, step).
+__global__ __launch_bounds__(64) void k_adj_signal(AdjDev a, int n0, int m0)
 {
-    using C = typename Prec<P>::C;
-    __shared__ double red[4][8];
-    const int kp = blockIdx.x;
-    if (kp >= a.n_probe) return;
-    const int k = a.probe_z[kp];
-    const int nxy = a.M.nx * a.M.ny;
-    double v[1] = {0.0};
-    for (int t = threadIdx.x; t < nxy; t += blockDim.x) {
-        const int cell = k * nxy + t;
-        if (a.own[cell] >= 0) continue;
-        const int j = t / a.M.nx, i = t - j * a.M.nx;
-        C f[kQ];
-        adj_gather<P>(a, fin, i, j, k, cell, f);
-        if (k == 0 && a.M.bc[4] == BC_PRESSURE) zou_he<C>(f, (C)(a.amp * a.shape[n]), false);
-        if (k == a.M.nz - 1 && a.M.bc[5] == BC_PRESSURE) zou_he<C>(f, C(0), true);
-        C drho, jx, jy, jz;
-        moments<C>(f, drho, jx, jy, jz);
-        v[0] += (double)drho;
-    }
-    block_sum<1>(v, red);
-    if (threadIdx.x == 0) a.P[(long long)n * a.n_probe + kp] = v[0] / a.probe_nfl[kp];
+    const int kp = blockIdx.x, m = m0 + (int)blockIdx.y, k = a.probe_z[kp];
+    const int s0 = a.pbase[k], s1 = a.pbase[k + 1], nwv = s1 > s0 ? ((s1 - 1) >> 6) - (s0 >> 6) + 1 : 0;
+    const double *p = a.part + ((size_t)m * a.n_probe + kp) * a.wpp;
+    double v = 0.0;
+    for (int w = threadIdx.x; w < nwv; w += 64) v += p[w];
+    v = wave_sum(v);
+    if (threadIdx.x == 0) a.P[(long long)(n0 + m) * a.n_probe + kp] = v / a.probe_nfl[kp];
 }
 
 // Fluid nodes of each probe plane (one workgroup per plane).
@@ -3215,47 +3457,55 @@ __global__ __launch_bounds__(256) void k_adj_nfl(AdjDev a, double *nfl)
 
 // Adjoint through step n at every fluid node: from lambda^{n+1} (dL/d of the post-collision
 // state) and the probe term, mu = dL/dg0 of the pre-face populations g0 of time level
-// n+1.  Collision transpose: with A = sum lambda_d w_d, B = sum lambda_d w_d c_d,
+// n+1, written straight to lambda^n: every post-collision population has one consumer, the
+// node that pulls it, so mu_e goes to the element direction e was pulled from (elements
+// that leave through a density face have none and stay zero from the start of the backward
+// pass).  Collision transpose: with A = sum lambda_d w_d, B = sum lambda_d w_d c_d,
 // Cm = sum lambda_d w_d (c_d.u) c_d, D = sum lambda_d w_d (c_d.u)^2 (lattice units,
 // 1/c_s^2 = 3), sum_d lambda_d df^eq_d/dg_e = A (1 + 1.5 u.u) - 4.5 D + (3 B + 9 Cm - 3 A u).c_e.
 // The density faces are transposed by hand from their closure formulas.  Also collected:
-// dL/domega = sum lambda_d (f^eq_d - g_d), dL/drho_in, and per node dL/dg0_e of every
-// direction whose source is a particle (for dL/dV).
+// dL/domega = sum lambda_d (f^eq_d - g_d), dL/drho_in, and dL/dg0_e of every link (for dL/dV).
 template <int P>
-__global__ __launch_bounds__(256) void k_adj_mu(AdjDev a, const typename Prec<P>::S *fin,
-                                                const typename Prec<P>::C *lam, typename Prec<P>::C *mu, int n)
+__global__ __launch_bounds__(256) void k_adj_back(AdjDev a, const typename Prec<P>::S *fin,
+                                                  const typename Prec<P>::C *lam, typename Prec<P>::C *out, int n)
 {
     using C = typename Prec<P>::C;
     __shared__ double red[4][8];
-    const int cell = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nc = a.ncell;
+    const int blk = xcd_swizzle((int)blockIdx.x, (int)gridDim.x);
+    const unsigned r = (unsigned)blk * 256 + threadIdx.x;
+    const int ns = a.ns;
     double acc[2] = {0.0, 0.0}; // dL/domega, dL/drho_in
-    if (cell < nc && a.own[cell] < 0) {
+    if ((int)r < a.nf) {
         int i, j, k;
-        adj_coords(a, cell, i, j, k);
+        adj_coords(a, a.node[r], i, j, k);
+        const int pidx = a.pzm[k];
+        const uint2 mk = a.mask[r];
+        const unsigned unk = (unsigned)adj_unknown(a, k);
+        unsigned idx[kQ - 1];
+        adj_sources(a, i, j, k, r, mk.x, unk, idx);
+        C l[kQ];
+#pragma unroll
+        for (int d = 0; d < kQ; ++d) l[d] = adj_ld<P>(lam, (unsigned)(d * ns) + r);
         C g[kQ];
-        const unsigned unk = adj_gather<P>(a, fin, i, j, k, cell, g);
+        adj_gather<P, true>(a, fin, k, r, idx, mk.y, unk, n, g);
         const int face = (k == 0 && a.M.bc[4] == BC_PRESSURE) ? 0 : ((k == a.M.nz - 1 && a.M.bc[5] == BC_PRESSURE) ? 1 : -1);
-        if (face == 0) zou_he<C>(g, (C)(a.amp * a.shape[n]), false);
-        if (face == 1) zou_he<C>(g, C(0), true);
         C drho, jx, jy, jz;
         moments<C>(g, drho, jx, jy, jz);
         const C rho = (C)a.rho_f + drho;
         const C ux = jx / rho, uy = jy / rho, uz = jz / rho;
         const C uu = ux * ux + uy * uy + uz * uz;
-        C l[kQ];
-#pragma unroll
-        for (int d = 0; d < kQ; ++d) l[d] = lam[d * nc + cell];
         C A = C(0), B0 = C(0), B1 = C(0), B2 = C(0), C0 = C(0), C1 = C(0), C2 = C(0), D = C(0);
         double gw = 0.0;
 #pragma unroll
         for (int d = 0; d < kQ; ++d) {
             const C wl = (C)kWd[d] * l[d];
-            const C cu = (C)kCX[d] * ux + (C)kCY[d] * uy + (C)kCZ[d] * uz;
+            const C cu = cdot(d, ux, uy, uz);
+            const C wc = wl * cu;
             A += wl;
-            B0 += wl * (C)kCX[d]; B1 += wl * (C)kCY[d]; B2 += wl * (C)kCZ[d];
-            C0 += wl * cu * (C)kCX[d]; C1 += wl * cu * (C)kCY[d]; C2 += wl * cu * (C)kCZ[d];
-            D += wl * cu * cu;
+            if (kCX[d] > 0) { B0 += wl; C0 += wc; } else if (kCX[d] < 0) { B0 -= wl; C0 -= wc; }
+            if (kCY[d] > 0) { B1 += wl; C1 += wc; } else if (kCY[d] < 0) { B1 -= wl; C1 -= wc; }
+            if (kCZ[d] > 0) { B2 += wl; C2 += wc; } else if (kCZ[d] < 0) { B2 -= wl; C2 -= wc; }
+            D += wc * cu;
             gw += (double)l[d] * (double)(feq_dev<C>(d, drho, rho, ux, uy, uz, uu) - g[d]);
         }
         acc[0] = gw;
@@ -3264,13 +3514,10 @@ __global__ __launch_bounds__(256) void k_adj_mu(AdjDev a, const typename Prec<P>
         const C v0 = C(3) * B0 + C(9) * C0 - C(3) * A * ux;
         const C v1 = C(3) * B1 + C(9) * C1 - C(3) * A * uy;
         const C v2 = C(3) * B2 + C(9) * C2 - C(3) * A * uz;
-        C pt = C(0);
-        for (int kp = 0; kp < a.n_probe; ++kp)
-            if (a.probe_z[kp] == k) pt += (C)(a.dLdP[(long long)n * a.n_probe + kp] / a.probe_nfl[kp]);
+        const C pt = pidx >= 0 ? (C)(a.dLdP[(long long)n * a.n_probe + pidx] / a.probe_nfl[pidx]) : C(0);
         C m[kQ];
 #pragma unroll
-        for (int e = 0; e < kQ; ++e)
-            m[e] = (C(1) - om) * l[e] + om * (base + (C)kCX[e] * v0 + (C)kCY[e] * v1 + (C)kCZ[e] * v2) + pt;
+        for (int e = 0; e < kQ; ++e) m[e] = (C(1) - om) * l[e] + om * (base + cdot(e, v0, v1, v2)) + pt;
         // density faces (paper index p -> m[p-1]); unknowns end with no dependence on g0
         if (face == 0) {
             const C av = m[4], bv = m[8], cv = m[12], dv = m[14], ev = m[16];
@@ -3302,77 +3549,34 @@ __global__ __launch_bounds__(256) void k_adj_mu(AdjDev a, const typename Prec<P>
             m[3] -= C(0.5) * Y; m[7] -= C(0.5) * Y; m[11] -= C(0.5) * Y;
             m[4] += av; m[8] += bv; m[12] += cv; m[14] += dv; m[16] += ev;
         }
-        (void)unk;
-        // moving walls: the directions whose source is a particle
-        const int dims[3] = {a.M.nx, a.M.ny, a.M.nz};
+        if (mk.y) {
+            double *q = a.macc + a.loff[r], t[kQ - 1];
 #pragma unroll
-        for (int e = 0; e < kQ - 1; ++e) {
-            int c[3] = {i - kCX[e], j - kCY[e], k - kCZ[e]};
-            bool ok = true;
-            for (int ax = 0; ax < 3; ++ax)
-                if (c[ax] < 0 || c[ax] >= dims[ax]) {
-                    if (a.M.per[ax]) c[ax] = c[ax] < 0 ? c[ax] + dims[ax] : c[ax] - dims[ax];
-                    else ok = false;
-                }
-            if (ok && a.own[(c[2] * dims[1] + c[1]) * dims[0] + c[0]] >= 0)
-                a.macc[(long long)e * nc + cell] += (double)m[e];
+            for (int e = 0; e < kQ - 1; ++e) t[e] = q[__popc(mk.y & ((1u << e) - 1u))];
+#pragma unroll
+            for (int e = 0; e < kQ - 1; ++e)
+                if ((mk.y >> e) & 1u) q[__popc(mk.y & ((1u << e) - 1u))] = t[e] + (double)m[e];
         }
 #pragma unroll
-        for (int e = 0; e < kQ; ++e) mu[e * nc + cell] = m[e];
+        for (int e = 0; e < kQ - 1; ++e)
+            if (!((unk >> e) & 1u)) adj_st<P>(out, idx[e], m[e]);
+        adj_st<P>(out, (unsigned)((kQ - 1) * ns) + r, m[kQ - 1]);
     }
     block_sum<2>(acc, red);
     if (threadIdx.x == 0) {
-        a.acc_w[blockIdx.x] += acc[0];
-        a.acc_a[blockIdx.x] += acc[1];
+        a.acc_w[blk] += acc[0];
+        a.acc_a[blk] += acc[1];
     }
-}
-
-// lambda^n from mu: every post-collision population f~_e(y) has one consumer, the node
-// y + c_e pulling direction e, or y itself bouncing it back from a wall or a particle;
-// populations leaving through a density face have none.
-template <int P>
-__global__ __launch_bounds__(256) void k_adj_pull(AdjDev a, const typename Prec<P>::C *mu, typename Prec<P>::C *lam)
-{
-    using C = typename Prec<P>::C;
-    const int cell = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nc = a.ncell;
-    if (cell >= nc) return;
-    if (a.own[cell] >= 0) {
-#pragma unroll
-        for (int e = 0; e < kQ; ++e) lam[e * nc + cell] = C(0);
-        return;
-    }
-    int i, j, k;
-    adj_coords(a, cell, i, j, k);
-    const int dims[3] = {a.M.nx, a.M.ny, a.M.nz};
-#pragma unroll
-    for (int e = 0; e < kQ - 1; ++e) {
-        int c[3] = {i + kCX[e], j + kCY[e], k + kCZ[e]};
-        int kind = 0;
-        for (int ax = 0; ax < 3; ++ax) {
-            if (c[ax] < 0 || c[ax] >= dims[ax]) {
-                const int f = a.M.bc[2 * ax + (c[ax] >= dims[ax] ? 1 : 0)];
-                if (f == BC_PRESSURE) kind = 2;
-                else if (f == BC_WALL) kind = max(kind, 1);
-                else c[ax] = c[ax] < 0 ? c[ax] + dims[ax] : c[ax] - dims[ax];
-            }
-        }
-        C v = C(0);
-        if (kind == 1) v = mu[kOPP[e] * nc + cell];
-        else if (kind == 0) {
-            const int x = (c[2] * dims[1] + c[1]) * dims[0] + c[0];
-            v = (a.own[x] >= 0) ? mu[kOPP[e] * nc + cell] : mu[e * nc + x];
-        }
-        lam[e * nc + cell] = v;
-    }
-    lam[18 * nc + cell] = mu[18 * nc + cell];
 }
 
 // dL/dV_q = sum over q's links (x, e) of -2 (w_d / c_s^2) rho_f c_d dL/dg0_e(x), d = e*:
-// one workgroup per particle over the nodes within R_q + 2 of X_q, in a fixed order.
-__global__ __launch_bounds__(256) void k_adj_vgrad(AdjDev a)
+// one workgroup per particle over the nodes within R_q + 2 of X_q, in a fixed order (16
+// waves: with few particles the kernel is a chain of loads per node, 4 waves took 359 us
+// for 275 spheres of radius 8).
+constexpr int kVgradThreads = 1024;
+__global__ __launch_bounds__(kVgradThreads) void k_adj_vgrad(AdjDev a)
 {
-    __shared__ double red[4][8];
+    __shared__ double red[kVgradThreads / 64][3];
     const int q = blockIdx.x;
     if (q >= a.np) return;
     const MemberDev &M = a.M;
@@ -3381,33 +3585,37 @@ __global__ __launch_bounds__(256) void k_adj_vgrad(AdjDev a)
     for (int ax = 0; ax < 3; ++ax) axis_range(a.X[3 * q + ax], a.R[q] + 2.0, dims[ax], M.per[ax], lo[ax], ext[ax]);
     const int tot = ext[0] * ext[1] * ext[2];
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int idx = threadIdx.x; idx < tot; idx += blockDim.x) {
+    for (int idx = threadIdx.x; idx < tot; idx += kVgradThreads) {
         const int ii = wrapc(lo[0] + idx % ext[0], dims[0]);
         const int jj = wrapc(lo[1] + (idx / ext[0]) % ext[1], dims[1]);
         const int kk = wrapc(lo[2] + idx / (ext[0] * ext[1]), dims[2]);
-        const int x = (kk * dims[1] + jj) * dims[0] + ii;
-        if (a.own[x] >= 0) continue;
-        for (int e = 0; e < kQ - 1; ++e) {
-            int c[3] = {ii - kCXd[e], jj - kCYd[e], kk - kCZd[e]};
-            bool ok = true;
-            for (int ax = 0; ax < 3; ++ax)
-                if (c[ax] < 0 || c[ax] >= dims[ax]) {
-                    if (M.per[ax]) c[ax] = c[ax] < 0 ? c[ax] + dims[ax] : c[ax] - dims[ax];
-                    else ok = false;
-                }
-            if (!ok || a.own[(c[2] * dims[1] + c[1]) * dims[0] + c[0]] != q) continue;
+        const uint2 w = a.rows[(kk * dims[1] + jj) * M.nw + (ii >> 5)];
+        const unsigned b = 1u << (ii & 31);
+        if (!(w.x & b)) continue; // solid
+        const unsigned r = w.y + (unsigned)__popc(w.x & (b - 1u));
+        const unsigned link = a.mask[r].y;
+        const double *mr = a.macc + a.loff[r];
+        for (unsigned m = link; m; m &= m - 1u, ++mr) {
+            const int e = __ffs(m) - 1;
+            if (a.own[adj_source_cell(a, e, ii, jj, kk)] != q) continue;
             // d g0_e / dV = -2 (w_d / c_s^2) rho_f c_d with c_d = -c_e and w_d = w_e
-            const int c2 = kCXd[e] * kCXd[e] + kCYd[e] * kCYd[e] + kCZd[e] * kCZd[e];
-            const double w = (c2 == 1) ? 1.0 / 18.0 : 1.0 / 36.0;
-            const double f = 2.0 * w / kCS2 * a.rho_f * a.macc[(long long)e * a.ncell + x];
+            const double wd = (e < 6) ? 1.0 / 18.0 : 1.0 / 36.0;
+            const double f = 2.0 * wd / kCS2 * a.rho_f * *mr;
             acc[0] += f * kCXd[e];
             acc[1] += f * kCYd[e];
             acc[2] += f * kCZd[e];
         }
     }
-    block_sum<3>(acc, red);
-    if (threadIdx.x == 0)
-        for (int ax = 0; ax < 3; ++ax) a.gv[3 * q + ax] = acc[ax];
+    for (int ax = 0; ax < 3; ++ax) {
+        const double v = wave_sum(acc[ax]);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][ax] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double v = 0.0;
+        for (int w = 0; w < kVgradThreads / 64; ++w) v += red[w][threadIdx.x];
+        a.gv[3 * q + threadIdx.x] = v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -3532,87 +3740,97 @@ hipError_t launch_remap_prec(int prec, const DevSet &s, int mode, int only_membe
     return hipGetLastError();
 }
 
-int adj_blocks(const AdjDev &a) { return (a.ncell + 255) / 256; }
+int adj_blocks(const AdjDev &a) { return (a.ns + 255) / 256; }
 
 template <int P> using StoreT = typename Prec<P>::S;
 template <int P> using CompT = typename Prec<P>::C;
 
-hipError_t launch_adj_step(int prec, const AdjDev &a, const void *fin, void *fout, int n, hipStream_t st)
+hipError_t launch_adj_geometry(const AdjDev &a, const int *own, hipStream_t st)
 {
+    hipLaunchKernelGGL(k_adj_rows, dim3(a.M.nz), dim3(256), 0, st, a, own);
+    hipLaunchKernelGGL(k_adj_planes, dim3(1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_adj_slots, dim3(a.M.nz), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj_start(int prec, const AdjDev &a, const void *src, void *dst, hipStream_t st)
+{
+    if (a.n_probe > 0) hipLaunchKernelGGL(k_adj_nfl, dim3(a.n_probe), dim3(256), 0, st, a, (double *)a.probe_nfl);
+    if (a.ns == 0) return hipGetLastError();
+    const dim3 g(adj_blocks(a)), b(256);
+    hipLaunchKernelGGL(k_adj_masks, g, b, 0, st, a);
     switch (prec) {
-    case PREC_FP64:
-        hipLaunchKernelGGL(k_adj_step<PREC_FP64>, dim3(adj_blocks(a)), dim3(256), 0, st, a,
-                           (const StoreT<PREC_FP64> *)fin, (StoreT<PREC_FP64> *)fout, n);
-        break;
-    case PREC_FP32:
-        hipLaunchKernelGGL(k_adj_step<PREC_FP32>, dim3(adj_blocks(a)), dim3(256), 0, st, a,
-                           (const StoreT<PREC_FP32> *)fin, (StoreT<PREC_FP32> *)fout, n);
-        break;
-    case PREC_FP16DEV:
-        hipLaunchKernelGGL(k_adj_step<PREC_FP16DEV>, dim3(adj_blocks(a)), dim3(256), 0, st, a,
-                           (const StoreT<PREC_FP16DEV> *)fin, (StoreT<PREC_FP16DEV> *)fout, n);
-        break;
-    default:
-        hipLaunchKernelGGL(k_adj_step<PREC_BF16DEV>, dim3(adj_blocks(a)), dim3(256), 0, st, a,
-                           (const StoreT<PREC_BF16DEV> *)fin, (StoreT<PREC_BF16DEV> *)fout, n);
-        break;
+    case PREC_FP64: hipLaunchKernelGGL(k_adj_start<double>, g, b, 0, st, a, (const double *)src, (double *)dst); break;
+    case PREC_FP32: hipLaunchKernelGGL(k_adj_start<float>, g, b, 0, st, a, (const float *)src, (float *)dst); break;
+    default: hipLaunchKernelGGL(k_adj_start<uint16_t>, g, b, 0, st, a, (const uint16_t *)src, (uint16_t *)dst); break;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_adj_probe(int prec, const AdjDev &a, const void *fin, int n, hipStream_t st)
+template <int P> hipError_t adj_wall_p(const AdjDev &a, hipStream_t st)
 {
-    const int g = a.n_probe > 0 ? a.n_probe : 1;
-    switch (prec) {
-    case PREC_FP64: hipLaunchKernelGGL(k_adj_probe<PREC_FP64>, dim3(g), dim3(256), 0, st, a, (const StoreT<PREC_FP64> *)fin, n); break;
-    case PREC_FP32: hipLaunchKernelGGL(k_adj_probe<PREC_FP32>, dim3(g), dim3(256), 0, st, a, (const StoreT<PREC_FP32> *)fin, n); break;
-    case PREC_FP16DEV: hipLaunchKernelGGL(k_adj_probe<PREC_FP16DEV>, dim3(g), dim3(256), 0, st, a, (const StoreT<PREC_FP16DEV> *)fin, n); break;
-    default: hipLaunchKernelGGL(k_adj_probe<PREC_BF16DEV>, dim3(g), dim3(256), 0, st, a, (const StoreT<PREC_BF16DEV> *)fin, n); break;
-    }
+    hipLaunchKernelGGL(k_adj_wall<P>, dim3(adj_blocks(a)), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+template <int P> hipError_t adj_step_p(const AdjDev &a, const void *fin, void *fout, int n, int m, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_adj_step<P>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const StoreT<P> *)fin, (StoreT<P> *)fout,
+                       n, m);
+    return hipGetLastError();
+}
+template <int P>
+hipError_t adj_back_p(const AdjDev &a, const void *fin, const void *lam, void *out, int n, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_adj_back<P>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const StoreT<P> *)fin,
+                       (const CompT<P> *)lam, (CompT<P> *)out, n);
     return hipGetLastError();
 }
 
-hipError_t launch_adj_mu(int prec, const AdjDev &a, const void *fin, const void *lam, void *mu, int n, hipStream_t st)
+hipError_t launch_adj_wall(int prec, const AdjDev &a, hipStream_t st)
 {
+    if (a.ns == 0) return hipSuccess;
     switch (prec) {
-    case PREC_FP64:
-        hipLaunchKernelGGL(k_adj_mu<PREC_FP64>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const StoreT<PREC_FP64> *)fin,
-                           (const CompT<PREC_FP64> *)lam, (CompT<PREC_FP64> *)mu, n);
-        break;
-    case PREC_FP32:
-        hipLaunchKernelGGL(k_adj_mu<PREC_FP32>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const StoreT<PREC_FP32> *)fin,
-                           (const CompT<PREC_FP32> *)lam, (CompT<PREC_FP32> *)mu, n);
-        break;
-    case PREC_FP16DEV:
-        hipLaunchKernelGGL(k_adj_mu<PREC_FP16DEV>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const StoreT<PREC_FP16DEV> *)fin,
-                           (const CompT<PREC_FP16DEV> *)lam, (CompT<PREC_FP16DEV> *)mu, n);
-        break;
-    default:
-        hipLaunchKernelGGL(k_adj_mu<PREC_BF16DEV>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const StoreT<PREC_BF16DEV> *)fin,
-                           (const CompT<PREC_BF16DEV> *)lam, (CompT<PREC_BF16DEV> *)mu, n);
-        break;
+    case PREC_FP64: return adj_wall_p<PREC_FP64>(a, st);
+    case PREC_FP32: return adj_wall_p<PREC_FP32>(a, st);
+    case PREC_FP16DEV: return adj_wall_p<PREC_FP16DEV>(a, st);
+    default: return adj_wall_p<PREC_BF16DEV>(a, st);
     }
+}
+
+hipError_t launch_adj_step(int prec, const AdjDev &a, const void *fin, void *fout, int n, int m, hipStream_t st)
+{
+    if (a.ns == 0) return hipSuccess;
+    switch (prec) {
+    case PREC_FP64: return adj_step_p<PREC_FP64>(a, fin, fout, n, m, st);
+    case PREC_FP32: return adj_step_p<PREC_FP32>(a, fin, fout, n, m, st);
+    case PREC_FP16DEV: return adj_step_p<PREC_FP16DEV>(a, fin, fout, n, m, st);
+    default: return adj_step_p<PREC_BF16DEV>(a, fin, fout, n, m, st);
+    }
+}
+
+hipError_t launch_adj_signal(const AdjDev &a, int n0, int count, hipStream_t st)
+{
+    if (a.n_probe == 0 || count == 0) return hipSuccess;
+    // (one grid row per step of the segment: rows of a grid are few, so in parts)
+    for (int m = 0; m < count; m += 32768)
+        hipLaunchKernelGGL(k_adj_signal, dim3(a.n_probe, min(32768, count - m)), dim3(64), 0, st, a, n0, m);
     return hipGetLastError();
 }
 
-hipError_t launch_adj_pull(int prec, const AdjDev &a, const void *mu, void *lam, hipStream_t st)
+hipError_t launch_adj_back(int prec, const AdjDev &a, const void *fin, const void *lam, void *out, int n, hipStream_t st)
 {
-    if (prec == PREC_FP64)
-        hipLaunchKernelGGL(k_adj_pull<PREC_FP64>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const double *)mu, (double *)lam);
-    else
-        hipLaunchKernelGGL(k_adj_pull<PREC_FP32>, dim3(adj_blocks(a)), dim3(256), 0, st, a, (const float *)mu, (float *)lam);
-    return hipGetLastError();
+    if (a.ns == 0) return hipSuccess;
+    switch (prec) {
+    case PREC_FP64: return adj_back_p<PREC_FP64>(a, fin, lam, out, n, st);
+    case PREC_FP32: return adj_back_p<PREC_FP32>(a, fin, lam, out, n, st);
+    case PREC_FP16DEV: return adj_back_p<PREC_FP16DEV>(a, fin, lam, out, n, st);
+    default: return adj_back_p<PREC_BF16DEV>(a, fin, lam, out, n, st);
+    }
 }
 
 hipError_t launch_adj_vgrad(const AdjDev &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_adj_vgrad, dim3(a.np > 0 ? a.np : 1), dim3(256), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_adj_nfl(const AdjDev &a, double *nfl, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_adj_nfl, dim3(a.n_probe > 0 ? a.n_probe : 1), dim3(256), 0, st, a, nfl);
+    if (a.np > 0) hipLaunchKernelGGL(k_adj_vgrad, dim3(a.np), dim3(kVgradThreads), 0, st, a);
     return hipGetLastError();
 }
 
