@@ -80,8 +80,7 @@ struct Geometry {
     int ring_len = 1;
     int pv_ring = 0;
     int chg_cap = 0;
-    int lcap = 1;
-    int bcap = 1;
+    int xcap = 1;
     int prec = PREC_FP32;
 };
 
@@ -251,16 +250,19 @@ void build_geometry(int32_t n, const lbdem_params *lat, const lbdem_config *cfg,
     G.wave_doubles = wave;
     G.pz = pz;
     G.chg_cap = (int)std::min<long long>(std::max<long long>(65536, 256LL * pt), 1LL << 26);
-    // shell-list capacity: lattice nodes with -kShell < d - R <= sqrt(2) + kShell are within
-    // the shell thickened by half a cell diagonal on both sides
+    // link-entry capacity of a chunk: per z plane, lattice nodes with R < d <= R + sqrt(2) are
+    // within an annulus thickened by half a cell diagonal, at most pi (R_o + R) (R_o - R +
+    // sqrt(2)) of them (R_o = R + sqrt(2)), one entry per image of the particle
     double rmax = 0.0;
+    int images = 1;
     for (int m = 0; m < n; ++m)
-        if (lat[m].max_particles > 0) rmax = std::max(rmax, lat[m].max_radius);
+        if (lat[m].max_particles > 0) {
+            rmax = std::max(rmax, lat[m].max_radius);
+            if (G.mem[m].narrow) images = 2;
+        }
     if (rmax > 0.0) {
-        const double ro = rmax + std::sqrt(2.0) + kShell + 0.8661, ri = std::max(0.0, rmax - kShell - 0.8661);
-        G.lcap = (int)std::ceil(4.0 / 3.0 * M_PI * (ro * ro * ro - ri * ri * ri)) + 64;
-        const double bo = rmax + kBandOut + 0.8661, bi = std::max(0.0, rmax - kBandIn - 0.8661);
-        G.bcap = (int)std::ceil(4.0 / 3.0 * M_PI * (bo * bo * bo - bi * bi * bi)) + 64;
+        const int hz = ((int)std::ceil(2.0 * (rmax + kSlabReach + kSlabLens + 1e-9)) + 4 + kChunks - 1) / kChunks;
+        G.xcap = images * hz * ((int)std::ceil(M_PI * (2.0 * rmax + std::sqrt(2.0)) * 2.0 * std::sqrt(2.0)) + 4);
     }
 }
 
@@ -284,6 +286,7 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.es = (int)es;
     s.rt = c.take<uint2>((size_t)std::max<long long>(G.compact ? G.rt_words : 1, 1));
     s.popC = c.take<char>(G.compact ? es * kQ * (size_t)G.cells : 1);
+    s.scratch = c.take<char>(64 * (size_t)G.cells);
     s.nplanes = (int)G.pz;
     s.clist = c.take<int>((size_t)G.cells);
     s.ccnt = c.take<int>((size_t)std::max<long long>(G.pz, 1));
@@ -301,8 +304,6 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.lwc = c.take<unsigned long long>((size_t)G.cells);
     s.lwc_bad = c.take<long long>(1);
     s.ncell_total = G.cells;
-    s.frec = c.take<char>(4 * (size_t)G.cells * (G.prec == PREC_FP64 ? 32 : 16));
-    s.rec_step = c.take<long long>(1);
     s.chg_cap = G.chg_cap;
     s.chg[0] = c.take<int>(2 * (size_t)G.chg_cap);
     s.chg[1] = c.take<int>(2 * (size_t)G.chg_cap);
@@ -333,7 +334,6 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.pspd = c.take<double>((size_t)P);
     s.pf[0] = c.take<float>(12 * (size_t)P);
     s.pf[1] = c.take<float>(12 * (size_t)P);
-    s.margin = c.take<double>(P);
     s.fixed = c.take<int>(P);
     s.pmem = c.take<int>(P);
     s.ppart = c.take<double>((size_t)P * kChunks * kLinkComp);
@@ -342,26 +342,16 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.zcache = c.take<double>((size_t)P * kChunks * kZComp);
     s.nearl = c.take<int>((size_t)P * kNearCap);
     s.nnear = c.take<int>(P);
-    s.near_at = c.take<long long>(P);
-    s.lcap = G.lcap;
-    s.lcell = c.take<int>((size_t)P * G.lcap);
-    s.ldr = c.take<float>((size_t)P * G.lcap);
-    s.lmask = c.take<unsigned>((size_t)P * G.lcap);
-    s.lcnt = c.take<int>(P);
-    s.xcell = c.take<int>((size_t)P * G.lcap);
-    s.xslot = c.take<int>((size_t)P * G.lcap);
-    s.xgrp = c.take<unsigned>((size_t)P * G.lcap);
+    s.near_due = c.take<long long>(G.mem.size());
+    s.Xn = c.take<double>(3 * (size_t)P);
+    s.xcap = G.xcap;
+    s.xcell = c.take<int>((size_t)P * kChunks * G.xcap);
+    s.xslot = c.take<int>((size_t)P * kChunks * G.xcap);
+    s.xgrp = c.take<unsigned>((size_t)P * kChunks * G.xcap);
     s.xcnt = c.take<int>((size_t)P * kChunks);
     s.lreb = c.take<long long>(P);
     s.ldirty = c.take<long long>((size_t)P * kChunks);
     s.lzr = c.take<int>(2 * (size_t)P);
-    s.lchunk = c.take<int>((size_t)P * (kChunks + 1));
-    s.rdisp = c.take<double>((size_t)P);
-    s.rlens = c.take<double>((size_t)P);
-    s.bcap = G.bcap;
-    s.bcell = c.take<int>((size_t)P * G.bcap);
-    s.bdr = c.take<float>((size_t)P * G.bcap);
-    s.bcnt = c.take<int>(P);
     for (int k = 0; k < 2; ++k) {
         s.hj[k] = c.take<int>((size_t)P * kHistCap);
         s.hf[k] = c.take<double>((size_t)P * kHistCap * 3);
@@ -524,7 +514,7 @@ int build_graph(lbdem_set *S, int steps)
         kp.blockDim = dim3(256);
         kp.sharedMemBytes = 0;
         kp.extra = nullptr;
-        // refresh -> link records -> link pass -> motion -> fluid -> re-projection
+        // refresh -> link pass -> motion -> fluid -> re-projection
         kp.func = refresh_kernel_ptr(S->G.prec);
         kp.gridDim = dim3(refresh_grid(S->ds));
         kp.kernelParams = fluid_args;
@@ -533,16 +523,11 @@ int build_graph(lbdem_set *S, int steps)
             // hydrodynamics switched off: no link pass and no fluid step
             n0 = n4;
         } else {
-            hipGraphNode_t nr;
-            kp.func = records_kernel_ptr(S->G.prec, S->G.compact, S->ds.narrow);
-            kp.gridDim = dim3(records_grid(S->ds));
-            kp.kernelParams = fluid_args;
-            HIPCHK(hipGraphAddKernelNode(&nr, S->graph, &n4, 1, &kp));
             kp.func = links_kernel_ptr(S->G.prec, S->ds.narrow);
             kp.gridDim = dim3(links_grid(S->ds));
             kp.blockDim = dim3(links_block());
             kp.kernelParams = part_args;
-            HIPCHK(hipGraphAddKernelNode(&n0, S->graph, &nr, 1, &kp));
+            HIPCHK(hipGraphAddKernelNode(&n0, S->graph, &n4, 1, &kp));
         }
         kp.blockDim = dim3(256);
         kp.kernelParams = part_args;
@@ -604,11 +589,7 @@ int launch_step_eager(lbdem_set *S)
         }
         hipError_t err;
         if (k == 4) err = launch_refresh(S->G.prec, S->ds, S->stream);
-        else if (k == 0) {
-            // the link records and the link pass share the links timing slot
-            err = launch_records(S->G.prec, S->ds, S->stream);
-            if (err == hipSuccess) err = launch_links(S->G.prec, S->ds, S->stream);
-        }
+        else if (k == 0) err = launch_links(S->G.prec, S->ds, S->stream);
         else if (k == 1) err = launch_motion(S->ds, 0, -1, S->stream);
         else if (k == 2) err = launch_fluid(S->G.prec, S->ds, S->stream);
         else err = launch_remap_prec(S->G.prec, S->ds, 0, -1, S->stream);
@@ -787,23 +768,17 @@ int lbdem_create(int32_t n_lat, const lbdem_params *lat, const lbdem_config *cfg
     }
     double *zero3[] = {s.Fg, s.Fh, s.Th, s.Ph, s.Lh, s.Xref};
     for (double *z : zero3) CHK(hipMemsetAsync(z, 0, sizeof(double) * 3 * P, st));
-    CHK(hipMemsetAsync(s.margin, 0, sizeof(double) * P, st));
     CHK(hipMemsetAsync(s.pspd, 0, sizeof(double) * P, st));
-    CHK(hipMemsetAsync(s.rdisp, 0, sizeof(double) * P, st));
-    CHK(hipMemsetAsync(s.rlens, 0, sizeof(double) * P, st));
+    CHK(hipMemsetAsync(s.Xn, 0, sizeof(double) * 3 * P, st));
     CHK(hipMemsetAsync(s.pf[0], 0, sizeof(float) * 12 * P, st));
     CHK(hipMemsetAsync(s.pf[1], 0, sizeof(float) * 12 * P, st));
     CHK(hipMemsetAsync(s.nnear, 0, sizeof(int) * P, st));
-    CHK(hipMemsetAsync(s.near_at, 0xff, sizeof(long long) * P, st)); // -1: build at the first step
-    CHK(hipMemsetAsync(s.lcnt, 0, sizeof(int) * P, st));
+    CHK(hipMemsetAsync(s.near_due, 0xff, sizeof(long long) * S->G.mem.size(), st)); // -1: none due
     CHK(hipMemsetAsync(s.xcnt, 0, sizeof(int) * P * kChunks, st));
-    CHK(hipMemsetAsync(s.bcnt, 0, sizeof(int) * P, st));
     CHK(hipMemsetAsync(s.lreb, 0xff, sizeof(long long) * P, st));
     CHK(hipMemsetAsync(s.ldirty, 0xff, sizeof(long long) * P * kChunks, st));
     CHK(hipMemsetAsync(s.lzr, 0, sizeof(int) * 2 * P, st));
-    CHK(hipMemsetAsync(s.lchunk, 0, sizeof(int) * P * (kChunks + 1), st));
     CHK(hipMemsetAsync(s.tstep, 0, sizeof(long long), st));
-    CHK(hipMemsetAsync(s.rec_step, 0x80, sizeof(long long), st)); // no link records yet
     CHK(hipMemsetAsync(s.tcopy, 0, sizeof(long long), st));
     CHK(hipMemsetAsync(s.flags, 0, sizeof(unsigned), st));
     CHK(launch_init_pops(S->G.prec, s, S->G.cells, st));
@@ -1270,8 +1245,6 @@ int lbdem_populations_set(lbdem_set *S, int32_t lattice, const double *f)
         }
     }
     HIPCHK(hipMemcpy(dst, raw.data(), raw.size(), hipMemcpyHostToDevice));
-    // the link records no longer describe the populations
-    HIPCHK(hipMemset(S->ds.rec_step, 0x80, sizeof(long long)));
     return LBDEM_OK;
 }
 
@@ -1322,8 +1295,8 @@ int lbdem_fields_get(lbdem_set *S, int32_t lattice, double *rho, double *u, int3
 namespace {
 
 // Checkpoint layout: header, the host copy of the per-lattice constants, then the
-// workspace image without the scratch population buffer of compact storage (it holds
-// nothing between kernels).
+// workspace image without the scratch population buffer of compact storage and the node
+// scratch (they hold nothing between calls).
 struct CkptHeader {
     char magic[8];
     uint32_t version, n_lat;
@@ -1331,7 +1304,7 @@ struct CkptHeader {
     int64_t t_host;
     int32_t node_layout, reserved;
 };
-constexpr uint32_t kCkptVersion = 1;
+constexpr uint32_t kCkptVersion = 2;
 
 void fnv(uint64_t &h, const void *p, size_t n)
 {
@@ -1363,7 +1336,8 @@ uint64_t set_digest(const lbdem_set *S)
 void ckpt_ranges(const lbdem_set *S, uint64_t &skip_off, uint64_t &skip_bytes)
 {
     skip_off = (uint64_t)((const char *)S->ds.popC - (const char *)S->ws);
-    skip_bytes = S->G.compact ? (uint64_t)elem_size(S->G.prec) * kQ * (uint64_t)S->G.cells : 0;
+    // (popC and the node scratch behind it)
+    skip_bytes = (uint64_t)((const char *)S->ds.scratch - (const char *)S->ds.popC) + 64 * (uint64_t)S->G.cells;
 }
 
 } // namespace

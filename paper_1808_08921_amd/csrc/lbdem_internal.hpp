@@ -16,19 +16,28 @@ constexpr int kQ = 19;
 constexpr int kNearCap = 32;       // near-neighbour table per particle
 constexpr int kHistCap = 16;       // tangential contact history per particle
 constexpr double kNearMargin = 3.0; // near list: |X_p - X_q| <= R_p + R_q + margin
-constexpr int kNearEvery = 5;       // steps between near-list builds (approach < 0.5 lu per step)
-constexpr double kShell = 0.5;      // skin of the per-particle shell lists (lattice units)
-constexpr double kBandIn = 0.15;    // surface band list: nodes with -kBandIn <= d - R <= kBandOut
-constexpr double kBandOut = 0.1;    // (lattice units)
+// near lists are built again once a particle of the lattice has moved this far since they
+// were: two particles then close by less than 2 (0.15 + 0.25 + 0.25) = 1.3 before the new
+// lists take effect, and a sphere that contains a neighbour node of a particle's swept node
+// lies within R_p + R_q + 0.25 + sqrt(2) of it, together within the margin
+constexpr double kNearMove = 0.15;
+// a particle's slabs and the reference point of its link sums follow it after this distance
+constexpr double kAnchorMove = 0.3;
+// half height of a particle's slabs beyond its radius (plus the overlap depth up to
+// kSlabLens, and one plane): a node with links lies within R + sqrt(2), and the particle
+// within kAnchorMove, of the reference point.  The link sums are added slab by slab, so
+// their rounding depends on this layout.
+constexpr double kSlabReach = 2.0;
+constexpr double kSlabLens = 1.0;
 // node lists keep the solid nodes within a skin of a surface; the skin of a rebuild is
 // kSkinSteps times the largest particle step of the lattice, within [kSkinMin, kListSkin]
 constexpr double kListSkin = 0.25;
 constexpr double kSkinMin = 0.05;
 constexpr double kSkinSteps = 12.0;
 constexpr int kPendCap = 16384;     // refills of unlisted nodes awaiting the next list rebuild
-constexpr int kChunks = 8;          // chunks of a shell list: waves per particle in the link pass
+constexpr int kChunks = 8;          // z-slabs of the nodes around a particle: waves per particle in the link pass
 // components of a link-pass partial per (particle, chunk): F0 (3) and sum xr x G (3), xr the
-// node position relative to the shell list's reference point
+// node position relative to the particle's reference point
 constexpr int kLinkComp = 6;
 // cached link-set sums per (particle, chunk): S (6, upper triangle), Qx (9, row-major), Wx (6)
 constexpr int kZComp = 21;
@@ -119,12 +128,8 @@ struct DevSet {
     unsigned long long *lwc;  // [ncell_total]
     long long *lwc_bad;
     long long ncell_total;
-    // per slot of a fluid node's link words, written by k_records of step t for the link
-    // pass of step t: G = sum c_d (f~_d(x,t) - w_d rho_f) over the slot's links and the link
-    // directions (FP32 float4, FP64 two double2), [4][ncell_total] at the node's storage
-    // slot; rec_step: the step whose k_records wrote them
-    void *frec;
-    long long *rec_step;
+    // 64 bytes per node that hold nothing between calls (fields of lbdem_fields_get)
+    void *scratch;
     int *chg[2];
     int chg_cap;
     int *chgcnt;              // [2]
@@ -139,7 +144,7 @@ struct DevSet {
     // particles
     int ptot;
     double *X[2], *V[2], *W[2];
-    double *R, *m, *I, *Fg, *Fh, *Th, *Ph, *Lh, *Xref, *margin;
+    double *R, *m, *I, *Fg, *Fh, *Th, *Ph, *Lh, *Xref;
     float *pf[2];             // FP32 wall state of the fluid kernel per particle (12 floats): X(t) and the
                               // velocities V, Omega of step t, at the parity of t
     int *fixed, *pmem;
@@ -148,30 +153,18 @@ struct DevSet {
     double *ppart;            // link-pass partials per (particle, chunk) [ptot*kChunks*kLinkComp]
     double *zcache;           // link-set sums per (particle, chunk), rebuilt with its entries [ptot*kChunks*kZComp]
     int *nearl, *nnear;       // [ptot*kNearCap], [ptot]
-    long long *near_at;       // step at which each near list was built [ptot]
-    // shell list per particle around X_ref: node, d_ref - R, link-candidate directions
-    int lcap;
-    int *lcell, *lcnt;
-    float *ldr;
-    unsigned *lmask;
-    // the shell-list entries that hold links of the particle: each chunk of a list keeps
-    // its own compacted run [ptot*lcap], counts [ptot*kChunks]
+    long long *near_due;      // step whose re-projection builds a lattice's near lists [nmem]
+    double *Xn;               // particle positions when its near list was built [ptot*3]
+    // link entries: the nodes with links of a particle, per chunk in list order (z, y, x), at
+    // [(p*kChunks + chunk)*xcap, + xcnt[p*kChunks + chunk])
+    int xcap;
     int *xcell, *xcnt;
-    int *xslot;               // storage slot of each cached entry's node [ptot*lcap]
-    unsigned *xgrp;           // the particle's link directions at each cached entry's node [ptot*lcap]
-    long long *lreb;          // step after which the shell list was last rebuilt [ptot]
-    long long *ldirty;        // last step in which a node of a chunk's z-slab, or next to
-                              // it, changed owner [ptot*kChunks]
-    // chunks are z-slabs of the list's scan box: first z (unwrapped), slab height, and
-    // the list offset where each chunk starts [ptot*2], [ptot*(kChunks+1)]
-    int *lzr, *lchunk;
-    // running maxima since the last shell-list rebuild of |X - X_ref| and of |X - X_ref|
-    // plus the overlap depth with the near neighbours [ptot] each
-    double *rdisp, *rlens;
-    // surface band: shell-list entries with -kBandIn <= d_ref - R <= kBandOut [ptot*bcap], [ptot]
-    int bcap;
-    int *bcell, *bcnt;
-    float *bdr;
+    int *xslot;               // storage slot of each cached entry's node
+    unsigned *xgrp;           // the particle's link directions at each cached entry's node
+    long long *lreb;          // step after which the particle's slabs were last laid out [ptot]
+    long long *ldirty;        // last step in which link words of a chunk's nodes changed [ptot*kChunks]
+    // chunks are z-slabs around X_ref: first z (unwrapped) and slab height [ptot*2]
+    int *lzr;
     int *hj[2];               // tangential history partner ids [ptot*kHistCap]
     double *hf[2];            // tangential history forces [ptot*kHistCap*3]
     int *hn[2];               // history counts [ptot]
@@ -218,7 +211,6 @@ enum { PREC_FP64 = 0, PREC_FP32 = 1, PREC_FP16DEV = 2, PREC_BF16DEV = 3 };
 
 // kernel launchers (lbdem_kernels.hip)
 hipError_t launch_refresh(int prec, const DevSet &s, hipStream_t st);
-hipError_t launch_records(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_links(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_motion(const DevSet &s, int mode, int only_member, hipStream_t st);
 hipError_t launch_fluid(int prec, const DevSet &s, hipStream_t st);
@@ -228,8 +220,6 @@ hipError_t launch_expand(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_fields(int prec, const DevSet &s, int m, long long ncell, double *out, hipStream_t st);
 // kernel entry points and grid sizes, for building HIP graphs
 void *refresh_kernel_ptr(int prec);
-void *records_kernel_ptr(int prec, int compact, int narrow);
-int records_grid(const DevSet &s);
 void *links_kernel_ptr(int prec, int narrow);
 void *motion_kernel_ptr();
 void *fluid_kernel_ptr(int prec, int compact, int narrow);

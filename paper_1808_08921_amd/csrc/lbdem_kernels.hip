@@ -3,22 +3,20 @@
 // Method: Cheng, Luding, Rivas, Harting, Magnanimo, "Hydro-micromechanical modeling of
 // wave propagation in saturated granular media", arXiv 1808.08921, Sec. 2.
 //
-// Six kernels make one time step t -> t+1 of every lattice of a set, in this order
+// Five kernels make one time step t -> t+1 of every lattice of a set, in this order
 // (Secs. 2.1-2.4; the paper gives no order: this one lets the particle velocities of the
 // step be solved together with the momentum their links exchange in it):
 //   k_refresh    brings the node map of step t up to date with the previous re-projection's
 //                changes, refreshes the link words of the changed nodes and their
 //                neighbours, and rebuilds the node lists (moving the populations of changed
 //                planes under compact storage) once a particle may have crossed their skin.
-//   k_records    first kChunks waves per particle, rebuilding the link entries of the
-//                chunks of its shell list whose link words changed, with their link-set
-//                sums (the 6 x 6 matrix Z of the motion kernel comes from them); then one
-//                thread per listed node (or node of a dense tile): per link slot of a fluid
-//                node, the sum of c_d (f~_d(x,t) - w_d rho_f) over the slot's links.
-//   k_links      kChunks waves per particle: the link pass.  With Eq. (mem) substituted, the
-//                link force of Eq. (fFS) is 2 c_d f~_d(x,t) minus a term linear in the
-//                particle's velocities; per (particle, chunk) the first part and its torque
-//                (F0, T0) are summed in FP64 from the records of f~(t).
+//   k_links      kChunks waves per particle, each for a z-slab of the nodes around it: the
+//                link pass.  A slab whose link words changed has its link entries found
+//                again first, with their link-set sums (the 6 x 6 matrix Z of the motion
+//                kernel comes from them).  With Eq. (mem) substituted, the link force of Eq.
+//                (fFS) is 2 c_d f~_d(x,t) minus a term linear in the particle's velocities;
+//                per (particle, slab) the first part and its torque (F0, T0) are summed in
+//                FP64 from the populations f~(t) at the entries' nodes.
 //   k_motion     one wave per particle: contacts (Eqs. fdLawn, fdLaws) at X(t), then the
 //                velocities of the step from (M + Z)(V', Omega') = M (V, Omega) + F0 + contacts
 //                + F_g + the conversion impulses of the previous re-projection (Eqs. translate,
@@ -49,6 +47,16 @@ constexpr int kOPP[kQ] = {1, 0, 3, 2, 5, 4, 11, 10, 13, 12, 7, 6, 9, 8, 17, 16, 
 __constant__ int kCXd[kQ] = {1, -1, 0, 0, 0, 0, 1, 1, 1, 1, -1, -1, -1, -1, 0, 0, 0, 0, 0};
 __constant__ int kCYd[kQ] = {0, 0, 1, -1, 0, 0, 1, -1, 0, 0, 1, -1, 0, 0, 1, 1, -1, -1, 0};
 __constant__ int kCZd[kQ] = {0, 0, 0, 0, 1, -1, 0, 0, 1, -1, 0, 0, 1, -1, 1, -1, 1, -1, 0};
+// component c_d + 1 of every direction, two bits each: a run-time direction without a load
+constexpr unsigned long long pack_dirs(const int (&c)[kQ])
+{
+    unsigned long long v = 0ull;
+    for (int d = 0; d < kQ; ++d) v |= (unsigned long long)(c[d] + 1) << (2 * d);
+    return v;
+}
+__device__ __forceinline__ int dir_x(int d) { return (int)(pack_dirs(kCX) >> (2 * d) & 3ull) - 1; }
+__device__ __forceinline__ int dir_y(int d) { return (int)(pack_dirs(kCY) >> (2 * d) & 3ull) - 1; }
+__device__ __forceinline__ int dir_z(int d) { return (int)(pack_dirs(kCZ) >> (2 * d) & 3ull) - 1; }
 // lattice weights (Sec. 2.1): 1/18 along the axes, 1/36 on the diagonals, 1/3 at rest
 constexpr double kWd[kQ] = {1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18,
                             1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36,
@@ -122,6 +130,26 @@ __device__ __forceinline__ void st(typename Prec<P>::S *a, unsigned idx, int d, 
     } else {
         sto(a, idx, f32_to_bf16(f * kInvW[d] - (float)rho_f));
     }
+}
+
+// the same for a loaded value, and for a direction known at run time by its weight w
+template <int P>
+__device__ __forceinline__ typename Prec<P>::C decode_full(typename Prec<P>::S v, int d, double rho_f)
+{
+    if constexpr (P == PREC_FP64) return v;
+    else if constexpr (P == PREC_FP32) return v + (float)(kWd[d] * rho_f);
+    else if constexpr (P == PREC_FP16DEV) return (float)kWd[d] * ((float)rho_f + (float)v);
+    else return (float)kWd[d] * ((float)rho_f + bf16_to_f32(v));
+}
+template <int P>
+__device__ __forceinline__ void encode_full(typename Prec<P>::S *a, typename Prec<P>::C f, double w, double rho_f)
+{
+    using S = typename Prec<P>::S;
+    const float iw = w > 0.3 ? 3.0f : (w > 0.05 ? 18.0f : 36.0f); // 1 / w_d, exact
+    if constexpr (P == PREC_FP64) *a = (S)f;
+    else if constexpr (P == PREC_FP32) *a = f - (float)(w * rho_f);
+    else if constexpr (P == PREC_FP16DEV) *a = (S)(f * iw - (float)rho_f);
+    else *a = f32_to_bf16(f * iw - (float)rho_f);
 }
 
 // ---------------------------------------------------------------------------
@@ -255,6 +283,14 @@ __device__ __forceinline__ double wave_min_d(double v)
         if (ohi < hi || (ohi == hi && olo < lo)) { hi = ohi; lo = olo; }
     }
     return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
+// Makes a wave's LDS writes visible to its other lanes.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Block-wide (256 threads) sums of N doubles in a fixed order; result valid in thread 0.
@@ -426,37 +462,6 @@ __device__ __forceinline__ void store_dev(typename Prec<P>::S *a, unsigned idx, 
     else sto(a, idx, f32_to_bf16(df * kInvW[d]));
 }
 
-// Record of one link slot of a fluid node for this step's link pass: the deviation part of
-// sum 2 c_d f~_d(x,t) over the slot's links (as G = sum c_d (f~_d - w_d rho_f); the
-// rest-state part comes from counts) and the link directions; FP32 float4, FP64 2 x double2,
-// at [slot][storage slot of the node]
-template <int P>
-__device__ __forceinline__ void put_record(const DevSet &s, int g, long long gr, typename Prec<P>::C G0,
-                                           typename Prec<P>::C G1, typename Prec<P>::C G2, unsigned grp)
-{
-    if constexpr (sizeof(typename Prec<P>::C) == 4) {
-        reinterpret_cast<float4 *>(s.frec)[g * s.ncell_total + gr] = make_float4(G0, G1, G2, __uint_as_float(grp));
-    } else {
-        double2 *r = reinterpret_cast<double2 *>(s.frec) + 2 * (g * s.ncell_total + gr);
-        r[0] = make_double2(G0, G1);
-        r[1] = make_double2(G2, __longlong_as_double((long long)grp));
-    }
-}
-template <int P>
-__device__ __forceinline__ unsigned get_record(const DevSet &s, int g, long long gr, double &G0, double &G1, double &G2)
-{
-    if constexpr (sizeof(typename Prec<P>::C) == 4) {
-        const float4 v = reinterpret_cast<const float4 *>(s.frec)[g * s.ncell_total + gr];
-        G0 = v.x; G1 = v.y; G2 = v.z;
-        return __float_as_uint(v.w);
-    } else {
-        const double2 *r = reinterpret_cast<const double2 *>(s.frec) + 2 * (g * s.ncell_total + gr);
-        const double2 a = r[0], b = r[1];
-        G0 = a.x; G1 = a.y; G2 = b.x;
-        return (unsigned)__double_as_longlong(b.y);
-    }
-}
-
 // Rank of a true predicate among the workgroup's threads (thread order) and the total.
 __device__ __forceinline__ int block_rank(bool pred, int &total, int *cnt4)
 {
@@ -578,7 +583,7 @@ __device__ __forceinline__ unsigned long long compact_word(unsigned long long w0
     return solid ? kSolidWord : (w0 & ~kSolidWord);
 }
 
-// Marks the chunks of q's shell list whose z-slab lies within one plane of z.
+// Marks the chunk of q whose z-slab holds plane z.
 __device__ __forceinline__ void mark_dirty(const DevSet &s, const MemberDev *M, int q, int z, long long t)
 {
     if (q < 0) return;
@@ -586,16 +591,14 @@ __device__ __forceinline__ void mark_dirty(const DevSet &s, const MemberDev *M, 
     if (hz <= 0) return;
     int dz = z - z0;
     if (M->per[2]) dz = ((dz % M->nz) + M->nz) % M->nz;
-    for (int w = dz - 1; w <= dz + 1; ++w) {
-        const int c = (w >= 0) ? w / hz : -1;
-        if (c >= 0 && c < kChunks) s.ldirty[q * kChunks + c] = t;
-    }
+    if (dz < 0) return;
+    const int c = dz / hz;
+    if (c < kChunks) s.ldirty[q * kChunks + c] = t;
 }
 
 // Link words of a node changed (re-projection of the previous step): the cached link
-// entries of every particle named in the old or the new words are stale in the chunks
-// around the node's plane z (a particle's slot at the node can move even when its own
-// links there do not change).
+// entries of every particle named in the old or the new words are stale in the chunk that
+// holds the node's plane z.
 __device__ __forceinline__ void mark_words(const DevSet &s, const MemberDev *M, unsigned long long o0,
                                            unsigned long long o1, unsigned long long n0, unsigned long long n1,
                                            int z, long long stamp)
@@ -833,7 +836,7 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
                 w1 = (unsigned long long)shi | ((unsigned long long)(max(id2, 0) & 0x1fff) << 18) |
                      ((unsigned long long)(max(id3, 0) & 0x1fff) << 31);
             }
-            // a changed word marks the chunks around plane ck of every particle it names,
+            // a changed word marks the chunk at plane ck of every particle it names,
             // old or new: lane l < 8 takes slot l & 3 of the old (l < 4) or the new words, so
             // the particles' chunk layouts are loaded in one round
             const unsigned long long g0w = __shfl(o0, 0, 32), g1w = __shfl(o1, 0, 32);
@@ -986,134 +989,6 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
     }
 }
 
-template <bool NR>
-__device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk, long long t, int *lc, unsigned *lg);
-constexpr int kLinkLds = 384; // entries of a rebuilt chunk kept in LDS for its link-set sums
-
-// Workgroups of the record kernel that rebuild stale link chunks, four chunks each.
-__host__ __device__ __forceinline__ int rebuild_blocks(const DevSet &s) { return (s.ptot * kChunks + 3) / 4; }
-
-// After the refresh (link words and storage slots of step t final): first the rebuild of
-// the stale link chunks (rebuild_chunk), one wave per (particle, chunk); then the link
-// records of step t for the link pass, one thread per listed node (or per node of a dense
-// tile) on the fluid kernel's grid: per fluid node with links and per slot of its link
-// words, G = sum c_d (f~_d(x,t) - w_d rho_f) over the slot's links, read from the node's
-// own storage slot (consecutive threads read consecutive slots).
-template <int P, bool CMP, bool NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_FP64 ? 4 : 6))) void k_records(DevSet s)
-{
-    using S = typename Prec<P>::S;
-    using C = typename Prec<P>::C;
-    const long long t = *s.tstep;
-    const int par = (int)(t & 1);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *s.rec_step = t;
-    // the first workgroups rebuild the stale link chunks, one wave per chunk: those waves
-    // are few, long and latency-bound, so they start first and run beside the node waves
-    const int nrb = rebuild_blocks(s);
-    if ((int)blockIdx.x < nrb) {
-        __shared__ int rb_c[4][kLinkLds];
-        __shared__ unsigned rb_g[4][kLinkLds];
-        const int wv = (int)(threadIdx.x >> 6);
-        const int ci = (int)blockIdx.x * 4 + wv;
-        if (ci < s.ptot * kChunks) rebuild_chunk<NR>(s, ci / kChunks, ci - (ci / kChunks) * kChunks, t, rb_c[wv], rb_g[wv]);
-        return;
-    }
-    const int g = xcd_swizzle((int)blockIdx.x - nrb, (int)gridDim.x - nrb);
-    const MemberDev *M = member_of_tile(s, g);
-    const int tl = g - uni(M->tile_off);
-    const int ntx = uni(M->ntx), nty = uni(M->nty);
-    const int nx = uni(M->nx), ny = uni(M->ny), nz = uni(M->nz);
-    const int nxy = nx * ny;
-    const unsigned nc = (unsigned)uni(M->ncell);
-    const long long cell_off = uni(M->cell_off);
-    const S *A = (const S *)(par ? s.popB : s.popA) + uni(M->pop_off);
-    const double rho_f = uni(M->rho_f);
-    // compact storage: every listed node's compact word is rewritten here after a list
-    // rebuild or a full copy of the node map, and read from its slot otherwise
-    const bool full_compact = CMP && (*s.relist_at == t || *s.lwc_bad == t);
-    const int *own = s.own[par] + cell_off;
-    auto records = [&](int cell, int slot) {
-        const long long gc = cell_off + cell;
-        unsigned long long w0;
-        if constexpr (CMP) {
-            if (full_compact) {
-                w0 = compact_word(s.lw[gc], own[cell] >= 0);
-                s.lwc[cell_off + slot] = w0;
-            } else {
-                w0 = s.lwc[cell_off + slot];
-            }
-            if (w0 & kSolidWord) return;
-        } else {
-            w0 = s.lw[gc];
-        }
-        if (((unsigned)w0 & 0x3ffffu) == 0u) return;
-        const unsigned long long w1 = (w0 >> 62) ? s.lw[s.ncell_total + gc] : 0ull;
-        const int ng = (w0 >> 62) ? 4 : 2;
-        // the node's populations in the link directions, loaded without a branch
-        const unsigned all = (unsigned)w0 & 0x3ffffu;
-        C v[kQ - 1];
-#pragma unroll
-        for (int e = 0; e < kQ - 1; ++e) {
-            const int d = kOPP[e];
-            const bool on = (all >> e) & 1u;
-            // (every lane loads; a lane without the link reads the array's first element)
-            const C x = decode_dev<P>(ldo(A, on ? (unsigned)d * nc + (unsigned)slot : 0u), d, rho_f);
-            v[e] = on ? x : C(0);
-        }
-        // slots 0 and 1 in one pass without branches (v is 0 outside the links)
-        const unsigned lo = (unsigned)(w0 >> 18) & 0x3ffffu, hi = (unsigned)w1 & 0x3ffffu;
-        const unsigned g0 = all & ~lo & ~hi, g1 = all & lo & ~hi;
-        C A0 = C(0), A1 = C(0), A2 = C(0), B0 = C(0), B1 = C(0), B2 = C(0);
-#pragma unroll
-        for (int e = 0; e < kQ - 1; ++e) {
-            const int d = kOPP[e];
-            const C va = ((g0 >> e) & 1u) ? v[e] : C(0), vb = ((g1 >> e) & 1u) ? v[e] : C(0);
-            if (kCX[d] > 0) { A0 += va; B0 += vb; } else if (kCX[d] < 0) { A0 -= va; B0 -= vb; }
-            if (kCY[d] > 0) { A1 += va; B1 += vb; } else if (kCY[d] < 0) { A1 -= va; B1 -= vb; }
-            if (kCZ[d] > 0) { A2 += va; B2 += vb; } else if (kCZ[d] < 0) { A2 -= va; B2 -= vb; }
-        }
-        if (g0 != 0u) put_record<P>(s, 0, cell_off + slot, A0, A1, A2, g0);
-        if (g1 != 0u) put_record<P>(s, 1, cell_off + slot, B0, B1, B2, g1);
-#pragma unroll 1
-        for (int gg = 2; gg < ng; ++gg) {
-            int q;
-            const unsigned grp = slot_dirs(w0, w1, gg, q);
-            if (grp == 0u) continue;
-            C G0 = C(0), G1 = C(0), G2 = C(0);
-#pragma unroll
-            for (int e = 0; e < kQ - 1; ++e) {
-                if (!((grp >> e) & 1u)) continue;
-                const int d = kOPP[e];
-                if (kCX[d] > 0) G0 += v[e]; else if (kCX[d] < 0) G0 -= v[e];
-                if (kCY[d] > 0) G1 += v[e]; else if (kCY[d] < 0) G1 -= v[e];
-                if (kCZ[d] > 0) G2 += v[e]; else if (kCZ[d] < 0) G2 -= v[e];
-            }
-            put_record<P>(s, gg, cell_off + slot, G0, G1, G2, grp);
-        }
-    };
-    if (s.listmode) {
-        const int lb = tl % ntx, z = tl / ntx;
-        const int cnt = s.ccnt[uni(M->pz_off) + z];
-        for (int lbx = lb; lbx * 256 < cnt; lbx += ntx) {
-            const int kk = lbx * 256 + (int)threadIdx.x;
-            if (kk >= cnt) break;
-            const int c = s.clist[cell_off + (long long)z * nxy + kk];
-            records(c, CMP ? z * nxy + kk : c);
-        }
-    } else {
-        const int bxl = uni(M->bx_log2);
-        const int lx = threadIdx.x & ((1 << bxl) - 1), ly = threadIdx.x >> bxl;
-        const int tx = tl % ntx, trem = tl / ntx, ty = trem % nty, tz = trem / nty;
-        const int i = (tx << bxl) + lx, j = ty * uni(M->by) + ly;
-        if (i >= nx || j >= ny) return;
-        const int z0 = tz * s.nzt, z1 = min(z0 + s.nzt, nz);
-        for (int z = z0; z < z1; ++z) {
-            const int c = (z * ny + j) * nx + i;
-            records(c, c);
-        }
-    }
-}
-
 // Pull streaming (Eq. stream), stationary half-way walls, moving half-way walls on the
 // particles (Eq. mem, from the node's link words), the density faces (Sec. 2.4), BGK
 // collision (Eqs. bgk, BGKequili, rhoAndU) and probe partial sums.
@@ -1151,6 +1026,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
     long long ti = t + 1;
     if (ti > t_n + 1) ti = t_n + 1;
     const C drho_in = (C)(s.wave[uni(M->wave_off) + ti] - rho_fd);
+    // compact storage: every listed node's compact word is written here after a list rebuild
+    // or a full copy of the node map, and read from its slot otherwise
+    const bool full_compact = CMP && (*s.relist_at == t || *s.lwc_bad == t);
 
     // CMP: compact storage (node lists, populations at the nodes' ranks in the lists)
     const bool lists = CMP || s.listmode != 0;
@@ -1348,7 +1226,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
             const bool v = kk < cnt;
             const int c = v ? s.clist[cell_off + (long long)z * nxy + kk] - z * nxy : 0;
             // compact storage: the node's first link word (or the solid marker) at its slot
-            const unsigned long long wcl = (CMP && v) ? s.lwc[cell_off + (long long)z * nxy + kk] : 0ull;
+            unsigned long long wcl = (CMP && v) ? s.lwc[cell_off + (long long)z * nxy + kk] : 0ull;
+            if (CMP && full_compact && v) {
+                const int cell = z * nxy + c;
+                wcl = compact_word(s.lw[cell_off + cell], own[cell] >= 0);
+                s.lwc[cell_off + (long long)z * nxy + kk] = wcl;
+            }
             const int jj = c / nx;
             const uint2 *lrt = nullptr;
             int jb = 0, nrows = 0;
@@ -1418,9 +1301,11 @@ __device__ __forceinline__ int div_uni(int n, int d, double inv)
     return q;
 }
 
-constexpr int kLinksBlock = 64;
-constexpr int kLinkBatch = 2;
-constexpr int kLinkScan = 4;  // shell cells per lane per scan round of a rebuilt chunk
+constexpr int kLinksWaves = 4;   // chunks per workgroup of the link pass
+constexpr int kLinkScan = 2;     // candidate cells per lane per scan round of a rebuilt chunk
+constexpr int kLinkLds = 320;    // entries of a rebuilt chunk kept in LDS for its link-set sums
+constexpr int kCellLds = kLinkLds; // candidate cells of a rebuilt chunk listed at a time
+
 // Direction masks over the links e (d = e*, c_d = -c_e), for sums over a node's links by
 // counting: per axis and weight class (w = 1/18 on the axes, e < 6; 1/36 on the
 // diagonals) the links whose c_d component is +1 or -1 ...
@@ -1445,42 +1330,77 @@ constexpr unsigned pair_mask(int a, int b, int sign)
     return m;
 }
 
-// Rebuild of one chunk of a particle's shell list (the wave of the calling lanes, for
-// particle p): when the shell list was rebuilt, the node lists were rebuilt (storage slots
-// move) or a node within one plane of the chunk's slab changed owner in the previous step,
-// the chunk's entries that hold links of p are found again, compacted in list order, and
-// its link-set sums recomputed; every other chunk keeps its entries.  It reads the link
-// words of this step (after the refresh) and no link record: the record kernel runs it in
-// waves of its own before its node waves, and the link pass reads the entries.
-template <bool NR>
-__device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk, long long t, int *lc, unsigned *lg)
+// Rows of nodes around a centre: the two intervals of x (unwrapped, relative to the integer
+// base) whose distance from the centre lies between the radii of inner2 and outer2 (squared;
+// inner2 <= 0: one interval), for a row at squared distance rho2 from the axis through the
+// centre; fx is the centre's x relative to the base.  FP32, widened by eps: a superset, whose
+// nodes are then tested exactly.
+struct RowSpan { int a0, a1, b0, b1; };
+__device__ __forceinline__ RowSpan row_span(float rho2, float fx, float inner2, float outer2)
 {
-    const int par = (int)(t & 1);
-    const int lane = threadIdx.x & 63;
-    // the chunk's state is loaded together with p's lattice, before the checks that need
-    // the lattice (everything here is indexed by p < ptot)
-    const int m = uni(s.pmem[p]);
-    const double *Xo = s.X[par];
-    const double X0 = Xo[3 * p], X1 = Xo[3 * p + 1], X2 = Xo[3 * p + 2];
-    const int k0 = s.lchunk[p * (kChunks + 1) + chunk], k1 = s.lchunk[p * (kChunks + 1) + chunk + 1];
-    // (a list rebuild under compact storage moves the nodes' storage slots)
-    const bool fresh = (s.lreb[p] == t - 1) || (s.ldirty[p * kChunks + chunk] == t - 1) ||
-                       (s.compact && *s.relist_at == t);
-    if (!fresh) return;
-    const MemberDev *M = s.mem + m;
-    const int pl = p - uni(M->p_off);
-    if (pl >= uni(M->np)) return;
+    constexpr float eps = 1e-4f;
+    RowSpan r = {0, -1, 0, -1};
+    const float h2 = outer2 - rho2;
+    if (h2 < 0.0f) return r;
+    const float h = sqrtf(h2) + eps;
+    const float l2 = inner2 - rho2;
+    const int lo = (int)ceilf(fx - h), hi = (int)floorf(fx + h);
+    if (l2 <= 0.0f) {
+        r.a0 = lo; r.a1 = hi;
+        return r;
+    }
+    const float l = sqrtf(l2) - eps;
+    const int ml = (int)floorf(fx - l), mr = (int)ceilf(fx + l);
+    r.a0 = lo; r.a1 = ml;
+    r.b0 = max(mr, ml + 1); r.b1 = hi;
+    return r;
+}
 
-    const int nx = uni(M->nx), ny = uni(M->ny);
+// Node range [lo, hi] of one axis (unwrapped) within h of c: clipped on a bounded axis, at
+// most one period, centred on c, on a periodic one.
+__device__ __forceinline__ void near_range(double c, double h, int n, int per, int &lo, int &hi)
+{
+    lo = (int)ceil(c - h);
+    hi = (int)floor(c + h);
+    if (per) {
+        if (hi - lo + 1 > n) {
+            lo = (int)ceil(c - 0.5 * (double)n);
+            hi = lo + n - 1;
+        }
+    } else {
+        lo = max(lo, 0);
+        hi = min(hi, n - 1);
+    }
+}
+
+// Margin of the FP32 row tests for spheres of radius R: rounding of squared distances, of
+// order R^2 2^-23, shifts a radius by about R 2^-23.
+__device__ __forceinline__ double row_margin(double R) { return 2e-5 + 1e-6 * R; }
+
+// Rebuild of one chunk of a particle's link entries, the nodes with links of p in a z-slab
+// around it (by the wave of the calling lanes): needed when the slabs were laid out anew, the
+// node lists were rebuilt (storage slots move) or a link word of the slab changed in the
+// previous step; every other chunk keeps its entries.  The candidates are the nodes with R <
+// |x - X| <= R + sqrt(2) (a link's source lies inside p), found row by row from the sphere's
+// equation, so the rebuild loads only their link words: one round of loads for the usual
+// chunk (about 190 candidates at R = 8.5), then the slots of the nodes that have links.
+// Returns the number of entries.
+template <bool NR>
+__device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M, int p, int chunk, double X0, double X1,
+                                              double X2, int *cells, int2 *segs, int *lc, unsigned *lg)
+{
+    const int lane = threadIdx.x & 63;
+    const int pl = p - uni(M->p_off);
+    const int nx = uni(M->nx), ny = uni(M->ny), nz = uni(M->nz);
     const int per0 = uni(M->per[0]), per1 = uni(M->per[1]), per2 = uni(M->per[2]);
     const double box0 = uni(M->box[0]), box1 = uni(M->box[1]), box2 = uni(M->box[2]);
     const long long cell_off = uni(M->cell_off);
     const double rho_f = uni(M->rho_f);
     const int nxy = nx * ny;
-    const long long lbase = (long long)p * s.lcap;
-    int *xc = s.xcell + lbase + k0;
-    int *xs = s.xslot + lbase + k0;
-    unsigned *xg = s.xgrp + lbase + k0;
+    const long long lbase = ((long long)p * kChunks + chunk) * s.xcap;
+    int *xc = s.xcell + lbase;
+    int *xs = s.xslot + lbase;
+    unsigned *xg = s.xgrp + lbase;
     const double R0 = s.Xref[3 * p], R1 = s.Xref[3 * p + 1], R2 = s.Xref[3 * p + 2];
     const double inv_nxy = 1.0 / (double)nxy, inv_nx = 1.0 / (double)nx;
 
@@ -1543,27 +1463,104 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
         zwl[0] += w00; zwl[1] += w01; zwl[2] += w02; zwl[3] += w11; zwl[4] += w12; zwl[5] += w22;
     };
 
-    // (1) the chunk's shell-list entries that hold links of p, compacted in list order;
-    // kept from the previous step unless the list was rebuilt or a node within one plane
-    // of the chunk's slab changed owner in the previous step (the refresh of this step
-    // has brought the link words up to date)
+    // (1) the chunk's candidates in (z, y, x) order, kCellLds at a time, and of them the
+    // nodes that hold links of p
     int cntx = 0;
-    {
-        // kLinkScan cells per lane and round: their list masks and cells, then their link
-        // words, then the second words and storage slots are loaded in three rounds
-        // instead of three per cell; the cells are then taken in list order
-        for (int base = k0; base < k1; base += kLinksBlock * kLinkScan) {
+    const double R = s.R[p], mrg = row_margin(R);
+    const double reach = R + 1.4142135623730951 + mrg, skip = R - mrg;
+    const float inner2 = skip > 0.0 ? (float)(skip * skip) : -1.0f, outer2 = (float)(reach * reach);
+    int y0, y1, x0, x1;
+    near_range(X0, reach, nx, per0, x0, x1);
+    near_range(X1, reach, ny, per1, y0, y1);
+    const int ix = (int)floor(X0);
+    const float fx = (float)(X0 - (double)ix);
+    // the slab's planes, unwrapped next to X_ref (at most one period, or the bounded extent)
+    const int zr0 = s.lzr[2 * p], hz = s.lzr[2 * p + 1];
+    const int zs = per2 ? zr0 + chunk * hz : max(zr0 + chunk * hz, 0);
+    const int ze = min(zr0 + (chunk + 1) * hz, per2 ? zr0 + nz : nz);
+    const int nj = max(y1 - y0 + 1, 0), nrow = nj * max(ze - zs, 0);
+    const double inv_nj = 1.0 / (double)max(nj, 1);
+    for (int row0 = 0; row0 < nrow; row0 += 128) {
+        // two consecutive rows per lane (a usual slab has about 70)
+        RowSpan sp[2];
+        int base_cell[2], na[2], nb[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int row = row0 + 2 * lane + h;
+            sp[h] = {0, -1, 0, -1};
+            base_cell[h] = 0;
+            if (row < nrow) {
+                const int kz = div_uni(row, nj, inv_nj), ky = row - kz * nj;
+                int zz = zs + kz, yy = y0 + ky;
+                const double dy = (double)yy - X1;
+                if (per2) zz = ((zz % nz) + nz) % nz;
+                if (per1) yy = yy < 0 ? yy + ny : (yy >= ny ? yy - ny : yy);
+                const double dz = mimg((double)zz - X2, per2, box2);
+                sp[h] = row_span((float)(dy * dy + dz * dz), fx, inner2, outer2);
+                sp[h].a0 = max(sp[h].a0, x0 - ix); sp[h].b0 = max(sp[h].b0, x0 - ix);
+                sp[h].a1 = min(sp[h].a1, x1 - ix); sp[h].b1 = min(sp[h].b1, x1 - ix);
+                base_cell[h] = zz * nxy + yy * nx;
+            }
+            na[h] = max(sp[h].a1 - sp[h].a0 + 1, 0);
+            nb[h] = max(sp[h].b1 - sp[h].b0 + 1, 0);
+        }
+        const int own_n = na[0] + nb[0] + na[1] + nb[1];
+        int inc = own_n;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += o;
+        }
+        const int total = __builtin_amdgcn_readlane(inc, 63);
+        // the lane's four runs of nodes: where each starts in the list, its cell and first x
+        {
+            int at = inc - own_n;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                segs[4 * lane + 2 * h] = make_int2(base_cell[h], ix + sp[h].a0 - at);
+                segs[4 * lane + 2 * h + 1] = make_int2(base_cell[h], ix + sp[h].b0 - (at + na[h]));
+                at += na[h] + nb[h];
+            }
+        }
+        for (int part = 0; part < total; part += kCellLds) {
+        const int npart = min(total - part, kCellLds);
+        // a mark at the first node of each run; a running maximum of the marks then gives each
+        // lane its node's run (the lanes writing out their runs node by node took 10 us)
+        for (int k = lane; k < npart; k += 64) cells[k] = 0;
+        wave_fence();
+        {
+            int at = inc - own_n - part;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (na[h] > 0 && at + na[h] > 0 && at < npart) cells[max(at, 0)] = 4 * lane + 2 * h + 1;
+                at += na[h];
+                if (nb[h] > 0 && at + nb[h] > 0 && at < npart) cells[max(at, 0)] = 4 * lane + 2 * h + 2;
+                at += nb[h];
+            }
+        }
+        wave_fence();
+        int run = 0;
+        // kLinkScan cells per lane and round, their link words loaded together; the cells are
+        // then taken in list order
+        for (int base = 0; base < npart; base += 64 * kLinkScan) {
             unsigned mk[kLinkScan];
             int cl[kLinkScan];
 #pragma unroll
             for (int b = 0; b < kLinkScan; ++b) {
-                const int k = base + b * kLinksBlock + lane;
-                // (every lane loads: past the chunk's end it reads the chunk's first entry)
-                const int kc = k < k1 ? k : k0;
-                const unsigned mkr = s.lmask[lbase + kc];
-                const int clr = s.lcell[lbase + kc];
-                mk[b] = k < k1 ? mkr : 0u;
-                cl[b] = k < k1 ? clr : 0;
+                const int k = base + b * 64 + lane;
+                mk[b] = k < npart ? 1u : 0u;
+                int v = cells[min(k, npart - 1)];
+                v = max(v, dpp_i<0x111, 0xF>(v, 0)); // row_shr 1, 2, 4, 8: maxima within rows of 16
+                v = max(v, dpp_i<0x112, 0xF>(v, 0));
+                v = max(v, dpp_i<0x114, 0xF>(v, 0));
+                v = max(v, dpp_i<0x118, 0xF>(v, 0));
+                v = max(v, dpp_i<0x142, 0xA>(v, 0)); // row_bcast 15, 31: carried over the rows
+                v = max(v, dpp_i<0x143, 0xC>(v, 0));
+                v = max(v, run);
+                run = __builtin_amdgcn_readlane(v, 63);
+                const int2 sg = segs[v - 1];
+                int x = sg.y + part + min(k, npart - 1);
+                if (per0) x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
+                cl[b] = sg.x + x;
             }
             unsigned long long w0b[kLinkScan];
 #pragma unroll
@@ -1571,23 +1568,11 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
                 const unsigned long long wr = s.lw[cell_off + cl[b]];
                 w0b[b] = mk[b] != 0u ? wr : 0ull;
             }
-            unsigned long long w1b[kLinkScan];
-            int nsb[kLinkScan];
-#pragma unroll
-            for (int b = 0; b < kLinkScan; ++b) {
-                if (((unsigned)w0b[b] & 0x3ffffu) == 0u) w0b[b] = 0ull;
-                w1b[b] = (w0b[b] >> 62) ? s.lw[s.ncell_total + cell_off + cl[b]] : 0ull;
-                {
-                    const int cell = cl[b], kk = div_uni(cell, nxy, inv_nxy), rem = cell - kk * nxy;
-                    const int jj = div_uni(rem, nx, inv_nx);
-                    const int ns = node_slot(s, M, cell, rem - jj * nx, jj, kk);
-                    nsb[b] = w0b[b] != 0ull ? ns : 0;
-                }
-            }
 #pragma unroll
             for (int b = 0; b < kLinkScan; ++b) {
                 const int cell = cl[b];
-                const unsigned long long w0 = w0b[b], w1 = w1b[b];
+                const unsigned long long w0 = ((unsigned)w0b[b] & 0x3ffffu) != 0u ? w0b[b] : 0ull;
+                const unsigned long long w1 = (w0 >> 62) ? s.lw[s.ncell_total + cell_off + cell] : 0ull;
                 const int ng = (w0 >> 62) ? 4 : 2;
                 // one entry per slot of p at the node: one pass, or more in a set with a
                 // narrow lattice, where a node can hold links into two images of p (one slot
@@ -1606,14 +1591,13 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
                     if (bal == 0ull) break;
                     if (has) {
                         const int at = cntx + __popcll(bal & ((1ull << lane) - 1ull));
-                        if (at < k1 - k0) {
-                            xc[at] = (int)((unsigned)cell | ((unsigned)slot << 30));
-                            xs[at] = nsb[b];
+                        if (at < s.xcap) {
+                            xc[at] = cell;
                             xg[at] = grp;
                             // (the first kLinkLds entries also in this wave's LDS, where the
                             // link-set sums read them)
                             if (at < kLinkLds) {
-                                lc[at] = (int)((unsigned)cell | ((unsigned)slot << 30));
+                                lc[at] = cell;
                                 lg[at] = grp;
                             }
                         } else {
@@ -1623,10 +1607,14 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
                     } else {
                         g0 = ng;
                     }
-                    cntx = min(cntx + __popcll(bal), k1 - k0);
+                    cntx = min(cntx + __popcll(bal), s.xcap);
                 }
             }
         }
+        wave_fence(); // (the next part marks the list again once every lane has read it)
+        }
+    }
+    {
         if (lane == 0) s.xcnt[p * kChunks + chunk] = cntx;
         // (the link-set sums read the entries back, from LDS, or from memory for a chunk
         // with more than kLinkLds entries: the wave's writes are made visible to the wave
@@ -1642,13 +1630,32 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
         }
     }
     const bool from_lds = cntx <= kLinkLds;
+    // storage slots of the entries' nodes (kept in LDS too, over the candidates), four a lane
+    // in flight
+    for (int base = 0; base < cntx; base += 256) {
+        int cell[4], ns[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int k = min(base + 64 * b + lane, cntx - 1);
+            cell[b] = from_lds ? lc[k] : xc[k];
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int kk = div_uni(cell[b], nxy, inv_nxy), rem = cell[b] - kk * nxy;
+            const int jj = div_uni(rem, nx, inv_nx);
+            ns[b] = node_slot(s, M, cell[b], rem - jj * nx, jj, kk);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int k = base + 64 * b + lane;
+            if (k >= cntx) continue;
+            xs[k] = ns[b];
+            if (from_lds) cells[k] = ns[b];
+        }
+    }
 
-
-    // Positions of the entries' nodes relative to the shell list's reference point X_ref,
-    // xr = x - X_ref (minimum image; X_ref moves only when the shell list is rebuilt, which
-    // rebuilds the entries).  With delta = X - X_ref, r = xr - delta, so the torque is
-    // sum xr x G - delta x F0, and Z follows from sums over the link set alone:
-    // S = sum S_n, Qx = sum [xr] S_n, Wx = sum [xr] S_n [xr]^T (the motion kernel applies delta).
+    // Positions of the entries' nodes relative to the particle's reference point X_ref, as in
+    // the link pass.
     const double z18 = rho_f / 3.0, z36 = rho_f / 6.0;                  // 6 rho_f w_d
     // (in a set with a narrow lattice the entry's image of p is the one that holds its link
     // group: its arm from the current centre X, as group_arm, plus the small displacement
@@ -1672,9 +1679,9 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
     // entries in list order
     if (!NR) {
         if (from_lds)
-            for (int k = lane; k < cntx; k += kLinksBlock) add_link_set((int)((unsigned)lc[k] & 0x3fffffffu), lg[k]);
+            for (int k = lane; k < cntx; k += 64) add_link_set(lc[k], lg[k]);
         else
-            for (int k = lane; k < cntx; k += kLinksBlock) add_link_set((int)((unsigned)xc[k] & 0x3fffffffu), xg[k]);
+            for (int k = lane; k < cntx; k += 64) add_link_set(xc[k], xg[k]);
         int si[15];
 #pragma unroll
         for (int c = 0; c < 15; ++c) si[c] = wave_sum_i(zsi[c]);
@@ -1738,10 +1745,10 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
         double zs[21];
 #pragma unroll
         for (int c = 0; c < 21; ++c) zs[c] = 0.0;
-        for (int k = lane; k < cntx; k += kLinksBlock) {
+        for (int k = lane; k < cntx; k += 64) {
             const unsigned g = from_lds ? lg[k] : xg[k];
             double x0, x1, x2;
-            rel_pos((int)((unsigned)(from_lds ? lc[k] : xc[k]) & 0x3fffffffu), g, x0, x1, x2);
+            rel_pos(from_lds ? lc[k] : xc[k], g, x0, x1, x2);
             // S_n = sum 6 w_d rho_f c_d c_d^T over the node's links, from counts
             auto diag = [&](int axis) {
                 return z18 * (double)__popc(g & (link_mask(axis, 1, false) | link_mask(axis, -1, false))) +
@@ -1790,10 +1797,10 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
             for (int c = 0; c < 21; ++c) zc[c] = zs[c];
         }
     }
-
+    return cntx;
 }
 
-// Link pass, one wave per (particle p, chunk of p's shell list).  A link of p is a fluid
+// Link pass, one wave per (particle p, chunk of p's link entries).  A link of p is a fluid
 // node x and a direction e whose source x - c_e lies in p; with d = e* pointing into p,
 // Eq. (fFS) with Eq. (mem) substituted gives
 //   F = c_d f~_d(x,t) - c_e f_e(x,t+1) = 2 c_d f~_d(x,t) - (2 w_d / c_s^2) rho_f c_d (c_d . V_b),
@@ -1805,47 +1812,67 @@ __device__ __forceinline__ void rebuild_chunk(const DevSet &s, int p, int chunk,
 // summed from the deviations f~_d - w_d rho_f (the rest part 2 rho_f sum w_d c_d and S come
 // from counts of links per direction class), the sums over the chunk in FP64 in a fixed
 // order; the motion kernel adds the chunks in chunk order and solves for (V, Omega).
-// The deviation sums of a node's links come from the record k_records wrote for the node's
-// slot in this step.
+// A stale chunk's entries are found again first (rebuild_chunk).  Each lane then takes the
+// entries of its rank and reads the populations of the entry's link directions at the node's
+// own slot: the entries are in (z, y, x) order, so along a row neighbouring lanes read
+// neighbouring values.  Bound by those gathers and their latency.  (Records of G per node and
+// slot, written by a kernel over every listed node and gathered here, cost 30 + 18 us on the
+// FCC wave case (FP64 45 + 25) against 31 us (48) for this kernel, 23 us without stale slabs: the records
+// took a pass over the link words of every node and 16 bytes per link node each way.)
 template <int P, bool NR>
-__global__ __launch_bounds__(kLinksBlock) void k_links(DevSet s, int mode, int only)
+__global__ __launch_bounds__(64 * kLinksWaves) void k_links(DevSet s, int mode, int only)
 {
+    using S = typename Prec<P>::S;
+    using C = typename Prec<P>::C;
+    __shared__ int l_cells[kLinksWaves][kCellLds], l_c[kLinksWaves][kLinkLds];
+    __shared__ unsigned l_g[kLinksWaves][kLinkLds];
+    __shared__ int2 l_segs[kLinksWaves][256];
     const long long t = *s.tstep;
     const int par = (int)(t & 1);
-    const int lane = threadIdx.x;
-    const int p = blockIdx.x / kChunks, chunk = blockIdx.x - p * kChunks;
-    if (p >= s.ptot || mode != 0) return;
+    const int lane = threadIdx.x & 63, wv = (int)(threadIdx.x >> 6);
+    // two workgroups per particle: first the equatorial slabs of every particle, which hold
+    // most of the entries, then the polar ones (in slab order the long waves of the last
+    // workgroups ran alone: 39 us instead of 36 on the FCC wave case); particles in XCD order,
+    // neighbours sharing lines of the populations (45 us in launch order)
+    static_assert(kChunks == 2 * kLinksWaves, "two workgroups per particle");
+    if (s.ptot == 0 || mode != 0) return;
+    const int half = (int)blockIdx.x >= s.ptot ? 1 : 0;
+    const int p = uni(xcd_swizzle((int)blockIdx.x - half * s.ptot, s.ptot));
+    const int chunk = uni(half ? (wv < kLinksWaves / 2 ? wv : wv + kLinksWaves) : wv + kLinksWaves / 2);
     // the chunk's state is loaded together with p's lattice, before the checks that need
     // the lattice (everything here is indexed by p < ptot)
     const int m = uni(s.pmem[p]);
     const double *Xo = s.X[par];
     const double X0 = Xo[3 * p], X1 = Xo[3 * p + 1], X2 = Xo[3 * p + 2];
-    const int k0 = s.lchunk[p * (kChunks + 1) + chunk], k1 = s.lchunk[p * (kChunks + 1) + chunk + 1];
-    // the chunk's entries (rebuilt by the record kernel of this step where they changed)
-    const int cntx = s.xcnt[p * kChunks + chunk];
+    const double R0 = s.Xref[3 * p], R1 = s.Xref[3 * p + 1], R2 = s.Xref[3 * p + 2];
+    // (a list rebuild under compact storage moves the nodes' storage slots)
+    const bool stale = (s.lreb[p] == t - 1) || (s.ldirty[p * kChunks + chunk] == t - 1) ||
+                       (s.compact && *s.relist_at == t);
+    int cntx = s.xcnt[p * kChunks + chunk];
     const MemberDev *M = s.mem + m;
     const int pl = p - uni(M->p_off);
     if (pl >= uni(M->np)) return;
     if (only >= 0 && m != only) return;
+    if (stale) cntx = rebuild_chunk<NR>(s, M, p, chunk, X0, X1, X2, l_cells[wv], l_segs[wv], l_c[wv], l_g[wv]);
+    const bool in_lds = stale && cntx <= kLinkLds; // (the wave's own LDS)
 
     const int nx = uni(M->nx), ny = uni(M->ny);
     const int per0 = uni(M->per[0]), per1 = uni(M->per[1]), per2 = uni(M->per[2]);
     const double box0 = uni(M->box[0]), box1 = uni(M->box[1]), box2 = uni(M->box[2]);
-    const long long cell_off = uni(M->cell_off);
+    const unsigned nc = (unsigned)uni(M->ncell);
+    const S *A = (const S *)(par ? s.popB : s.popA) + uni(M->pop_off);
     const double rho_f = uni(M->rho_f);
     const bool rest_free = uni(M->rest_free) != 0;
     const int nxy = nx * ny;
-    const long long lbase = (long long)p * s.lcap;
-    const int *xc = s.xcell + lbase + k0;
-    const int *xs = s.xslot + lbase + k0;
-    const unsigned *xg = s.xgrp + lbase + k0;
-    const double R0 = s.Xref[3 * p], R1 = s.Xref[3 * p + 1], R2 = s.Xref[3 * p + 2];
+    const long long lbase = ((long long)p * kChunks + chunk) * s.xcap;
+    const int *xc = s.xcell + lbase;
+    const int *xs = s.xslot + lbase;
+    const unsigned *xg = s.xgrp + lbase;
     const double inv_nxy = 1.0 / (double)nxy, inv_nx = 1.0 / (double)nx;
 
-
-    // Positions of the entries' nodes relative to the shell list's reference point X_ref,
-    // xr = x - X_ref (minimum image; X_ref moves only when the shell list is rebuilt, which
-    // rebuilds the entries).  With delta = X - X_ref, r = xr - delta, so the torque is
+    // Positions of the entries' nodes relative to the particle's reference point X_ref,
+    // xr = x - X_ref (minimum image; X_ref moves only with the slabs, which rebuilds the
+    // entries).  With delta = X - X_ref, r = xr - delta, so the torque is
     // sum xr x G - delta x F0, and Z follows from sums over the link set alone:
     // S = sum S_n, Qx = sum [xr] S_n, Wx = sum [xr] S_n [xr]^T (the motion kernel applies delta).
     const double a18 = 2.0 * rho_f / 18.0, a36 = 2.0 * rho_f / 36.0;   // 2 rho_f w_d
@@ -1866,58 +1893,64 @@ __global__ __launch_bounds__(kLinksBlock) void k_links(DevSet s, int mode, int o
         }
     };
 
-    // (3) F0 = sum 2 c_d f~_d and sum xr x (the node's part of F0) over the entries
+    // F0 = sum 2 c_d f~_d and sum xr x (the node's part of F0) over the entries
     double acc[kLinkComp];
 #pragma unroll
     for (int c = 0; c < kLinkComp; ++c) acc[c] = 0.0;
-    for (int base = 0; base < cntx; base += kLinksBlock * kLinkBatch) {
-        int cellb[kLinkBatch];
-        unsigned gb[kLinkBatch];
-        // (records are kept in the collision precision until they are summed)
-        typename Prec<P>::C Db[kLinkBatch][3];
-#pragma unroll
-        for (int b = 0; b < kLinkBatch; ++b) {
-            const int k = base + b * kLinksBlock + lane;
-            const bool v = k < cntx;
-            const int kv = v ? k : 0;
-            const unsigned ent = v ? (unsigned)xc[kv] : 0u;
-            cellb[b] = (int)(ent & 0x3fffffffu);
-            // (a node with links is fluid, hence listed; entries past the count read the
-            // first record and carry no directions)
-            const int xsr = xs[kv];
-            const unsigned xgr = xg[kv];
-            const int at = v ? max(xsr, 0) : 0;
-            gb[b] = v ? xgr : 0u;
-            if constexpr (sizeof(typename Prec<P>::C) == 4) {
-                const float4 v4 = reinterpret_cast<const float4 *>(s.frec)[(int)(ent >> 30) * s.ncell_total + cell_off + at];
-                Db[b][0] = v4.x; Db[b][1] = v4.y; Db[b][2] = v4.z;
-            } else {
-                double G0, G1, G2;
-                (void)get_record<P>(s, (int)(ent >> 30), cell_off + at, G0, G1, G2);
-                Db[b][0] = G0; Db[b][1] = G1; Db[b][2] = G2;
-            }
+    // (the entries of the next round are loaded while this round's populations are)
+    struct Entry { int cell; unsigned at, g; };
+    auto entry = [&](int k) {
+        const int kv = k < cntx ? k : 0;
+        Entry en;
+        if (in_lds) {
+            en.cell = l_c[wv][kv];
+            en.at = (unsigned)max(l_cells[wv][kv], 0);
+            en.g = k < cntx ? l_g[wv][kv] : 0u;
+        } else {
+            en.cell = xc[kv];
+            en.at = (unsigned)max(xs[kv], 0); // (a node with links is fluid, hence listed)
+            const unsigned g = xg[kv];
+            en.g = k < cntx ? g : 0u;
         }
+        return en;
+    };
+    Entry next = entry(lane);
+    for (int base = 0; base < cntx; base += 64) {
+        const int cell = next.cell;
+        const unsigned at = next.at, g = next.g;
+        // every lane loads for every direction, a lane without the link the array's first
+        // element (one shared line)
+        S raw[kQ - 1];
 #pragma unroll
-        for (int b = 0; b < kLinkBatch; ++b) {
-            const unsigned g = gb[b];
-            if (g == 0u) continue;
-            // G = sum 2 c_d (f~_d - w_d rho_f) + 2 rho_f sum w_d c_d
-            auto rest = [&](int axis) {
-                const int na = (int)__popc(g & link_mask(axis, 1, false)) - (int)__popc(g & link_mask(axis, -1, false));
-                const int nd = (int)__popc(g & link_mask(axis, 1, true)) - (int)__popc(g & link_mask(axis, -1, true));
-                return a18 * (double)na + a36 * (double)nd;
-            };
-            // (rest_free: without the rest state's part)
-            const double G0 = 2.0 * (double)Db[b][0] + (rest_free ? 0.0 : rest(0));
-            const double G1 = 2.0 * (double)Db[b][1] + (rest_free ? 0.0 : rest(1));
-            const double G2 = 2.0 * (double)Db[b][2] + (rest_free ? 0.0 : rest(2));
-            double x0, x1, x2;
-            rel_pos(cellb[b], g, x0, x1, x2);
-            acc[0] += G0; acc[1] += G1; acc[2] += G2;
-            acc[3] += x1 * G2 - x2 * G1;
-            acc[4] += x2 * G0 - x0 * G2;
-            acc[5] += x0 * G1 - x1 * G0;
+        for (int e = 0; e < kQ - 1; ++e) raw[e] = ldo(A, ((g >> e) & 1u) ? (unsigned)kOPP[e] * nc + at : 0u);
+        next = entry(base + 64 + lane);
+        if (g == 0u) continue;
+        // G = sum c_d (f~_d - w_d rho_f), in the collision precision
+        C D0 = C(0), D1 = C(0), D2 = C(0);
+#pragma unroll
+        for (int e = 0; e < kQ - 1; ++e) {
+            const int d = kOPP[e];
+            const C v = ((g >> e) & 1u) ? decode_dev<P>(raw[e], d, rho_f) : C(0);
+            if (kCX[d] > 0) D0 += v; else if (kCX[d] < 0) D0 -= v;
+            if (kCY[d] > 0) D1 += v; else if (kCY[d] < 0) D1 -= v;
+            if (kCZ[d] > 0) D2 += v; else if (kCZ[d] < 0) D2 -= v;
         }
+        // sum 2 c_d f~_d = 2 G + 2 rho_f sum w_d c_d
+        auto rest = [&](int axis) {
+            const int na = (int)__popc(g & link_mask(axis, 1, false)) - (int)__popc(g & link_mask(axis, -1, false));
+            const int nd = (int)__popc(g & link_mask(axis, 1, true)) - (int)__popc(g & link_mask(axis, -1, true));
+            return a18 * (double)na + a36 * (double)nd;
+        };
+        // (rest_free: without the rest state's part)
+        const double G0 = 2.0 * (double)D0 + (rest_free ? 0.0 : rest(0));
+        const double G1 = 2.0 * (double)D1 + (rest_free ? 0.0 : rest(1));
+        const double G2 = 2.0 * (double)D2 + (rest_free ? 0.0 : rest(2));
+        double x0, x1, x2;
+        rel_pos(cell, g, x0, x1, x2);
+        acc[0] += G0; acc[1] += G1; acc[2] += G2;
+        acc[3] += x1 * G2 - x2 * G1;
+        acc[4] += x2 * G0 - x0 * G2;
+        acc[5] += x0 * G1 - x1 * G0;
     }
 #pragma unroll
     for (int c = 0; c < kLinkComp; ++c) acc[c] = wave_sum(acc[c]);
@@ -2121,7 +2154,6 @@ __global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode
     if (lane == 0) {
         if (build) {
             s.nnear[p] = min(near_total, kNearCap);
-            s.near_at[p] = t;
         }
         if (mode == 0) s.hn[par ^ 1][p] = min(hist_total, kHistCap);
     }
@@ -2283,11 +2315,15 @@ struct RemapCtx {
 
 constexpr int kRemapWaves = 4; // particles per workgroup of the re-projection kernel
 
-// Re-projection (Sec. 2.3), one wave per particle for the common case: the candidates of
-// a small step, from the particle's surface band or shell list, evaluated by the wave's
-// 64 lanes.  A particle that needs its shell list rebuilt (set-up, or motion beyond the
-// shell) and the periodic near-list build use the whole workgroup, one particle after the
-// other.  Workgroups past the particles reduce the probe planes.
+// Re-projection (Sec. 2.3), one wave per particle.  The nodes whose owner the step can have
+// changed lie within the particle's displacement of its surface, or inside it within the
+// overlap depth with a neighbour; they are found row by row from the sphere's equation (a
+// few FP32 operations per row and no memory, about 360 rows at R = 8.5), queued, and
+// evaluated exactly 64 at a time.  Bound by the latency of its few dependent loads.  (Shell
+// and surface-band lists per particle, read every step and built again by a whole workgroup
+// once the particle had left its shell, cost 25 us per step on the FCC wave case and 370 us
+// on a suspension of 288 moving spheres, where some list was always being built, against
+// 16 and 26 us.)  Waves never synchronise; workgroups past the particles reduce the probe planes.
 template <int P>
 __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
 {
@@ -2295,15 +2331,9 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
     __shared__ double red[4][8];
     __shared__ double nbw[kRemapWaves][kNearCap][4];
     __shared__ int nbidw[kRemapWaves][kNearCap];
-    __shared__ int cnt4[4];
-    __shared__ int cstart[kChunks + 1];
-    __shared__ double accw[kRemapWaves][6];
-    __shared__ double ctxw[kRemapWaves][9]; // x, x_ref unwrapped next to x, lr, dr, overlap depth
-    __shared__ int flagw[kRemapWaves];
-    __shared__ int ncnt[kRemapWaves][4]; // near-list candidates per (particle, wave)
-    // each wave's queue of candidate nodes (cell, owner before the projection or -2)
+    // each wave's queue of candidate nodes
     constexpr int kQueue = 256;
-    __shared__ int qcell[kRemapWaves][kQueue], qwas[kRemapWaves][kQueue];
+    __shared__ int qcell[kRemapWaves][kQueue];
     // the step being completed: copied by the fluid kernel (mode 0); the counter itself is
     // advanced here and read by no workgroup of this kernel
     const long long t = (mode == 0) ? *s.tcopy : *s.tstep;
@@ -2350,13 +2380,14 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
         return (dx * dx + dy * dy) + dz * dz;
     };
 
-    // owner of one node after the motion; conversions of covered / uncovered nodes
-    auto evaluate = [&](const RemapCtx &c, int ii, int jj, int kk, int cell, double d2n, int was_pre,
-                        double (&acc)[6], int &conv) {
+    // owner of one node after the motion; conversion of a covered node; opened: p uncovered it
+    auto evaluate = [&](const RemapCtx &c, int ii, int jj, int kk, int cell, double (&acc)[6], int &conv,
+                        bool &opened) {
         const MemberDev *M = c.M;
         const int p = c.p;
-        const int dims[3] = {M->nx, M->ny, M->nz};
         const int *cur = s.own[par] + M->cell_off;
+        const int was = cur[cell];
+        const double d2n = dist2c(c, ii, jj, kk, c.X[0], c.X[1], c.X[2]);
         // owner: smallest d^2, then smallest index, among the spheres containing the node
         int best = -1;
         double bd = 0.0;
@@ -2372,25 +2403,8 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
             if (best >= 0) { s.own[0][M->cell_off + cell] = best; s.own[1][M->cell_off + cell] = best; }
             return;
         }
-        const int was = (was_pre >= -1) ? was_pre : cur[cell];
         if (best == was) return;
         s.own[par ^ 1][M->cell_off + cell] = best;
-        // the 18 neighbours and their owners before the re-projection (loads together)
-        int nbc[kQ - 1], ow[kQ - 1];
-#pragma unroll
-        for (int e = 0; e < kQ - 1; ++e) {
-            int cc[3] = {ii + kCX[e], jj + kCY[e], kk + kCZ[e]};
-            bool ok = true;
-            for (int a = 0; a < 3; ++a) {
-                if (cc[a] < 0 || cc[a] >= dims[a]) {
-                    if (c.per[a]) cc[a] = cc[a] < 0 ? cc[a] + dims[a] : cc[a] - dims[a];
-                    else ok = false;
-                }
-            }
-            nbc[e] = ok ? (cc[2] * dims[1] + cc[1]) * dims[0] + cc[0] : -1;
-        }
-#pragma unroll
-        for (int e = 0; e < kQ - 1; ++e) ow[e] = nbc[e] >= 0 ? cur[nbc[e]] : -1;
         // (the cached link entries that this change makes stale are marked by the next
         // refresh, which sees which link words actually change)
         const int slot = atomicAdd(s.chgcnt + par, 1);
@@ -2420,69 +2434,85 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
             acc[3] += r1 * j2 - r2 * j1;
             acc[4] += r2 * j0 - r0 * j2;
             acc[5] += r0 * j1 - r1 * j0;
-        } else if (was == p && best < 0) {
-            // Eq. (convertSF): an uncovered node is refilled with f^eq(rho_bar, V_b)
-            // and takes rho_bar V_b from the particle; rho_bar averages the
-            // neighbours that are fluid before and after the re-projection.  Under
-            // compact storage a node outside the lists has its refill parked for the
-            // list rebuild at the start of the next step.
-            unsigned use = 0u;
+        }
+        opened = was == p && best < 0;
+    };
+
+    // Eq. (convertSF): node `cell` uncovered by p is refilled with f^eq(rho_bar, V_b) and takes
+    // rho_bar V_b from the particle; rho_bar averages the neighbours that are fluid before and
+    // after the re-projection.  32 lanes per node: lane e < 18 takes neighbour e, so the node
+    // maps, slots and populations of all neighbours are loaded together (one lane taking them
+    // in turn cost 18 rounds of loads); then lane d < 19 stores population d.  Under compact
+    // storage a node outside the lists has its refill parked for the list rebuild at the start
+    // of the next step.  `on` is the same in a node's lanes.
+    auto refill = [&](const RemapCtx &c, int cell, bool on, double (&acc)[6]) {
+        const MemberDev *M = c.M;
+        const int p = c.p, h = lane & 31;
+        const int nx = M->nx, ny = M->ny, nz = M->nz, nxy = nx * ny, nc = (int)M->ncell;
+        const int *cur = s.own[par] + M->cell_off;
+        S *Bn = (S *)(sn ? s.popB : s.popA) + M->pop_off;
+        const double rho_ff = M->rho_f;
+        const int kk = cell / nxy, rem = cell - kk * nxy, jj = rem / nx, ii = rem - jj * nx;
+        int xx = ii + dir_x(h), yy = jj + dir_y(h), zz = kk + dir_z(h);
+        bool use = on && h < kQ - 1 && (c.per[0] || (xx >= 0 && xx < nx)) && (c.per[1] || (yy >= 0 && yy < ny)) &&
+                   (c.per[2] || (zz >= 0 && zz < nz));
+        xx = wrapc(xx, nx); yy = wrapc(yy, ny); zz = wrapc(zz, nz);
+        const int yc = use ? (zz * ny + yy) * nx + xx : cell;
+        const int ow = cur[yc];
+        const int sl = s.compact ? slot_of(s, M, ii, jj, kk) : cell;
+        int ys = s.compact ? slot_of(s, M, use ? xx : ii, use ? yy : jj, use ? zz : kk) : yc;
+        use = use && ow < 0;
+        if (use) {
+            bool inside = dist2c(c, xx, yy, zz, c.X[0], c.X[1], c.X[2]) <= c.R2;
+            for (int k = 0; k < c.nn && !inside; ++k)
+                inside = dist2c(c, xx, yy, zz, nbw[c.w][k][0], nbw[c.w][k][1], nbw[c.w][k][2]) <=
+                         nbw[c.w][k][3] * nbw[c.w][k][3];
+            use = !inside;
+            if (use && ys < 0) { atomicOr(s.flags, 0x100u); use = false; }
+        }
+        ys = use ? ys : 0;
+        double rr = 0.0;
+        {
+            S raw[kQ];
 #pragma unroll
-            for (int e = 0; e < kQ - 1; ++e) {
-                if (nbc[e] < 0 || ow[e] >= 0) continue;
-                const int yc = nbc[e];
-                const int zc = yc / (dims[0] * dims[1]), rc = yc - zc * dims[0] * dims[1];
-                const int yy = rc / dims[0], xx = rc - yy * dims[0];
-                bool inside = dist2c(c, xx, yy, zc, c.X[0], c.X[1], c.X[2]) <= c.R2;
-                for (int k = 0; k < c.nn && !inside; ++k)
-                    inside = dist2c(c, xx, yy, zc, nbw[c.w][k][0], nbw[c.w][k][1], nbw[c.w][k][2]) <=
-                             nbw[c.w][k][3] * nbw[c.w][k][3];
-                if (!inside) use |= 1u << e;
-            }
-            const int sl = node_slot(s, M, cell, ii, jj, kk);
-            double sum = 0.0;
-            int cnt = 0;
-#pragma unroll 1
-            for (int e = 0; e < kQ - 1; ++e) {
-                if (!((use >> e) & 1u)) continue;
-                int yc = 0;
+            for (int d = 0; d < kQ; ++d) raw[d] = Bn[d * nc + ys];
+            if (use)
 #pragma unroll
-                for (int q = 0; q < kQ - 1; ++q)
-                    if (q == e) yc = nbc[q];
-                if (s.compact) {
-                    const int zc = yc / (dims[0] * dims[1]), rc = yc - zc * dims[0] * dims[1];
-                    const int yy = rc / dims[0];
-                    yc = slot_of(s, M, rc - yy * dims[0], yy, zc);
-                    if (yc < 0) { atomicOr(s.flags, 0x100u); continue; }
-                }
-                double rr = 0.0;
-                for (int d = 0; d < kQ; ++d) rr += (double)ld<P>(Bn, d * nc + yc, d, rho_ff);
-                sum += rr;
-                cnt += 1;
-            }
-            const double rbar = cnt > 0 ? sum / cnt : M->rho_f;
-            const double *Vp = Vs + 3 * p, *Wp = Ws + 3 * p;
-            const double vb0 = Vp[0] + (Wp[1] * r2 - Wp[2] * r1);
-            const double vb1 = Vp[1] + (Wp[2] * r0 - Wp[0] * r2);
-            const double vb2 = Vp[2] + (Wp[0] * r1 - Wp[1] * r0);
+                for (int d = 0; d < kQ; ++d) rr += (double)decode_full<P>(raw[d], d, rho_ff);
+        }
+        for (int off = 16; off >= 1; off >>= 1) rr += __shfl_xor(rr, off, 64);
+        const unsigned long long bal = __ballot(use);
+        const int cnt = __popc((unsigned)(lane < 32 ? bal : bal >> 32));
+        if (!on) return;
+        const double r0 = mimg((double)ii - c.X[0], c.per[0], c.box[0]);
+        const double r1 = mimg((double)jj - c.X[1], c.per[1], c.box[1]);
+        const double r2 = mimg((double)kk - c.X[2], c.per[2], c.box[2]);
+        const double rbar = cnt > 0 ? rr / cnt : rho_ff;
+        const double *Vp = Vs + 3 * p, *Wp = Ws + 3 * p;
+        const double vb0 = Vp[0] + (Wp[1] * r2 - Wp[2] * r1);
+        const double vb1 = Vp[1] + (Wp[2] * r0 - Wp[0] * r2);
+        const double vb2 = Vp[2] + (Wp[0] * r1 - Wp[1] * r0);
+        if (sl >= 0) {
             const double uu = vb0 * vb0 + vb1 * vb1 + vb2 * vb2;
-            if (sl >= 0) {
-#pragma unroll
-                for (int d = 0; d < kQ; ++d)
-                    st<P>(Bn, d * nc + sl, d, (typename Prec<P>::C)feq<double>(d, rbar, vb0, vb1, vb2, uu), rho_ff);
-            } else {
-                const int pi = atomicAdd(s.pcnt + par, 1);
-                if (pi < kPendCap) {
-                    double *rec = s.pbuf[par] + 4 * pi;
-                    rec[0] = rbar; rec[1] = vb0; rec[2] = vb1; rec[3] = vb2;
-                    s.pend[M->cell_off + cell] = pi;
-                    *s.relist_at = t + 1;
-                    atomicOr(s.flags, 0x200u);
-                } else {
-                    atomicOr(s.flags, 0x100u);
-                }
+            if (h < kQ) {
+                const double cu = (double)dir_x(h) * vb0 + (double)dir_y(h) * vb1 + (double)dir_z(h) * vb2;
+                const double w = h == kQ - 1 ? kWd[kQ - 1] : (h < 6 ? kWd[0] : kWd[6]);
+                const double f = w * rbar * (1.0 + 3.0 * cu + 4.5 * (cu * cu) - 1.5 * uu);
+                encode_full<P>(Bn + h * nc + sl, (typename Prec<P>::C)f, w, rho_ff);
             }
-            conv = 1;
+        } else if (h == 0) {
+            const int pi = atomicAdd(s.pcnt + par, 1);
+            if (pi < kPendCap) {
+                double *rec = s.pbuf[par] + 4 * pi;
+                rec[0] = rbar; rec[1] = vb0; rec[2] = vb1; rec[3] = vb2;
+                s.pend[M->cell_off + cell] = pi;
+                *s.relist_at = t + 1;
+                atomicOr(s.flags, 0x200u);
+            } else {
+                atomicOr(s.flags, 0x100u);
+            }
+        }
+        if (h == 0) {
             const double m0 = rbar * vb0, m1 = rbar * vb1, m2 = rbar * vb2;
             acc[0] -= m0; acc[1] -= m1; acc[2] -= m2;
             acc[3] -= r1 * m2 - r2 * m1;
@@ -2491,196 +2521,153 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
         }
     };
 
-    // ------------------------------------------------------------------------------
-    // phase A: one wave per particle
-    // ------------------------------------------------------------------------------
     const int p = blockIdx.x * kRemapWaves + wv;
-    // Per-particle values that depend on nothing else are loaded together, before any
-    // branch (index clamped past the particles): the member, the near list, the reference
-    // state, the first band entries of each lane, and p's position in both buffers.
-    constexpr int kPre = 4; // band entries preloaded per lane
-    bool active = p < s.ptot;
-    const int pc = active ? p : 0;
-    const int m = s.pmem[pc];
-    const int nn_raw = s.nnear[pc];
-    const int q_raw = s.nearl[(long long)pc * kNearCap + (lane & (kNearCap - 1))];
-    const double Rp = s.R[pc];
-    const double Xr_ld[3] = {s.Xref[3 * pc], s.Xref[3 * pc + 1], s.Xref[3 * pc + 2]};
-    const double Xb0[3] = {s.X[0][3 * pc], s.X[0][3 * pc + 1], s.X[0][3 * pc + 2]};
-    const double Xb1[3] = {s.X[1][3 * pc], s.X[1][3 * pc + 1], s.X[1][3 * pc + 2]};
-    const double Xl_ld[3] = {s.Xl[3 * pc], s.Xl[3 * pc + 1], s.Xl[3 * pc + 2]};
-    const double mg_ld = s.margin[pc], rdisp_ld = s.rdisp[pc], rlens_ld = s.rlens[pc];
-    const long long nat_ld = s.near_at[pc];
-    const int bnum = min(s.bcnt[pc], s.bcap);
-    int bc[kPre];
-    float bd[kPre];
+    if (p >= s.ptot) return;
+    // Per-particle values that depend on nothing else are loaded together: the member, the
+    // near list, the reference states, and p's position in both buffers.
+    const int m = s.pmem[p];
+    const int nn = min(s.nnear[p], kNearCap);
+    const int q_near = s.nearl[(long long)p * kNearCap + (lane & (kNearCap - 1))];
+    const double R = s.R[p];
+    const double Xr[3] = {s.Xref[3 * p], s.Xref[3 * p + 1], s.Xref[3 * p + 2]};
+    const double Xb0[3] = {s.X[0][3 * p], s.X[0][3 * p + 1], s.X[0][3 * p + 2]};
+    const double Xb1[3] = {s.X[1][3 * p], s.X[1][3 * p + 1], s.X[1][3 * p + 2]};
+    const double Xl[3] = {s.Xl[3 * p], s.Xl[3 * p + 1], s.Xl[3 * p + 2]};
+    const double Xn[3] = {s.Xn[3 * p], s.Xn[3 * p + 1], s.Xn[3 * p + 2]};
+    const MemberDev *M = s.mem + m;
+    if (p - M->p_off >= M->np || (only >= 0 && m != only)) return;
+    // (no wave stores the due step of a lattice whose near lists are due in this step)
+    const bool near_build = mode == 0 && s.near_due[m] == t;
+    const double skin = s.skin[m];
+    RemapCtx c;
+    c.p = p; c.w = wv; c.M = M;
+    double Xold[3]; // the position of the node map being replaced
+    for (int a = 0; a < 3; ++a) {
+        c.per[a] = M->per[a];
+        c.box[a] = M->box[a];
+        c.X[a] = sp ? Xb1[a] : Xb0[a];
+        Xold[a] = (mode == 1) ? c.X[a] : (par ? Xb1[a] : Xb0[a]);
+    }
+    c.R = R; c.R2 = R * R;
+    c.nn = nn;
+    auto dist = [&](const double *A, const double *B) {
+        double v = 0.0;
 #pragma unroll
-    for (int i = 0; i < kPre; ++i) {
-        const int k = lane + 64 * i;
-        // (every lane loads: past the band's end it reads the first entry)
-        const int kc = (k < bnum) ? k : 0;
-        const int bcr = s.bcell[(long long)pc * s.bcap + kc];
-        const float bdr = s.bdr[(long long)pc * s.bcap + kc];
-        bc[i] = (k < bnum) ? bcr : 0;
-        bd[i] = (k < bnum) ? bdr : 0.0f;
+        for (int a = 0; a < 3; ++a) {
+            const double d = mimg(A[a] - B[a], c.per[a], c.box[a]);
+            v += d * d;
+        }
+        return sqrt(v);
+    };
+    // near neighbours (one lane each): positions staged for the wave, and the largest overlap
+    // with p before and after the motion
+    double dmax = 0.0;
+    if (lane < nn) {
+        const int q = q_near;
+        const double Y[3] = {Xs[3 * q], Xs[3 * q + 1], Xs[3 * q + 2]}, Rq = s.R[q];
+        nbidw[wv][lane] = q;
+        nbw[wv][lane][0] = Y[0]; nbw[wv][lane][1] = Y[1]; nbw[wv][lane][2] = Y[2];
+        nbw[wv][lane][3] = Rq;
+        dmax = fmax(0.0, R + Rq - dist(Y, c.X));
+        if (mode == 0) {
+            const double *Z = s.X[par] + 3 * q;
+            const double Yo[3] = {Z[0], Z[1], Z[2]};
+            dmax = fmax(dmax, R + Rq - dist(Yo, Xold));
+        }
     }
-    const MemberDev *Mp = nullptr;
-    if (active) {
-        Mp = s.mem + m;
-        active = (p - Mp->p_off < Mp->np) && (only < 0 || m == only);
+    for (int off = 32; off >= 1; off >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, off, 64));
+    const double step = dist(c.X, Xold);
+    // node lists: rebuilt at the start of the next step once p may have moved the skin
+    if (s.listmode && lane == 0) {
+        if (mode == 1) {
+            *s.relist_at = t;
+            const double *Vp = Vs + 3 * p;
+            s.pspd[p] = sqrt(Vp[0] * Vp[0] + Vp[1] * Vp[1] + Vp[2] * Vp[2]);
+        } else {
+            // a node uncovered by the next re-projection should have a slot in the current
+            // lists, so they are rebuilt while the particle stays within the skin after one
+            // more step of up to list_margin times this step's displacement (under compact
+            // storage a node uncovered outside them is parked until the rebuild)
+            s.pspd[p] = step;
+            if (dist(c.X, Xl) + s.list_margin * step >= skin - 1e-9) *s.relist_at = t + 1;
+        }
     }
-    int flag = 0; // 1 active, 2 shell rebuild, 4 near-list build
+    // Candidates, by d = |x - X| after the motion: a node enters or leaves p only if |d - R|
+    // <= the displacement; the order between p and an overlapping sphere changes only at
+    // nodes of p within the overlap depth, before the motion (R - d <= depth + displacement)
+    // or after it.  (At set-up every node inside p.)
+    const double mrg = row_margin(R);
+    const double outer = R + step + mrg, inner = (mode == 1) ? -1.0 : R - (dmax + step) - mrg;
+    const float outer2 = (float)(outer * outer), inner2 = inner > 0.0 ? (float)(inner * inner) : -1.0f;
+    const int nx = M->nx, ny = M->ny, nz = M->nz;
+    int x0, x1, y0, y1, z0, z1;
+    near_range(c.X[0], outer, nx, c.per[0], x0, x1);
+    near_range(c.X[1], outer, ny, c.per[1], y0, y1);
+    near_range(c.X[2], outer, nz, c.per[2], z0, z1);
+    const int ix = (int)floor(c.X[0]);
+    const float fx = (float)(c.X[0] - (double)ix);
+    const int nj = max(y1 - y0 + 1, 0), nrow = nj * max(z1 - z0 + 1, 0);
+    const double inv_nj = 1.0 / (double)max(nj, 1);
+    const int dxy = nx * ny;
+    const double inv_dxy = 1.0 / (double)dxy, inv_nx = 1.0 / (double)nx;
+    const unsigned long long below = (1ull << lane) - 1ull;
     double acc[6] = {0, 0, 0, 0, 0, 0};
-    int conv = 0;
-    if (active) {
-        RemapCtx c;
-        c.p = p; c.w = wv; c.M = Mp;
-        for (int a = 0; a < 3; ++a) {
-            c.per[a] = Mp->per[a];
-            c.box[a] = Mp->box[a];
-            c.X[a] = sp ? Xb1[a] : Xb0[a];
-        }
-        c.R = Rp; c.R2 = Rp * Rp;
-        c.nn = min(nn_raw, kNearCap);
-        const double Xr[3] = {mode == 1 ? c.X[0] : Xr_ld[0], mode == 1 ? c.X[1] : Xr_ld[1], mode == 1 ? c.X[2] : Xr_ld[2]};
-        if (lane < c.nn) {
-            const int q = q_raw;
-            nbidw[wv][lane] = q;
-            nbw[wv][lane][0] = Xs[3 * q]; nbw[wv][lane][1] = Xs[3 * q + 1]; nbw[wv][lane][2] = Xs[3 * q + 2];
-            nbw[wv][lane][3] = s.R[q];
-        }
-        // owners of the preloaded band entries (the candidates of a small step)
-        const int *cur = s.own[par] + Mp->cell_off;
-        int was[kPre];
-#pragma unroll
-        for (int i = 0; i < kPre; ++i) {
-            const int wr = cur[bc[i]];
-            was[i] = (lane + 64 * i < bnum) ? wr : -1;
-        }
-        // the wave's staged neighbours are visible to all its lanes
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // overlap depth with the near neighbours (one lane each), maximum over the wave
-        double dmax = 0.0;
-        if (lane < c.nn) {
-            const double d0 = mimg(nbw[wv][lane][0] - c.X[0], c.per[0], c.box[0]);
-            const double d1 = mimg(nbw[wv][lane][1] - c.X[1], c.per[1], c.box[1]);
-            const double d2 = mimg(nbw[wv][lane][2] - c.X[2], c.per[2], c.box[2]);
-            dmax = fmax(0.0, c.R + nbw[wv][lane][3] - sqrt((d0 * d0 + d1 * d1) + d2 * d2));
-        }
-        for (int off = 32; off >= 1; off >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, off, 64));
-        double disp2 = 0.0, xr[3];
-        for (int a = 0; a < 3; ++a) {
-            const double d = mimg(c.X[a] - Xr[a], c.per[a], c.box[a]);
-            disp2 += d * d;
-            xr[a] = c.X[a] - d; // reference centre unwrapped next to X
-        }
-        // node lists: rebuilt at the start of the next step once p may have moved the skin
-        if (s.listmode) {
-            if (mode == 1) {
-                if (lane == 0) {
-                    *s.relist_at = t;
-                    const double *Vp = Vs + 3 * p;
-                    s.pspd[p] = sqrt(Vp[0] * Vp[0] + Vp[1] * Vp[1] + Vp[2] * Vp[2]);
-                }
-            } else {
-                double dl = 0.0, ds = 0.0;
-                for (int a = 0; a < 3; ++a) {
-                    const double d = mimg(c.X[a] - Xl_ld[a], c.per[a], c.box[a]);
-                    const double v = mimg(c.X[a] - (sp ? Xb0[a] : Xb1[a]), c.per[a], c.box[a]);
-                    dl += d * d;
-                    ds += v * v;
-                }
-                // a node uncovered by the next re-projection should have a slot in the
-                // current lists, so they are rebuilt while the particle stays within the
-                // skin after one more step of up to list_margin times this step's
-                // displacement (under compact storage a node uncovered outside them is
-                // parked until the rebuild)
-                const double reach = sqrt(dl) + s.list_margin * sqrt(ds);
-                if (lane == 0) {
-                    s.pspd[p] = sqrt(ds);
-                    if (reach >= s.skin[m] - 1e-9) *s.relist_at = t + 1;
-                }
+    int conv = 0, qn = 0;
+    RowSpan r = {0, -1, 0, -1};
+    int base_cell = 0, row0 = 0;
+    for (;;) {
+        const bool first = r.a0 <= r.a1, has = first || r.b0 <= r.b1;
+        const unsigned long long bal = __ballot(has);
+        if (bal == 0ull && row0 < nrow) {
+            // the spans of the next 64 rows
+            if (row0 + lane < nrow) {
+                const int kz = div_uni(row0 + lane, nj, inv_nj), ky = row0 + lane - kz * nj;
+                int zz = z0 + kz, yy = y0 + ky;
+                const double dy = (double)yy - c.X[1], dz = (double)zz - c.X[2];
+                r = row_span((float)(dy * dy + dz * dz), fx, inner2, outer2);
+                r.a0 = max(r.a0, x0 - ix); r.b0 = max(r.b0, x0 - ix);
+                r.a1 = min(r.a1, x1 - ix); r.b1 = min(r.b1, x1 - ix);
+                if (c.per[1]) yy = yy < 0 ? yy + ny : (yy >= ny ? yy - ny : yy);
+                if (c.per[2]) zz = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
+                base_cell = zz * dxy + yy * nx;
             }
+            row0 += 64;
+            continue;
         }
-        // Candidates, with d_ref = |x - X_ref| and maxima over this projection and every
-        // one since the shell list was built at X_ref (the node map being replaced comes
-        // from the previous one): a node enters or leaves p only if |d_ref - R| <= dr,
-        // dr = max |X - X_ref|; the order between p and an overlapping sphere changes only
-        // at nodes inside p within the overlap depth, d_ref - R >= -lr, lr = max(|X -
-        // X_ref| + overlap depth).  A node with d_ref - R > dr is outside p at both
-        // projections, so its owner is settled by the other spheres' workgroups.
-        const double disp = sqrt(disp2);
-        const double rd = (mode == 1) ? disp : fmax(rdisp_ld, disp);
-        const double rl = (mode == 1) ? disp + dmax : fmax(rlens_ld, disp + dmax);
-        const double dr = rd + 1e-9, lr = rl + 1e-9;
-        // the shell list around X_ref holds every node with |d_ref - R| < kShell: while
-        // lr stays below kShell the candidates are in it, else it is rebuilt at X
-        const bool rebuild = (mode == 1) || (lr >= kShell - 1e-6);
-        const bool use_list = !rebuild && (lr >= mg_ld);
-        if (use_list) {
-            // candidates have -lr <= d_ref - R <= dr: the band list holds them all while
-            // lr <= kBandIn and dr <= kBandOut, the whole shell list otherwise
-            const bool band = lr + 1e-6 <= kBandIn && dr + 1e-6 <= kBandOut;
-            const long long lbase = (long long)p * s.lcap;
-            const int n = band ? bnum : s.lcnt[p];
-            const int *lc = band ? s.bcell + (long long)p * s.bcap : s.lcell + lbase;
-            const float *dl = band ? s.bdr + (long long)p * s.bcap : s.ldr + lbase;
-            const int dxy = Mp->nx * Mp->ny, dx = Mp->nx;
-            static_assert(64 * kPre == kQueue, "one queue slot per entry of a batch");
-            const unsigned long long below = (1ull << lane) - 1ull;
-            // kPre entries per lane at a time (the first batch of the band is loaded
-            // already): the ones within the candidate range go to the wave's queue in list
-            // order, and the queue is evaluated 64 nodes at a time, so a wave evaluates
-            // ceil(candidates / 64) rounds per batch instead of one round per entry round
-            for (int base = 0; base < n; base += kQueue) {
-                int qn = 0;
-#pragma unroll
-                for (int u = 0; u < kPre; ++u) {
-                    const int k = base + 64 * u + lane;
-                    int cell = 0, wpre = -2;
-                    double dk = 0.0;
-                    if (band && base == 0) {
-                        cell = bc[u]; dk = (double)bd[u]; wpre = was[u];
-                    } else if (k < n) {
-                        cell = lc[k]; dk = (double)dl[k];
-                    }
-                    const bool take = k < n && !(dk < -lr - 1e-6 || dk > dr + 1e-6);
-                    const unsigned long long bal = __ballot(take);
-                    if (take) {
-                        const int at = qn + __popcll(bal & below);
-                        qcell[wv][at] = cell;
-                        qwas[wv][at] = wpre;
-                    }
-                    qn += __popcll(bal);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                for (int q = lane; q < qn; q += 64) {
-                    const int cell = qcell[wv][q], wpre = qwas[wv][q];
-                    const int kk = cell / dxy;
-                    const int rem = cell - kk * dxy;
-                    const int jj = rem / dx, ii = rem - jj * dx;
-                    evaluate(c, ii, jj, kk, cell, dist2c(c, ii, jj, kk, c.X[0], c.X[1], c.X[2]), wpre, acc, conv);
-                }
-                // (the next batch refills the queue once every lane has read its entry)
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (has) {
+            int x = ix + (first ? r.a0++ : r.b0++);
+            if (c.per[0]) x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
+            qcell[wv][qn + __popcll(bal & below)] = base_cell + x;
+        }
+        qn += __popcll(bal);
+        if (bal != 0ull && qn <= kQueue - 64) continue;
+        if (qn == 0) break; // no row and no node left
+        wave_fence();
+        // uncovered nodes go to the front of the queue (behind the round being evaluated)
+        int on = 0;
+        for (int q0 = 0; q0 < qn; q0 += 64) {
+            const int q = q0 + lane;
+            const int cell = q < qn ? qcell[wv][q] : 0;
+            bool opened = false;
+            if (q < qn) {
+                const int kk = div_uni(cell, dxy, inv_dxy), rem = cell - kk * dxy;
+                const int jj = div_uni(rem, nx, inv_nx), ii = rem - jj * nx;
+                evaluate(c, ii, jj, kk, cell, acc, conv, opened);
             }
+            const unsigned long long ob = __ballot(opened);
+            wave_fence();
+            if (opened) qcell[wv][on + __popcll(ob & below)] = cell;
+            on += __popcll(ob);
         }
-        flag = 1 | (rebuild ? 2 : 0) | ((mode == 0 && t + 1 - nat_ld >= kNearEvery) ? 4 : 0);
-        if (lane == 0) {
-            ctxw[wv][0] = c.X[0]; ctxw[wv][1] = c.X[1]; ctxw[wv][2] = c.X[2];
-            ctxw[wv][3] = xr[0]; ctxw[wv][4] = xr[1]; ctxw[wv][5] = xr[2];
-            ctxw[wv][6] = lr; ctxw[wv][7] = dr; ctxw[wv][8] = dmax;
-            if (mode == 0 && !rebuild) {
-                s.rdisp[p] = rd;
-                s.rlens[p] = rl;
-            }
+        wave_fence();
+        for (int q = 0; q < on; q += 2) {
+            const int at = q + (lane >> 5);
+            refill(c, qcell[wv][min(at, on - 1)], at < on, acc);
         }
+        conv |= on;
+        // (the queue is filled again once every lane has read its entries)
+        wave_fence();
+        qn = 0;
     }
     // the wave's conversion momentum (summed only when a lane made a conversion)
     if (__ballot(conv) != 0ull) {
@@ -2688,273 +2675,47 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
         for (int k = 0; k < 6; ++k) acc[k] = wave_sum(acc[k]);
     }
     if (lane == 0) {
-        flagw[wv] = flag;
-        for (int k = 0; k < 6; ++k) accw[wv][k] = acc[k];
-    }
-    __syncthreads();
-
-    // ------------------------------------------------------------------------------
-    // phase B: shell-list rebuilds and near-list builds, the whole workgroup per particle
-    // ------------------------------------------------------------------------------
-    // (the near lists of the workgroup's particles are built in one pass over the
-    // candidates when those particles share a lattice, which is the rule)
-    int near_w = 0, near_m = -1;
-    bool near_joint = true;
-    for (int w = 0; w < kRemapWaves; ++w) {
-        if (!(flagw[w] & 4)) continue;
-        const int mw = s.pmem[blockIdx.x * kRemapWaves + w];
-        near_joint = near_joint && (near_m < 0 || mw == near_m);
-        near_m = mw;
-        near_w |= 1 << w;
-    }
-    for (int w = 0; w < kRemapWaves; ++w) {
-        const int fw = flagw[w] & (near_joint ? 3 : 7);
-        if ((fw & 6) == 0) continue;
-        const int pw = blockIdx.x * kRemapWaves + w;
-        RemapCtx c;
-        c.p = pw; c.w = w; c.M = s.mem + s.pmem[pw];
-        const MemberDev *M = c.M;
-        for (int a = 0; a < 3; ++a) {
-            c.per[a] = M->per[a];
-            c.box[a] = M->box[a];
-            c.X[a] = ctxw[w][a];
-        }
-        c.R = s.R[pw]; c.R2 = c.R * c.R;
-        c.nn = min(s.nnear[pw], kNearCap);
-        const double xr[3] = {ctxw[w][3], ctxw[w][4], ctxw[w][5]};
-        const double lr = ctxw[w][6], dr = ctxw[w][7], dmax = ctxw[w][8];
-        const double R = c.R, R2 = c.R2;
-        const int dims[3] = {M->nx, M->ny, M->nz};
-        const double Xr[3] = {mode == 1 ? c.X[0] : s.Xref[3 * pw], mode == 1 ? c.X[1] : s.Xref[3 * pw + 1],
-                              mode == 1 ? c.X[2] : s.Xref[3 * pw + 2]};
-        if (fw & 2) {
-            double acc2[6] = {0, 0, 0, 0, 0, 0};
-            int conv2 = 0;
-            // scan the boxes around X and X_ref, evaluate the candidates, and rebuild the
-            // shell list at X: nodes with -kShell < d - R <= sqrt(2) + kShell, with the
-            // directions e whose source x - c_e lies within R + kShell (link candidates)
-            const double hout = R + 1.5 + kShell + lr;
-            const double Rin = R - kShell, Rin2 = Rin > 0.0 ? Rin * Rin : -1.0, Rout2 = hout * hout;
-            const double Rl2 = (R + kShell) * (R + kShell);
-            const long long lbase = (long long)pw * s.lcap;
-            int lo[3], ext[3];
-            for (int a = 0; a < 3; ++a) {
-                int l = (int)floor(fmin(c.X[a], xr[a]) - hout) - 1;
-                int h = (int)ceil(fmax(c.X[a], xr[a]) + hout) + 1;
-                if (!c.per[a]) { l = max(l, 0); h = min(h, dims[a] - 1); }
-                else if (h - l + 1 > dims[a]) { l = 0; h = dims[a] - 1; } // visit each node once
-                lo[a] = l;
-                ext[a] = max(h - l + 1, 0);
-            }
-            const int tot = ext[0] * ext[1] * ext[2];
-            double mrg = kShell;
-            int lcount = 0, bcount = 0;
-            const long long bbase = (long long)pw * s.bcap;
-            // chunks of the list are z-slabs of hz planes of the scan box
-            const int hz = (ext[2] + kChunks - 1) / kChunks;
-            if (tid <= kChunks) cstart[tid] = 0;
-            __syncthreads();
-            for (int base = 0; base < tot; base += 256) {
-                const int idx = base + tid;
-                bool in_list = false;
-                int cell = 0;
-                unsigned mask = 0u;
-                float dref = 0.0f;
-                if (idx < tot) {
-                    int ii = lo[0] + idx % ext[0];
-                    int jj = lo[1] + (idx / ext[0]) % ext[1];
-                    int kk = lo[2] + idx / (ext[0] * ext[1]);
-                    // (positions stay within one period of the lattice, so one wrap suffices;
-                    // a true modulo keeps every index in range regardless)
-                    ii = ((ii % dims[0]) + dims[0]) % dims[0];
-                    jj = ((jj % dims[1]) + dims[1]) % dims[1];
-                    kk = ((kk % dims[2]) + dims[2]) % dims[2];
-                    cell = (kk * dims[1] + jj) * dims[0] + ii;
-                    const double d2n = dist2c(c, ii, jj, kk, c.X[0], c.X[1], c.X[2]);
-                    bool ev;
-                    if (mode == 1) {
-                        ev = d2n <= R2;
-                    } else {
-                        const double dd = sqrt(dist2c(c, ii, jj, kk, Xr[0], Xr[1], Xr[2])) - R;
-                        ev = dd >= -lr && dd <= dr;
-                    }
-                    if (ev) evaluate(c, ii, jj, kk, cell, d2n, -2, acc2, conv2);
-                    if (d2n > Rin2 && d2n <= Rout2) {
-                        const double dn = sqrt(d2n) - R;
-                        if (dn > -kShell && dn <= 1.4142135623730951 + kShell) {
-                            in_list = true;
-                            dref = (float)dn;
-                            mrg = fmin(mrg, fabs(dn));
-#pragma unroll
-                            for (int e = 0; e < kQ - 1; ++e) {
-                                const int si = ii - kCX[e], sj = jj - kCY[e], sk = kk - kCZ[e];
-                                if ((!c.per[0] && (si < 0 || si >= dims[0])) || (!c.per[1] && (sj < 0 || sj >= dims[1])) ||
-                                    (!c.per[2] && (sk < 0 || sk >= dims[2])))
-                                    continue;
-                                if (dist2c(c, wrapc(si, dims[0]), wrapc(sj, dims[1]), wrapc(sk, dims[2]), c.X[0], c.X[1],
-                                           c.X[2]) <= Rl2)
-                                    mask |= 1u << e;
-                            }
-                        }
-                    }
-                }
-                int tcount = 0;
-                const int rk = block_rank(in_list, tcount, cnt4);
-                if (in_list && hz > 0) atomicAdd(&cstart[idx / (ext[0] * ext[1]) / hz + 1], 1);
-                if (in_list) {
-                    const int slot = lcount + rk;
-                    if (slot < s.lcap) {
-                        s.lcell[lbase + slot] = cell;
-                        s.ldr[lbase + slot] = dref;
-                        s.lmask[lbase + slot] = mask;
-                    } else {
-                        atomicOr(s.flags, 0x40u);
-                    }
-                }
-                lcount += tcount;
-                // the surface band, a sub-list for small displacements
-                const bool in_band = in_list && (double)dref >= -kBandIn && (double)dref <= kBandOut;
-                const int bk = block_rank(in_band, tcount, cnt4);
-                if (in_band) {
-                    const int slot = bcount + bk;
-                    if (slot < s.bcap) {
-                        s.bcell[bbase + slot] = cell;
-                        s.bdr[bbase + slot] = dref;
-                    } else {
-                        atomicOr(s.flags, 0x40u);
-                    }
-                }
-                bcount += tcount;
-            }
-            double mv = wave_min_d(mrg);
-            if ((tid & 63) == 0) red[tid >> 6][7] = mv;
-            __syncthreads();
-            if (tid == 0) {
-                mv = fmin(fmin(red[0][7], red[1][7]), fmin(red[2][7], red[3][7]));
-                s.margin[pw] = mv;
-                s.lcnt[pw] = min(lcount, s.lcap);
-                s.bcnt[pw] = min(bcount, s.bcap);
-                s.lreb[pw] = (mode == 1) ? t - 1 : t; // the next link pass recomputes its links
-                s.lzr[2 * pw] = lo[2];
-                s.lzr[2 * pw + 1] = hz;
-                int acc_c = 0;
-                for (int k = 0; k <= kChunks; ++k) {
-                    acc_c += cstart[k];
-                    s.lchunk[pw * (kChunks + 1) + k] = min(acc_c, s.lcap);
-                }
-                s.Xref[3 * pw] = c.X[0]; s.Xref[3 * pw + 1] = c.X[1]; s.Xref[3 * pw + 2] = c.X[2];
-                // maxima restart at the new reference, where this projection has
-                // displacement 0 and overlap depth dmax
-                s.rdisp[pw] = 0.0;
-                s.rlens[pw] = dmax;
-            }
-            // the momentum of this rebuild's conversions
-            if (mode == 0 && __syncthreads_or(conv2)) {
-                block_sum<6>(acc2, red);
-                if (tid == 0)
-                    for (int k = 0; k < 6; ++k) accw[w][k] += acc2[k];
-            }
-            __syncthreads();
-        }
-        if (fw & 4) {
-            // the near list for the next kNearEvery steps, from the positions after this
-            // step's motion: every particle within R_p + R_q + kNearMargin (each particle
-            // moves less than 0.25 per step, so the contacts and the spheres that can own
-            // a node of p stay among them until the next build)
-            const int q0 = M->p_off, nq = M->np;
-            int near_total = 0;
-            for (int base = 0; base < nq; base += 256) {
-                const int jj = base + tid;
-                bool isnear = false;
-                if (jj < nq && q0 + jj != pw) {
-                    const int q = q0 + jj;
-                    const double d0 = mimg(Xs[3 * q] - c.X[0], c.per[0], c.box[0]);
-                    const double d1 = mimg(Xs[3 * q + 1] - c.X[1], c.per[1], c.box[1]);
-                    const double d2 = mimg(Xs[3 * q + 2] - c.X[2], c.per[2], c.box[2]);
-                    isnear = sqrt((d0 * d0 + d1 * d1) + d2 * d2) <= R + s.R[q] + kNearMargin;
-                }
-                int tot = 0;
-                const int rk = block_rank(isnear, tot, cnt4);
-                if (isnear) {
-                    const int slot = near_total + rk;
-                    if (slot < kNearCap) s.nearl[(long long)pw * kNearCap + slot] = q0 + jj;
-                    else atomicOr(s.flags, 0x2u);
-                }
-                near_total += tot;
-            }
-            if (tid == 0) {
-                s.nnear[pw] = min(near_total, kNearCap);
-                s.near_at[pw] = t + 1;
-            }
-            __syncthreads();
+        if (mode == 0)
+            for (int a = 0; a < 3; ++a) { s.Ph[3 * p + a] = acc[a]; s.Lh[3 * p + a] = acc[3 + a]; }
+        // the slabs of p's link entries, laid out around X at set-up and once it has moved
+        // away from their reference point (the next link pass then finds its entries again)
+        if (mode == 1 || dist(c.X, Xr) > kAnchorMove) {
+            const double reach = R + kSlabReach + (fmin(dmax, kSlabLens) + 1e-9);
+            int lo = (int)floor(c.X[2] - reach) - 1, hi = (int)ceil(c.X[2] + reach) + 1;
+            if (!c.per[2]) { lo = max(lo, 0); hi = min(hi, nz - 1); }
+            const int ext = c.per[2] ? min(hi - lo + 1, nz) : max(hi - lo + 1, 0);
+            s.lzr[2 * p] = lo;
+            s.lzr[2 * p + 1] = (ext + kChunks - 1) / kChunks;
+            s.lreb[p] = (mode == 1) ? t - 1 : t;
+            for (int a = 0; a < 3; ++a) s.Xref[3 * p + a] = c.X[a];
         }
     }
-    if (near_joint && near_w != 0) {
-        // the same near lists for the particles of the workgroup together: each candidate's
-        // position is loaded once and tested against every one of them
-        const MemberDev *M = s.mem + near_m;
+    if (mode == 1) {
+        if (lane == 0)
+            for (int a = 0; a < 3; ++a) s.Xn[3 * p + a] = c.X[a];
+    } else if (!near_build) {
+        if (lane == 0 && dist(c.X, Xn) > kNearMove) s.near_due[m] = t + 1;
+    } else {
+        // the near list from the positions after this step's motion: every particle within
+        // R_p + R_q + kNearMargin, in index order
         const int q0 = M->p_off, nq = M->np;
-        const int per[3] = {M->per[0], M->per[1], M->per[2]};
-        const double box[3] = {M->box[0], M->box[1], M->box[2]};
-        double Rw[kRemapWaves];
-#pragma unroll
-        for (int w = 0; w < kRemapWaves; ++w) Rw[w] = s.R[min((int)blockIdx.x * kRemapWaves + w, s.ptot - 1)];
-        int near_total[kRemapWaves] = {};
-        const unsigned long long below = (1ull << (tid & 63)) - 1ull;
-        for (int base = 0; base < nq; base += 256) {
-            const int jj = base + tid;
-            const int q = q0 + min(jj, nq - 1);
-            const double Y0 = Xs[3 * q], Y1 = Xs[3 * q + 1], Y2 = Xs[3 * q + 2], Rq = s.R[q];
-            // the candidate's verdict for every particle of the workgroup, then one exchange
-            // of the waves' counts ranks the candidates of all of them in thread order
-            bool isnear[kRemapWaves];
-            unsigned long long bal[kRemapWaves];
-#pragma unroll
-            for (int w = 0; w < kRemapWaves; ++w) {
-                const int pw = blockIdx.x * kRemapWaves + w;
-                isnear[w] = false;
-                if (((near_w >> w) & 1) && jj < nq && q != pw) {
-                    const double d0 = mimg(Y0 - ctxw[w][0], per[0], box[0]);
-                    const double d1 = mimg(Y1 - ctxw[w][1], per[1], box[1]);
-                    const double d2 = mimg(Y2 - ctxw[w][2], per[2], box[2]);
-                    isnear[w] = sqrt((d0 * d0 + d1 * d1) + d2 * d2) <= Rw[w] + Rq + kNearMargin;
-                }
-                bal[w] = __ballot(isnear[w]);
-                if ((tid & 63) == 0) ncnt[w][wv] = __popcll(bal[w]);
+        int near_total = 0;
+#pragma unroll 4
+        for (int base = 0; base < nq; base += 64) {
+            const int q = q0 + min(base + lane, nq - 1);
+            const double Y[3] = {Xs[3 * q], Xs[3 * q + 1], Xs[3 * q + 2]};
+            const bool isnear = base + lane < nq && q != p && dist(Y, c.X) <= R + s.R[q] + kNearMargin;
+            const unsigned long long bal = __ballot(isnear);
+            if (isnear) {
+                const int slot = near_total + __popcll(bal & below);
+                if (slot < kNearCap) s.nearl[(long long)p * kNearCap + slot] = q;
+                else atomicOr(s.flags, 0x2u);
             }
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < kRemapWaves; ++w) {
-                int off = 0, tot = 0;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int c = ncnt[w][v];
-                    off += (v < wv) ? c : 0;
-                    tot += c;
-                }
-                if (isnear[w]) {
-                    const int slot = near_total[w] + off + __popcll(bal[w] & below);
-                    const int pw = blockIdx.x * kRemapWaves + w;
-                    if (slot < kNearCap) s.nearl[(long long)pw * kNearCap + slot] = q;
-                    else atomicOr(s.flags, 0x2u);
-                }
-                near_total[w] += tot;
-            }
-            __syncthreads();
+            near_total += __popcll(bal);
         }
-#pragma unroll
-        for (int w = 0; w < kRemapWaves; ++w) {
-            if (tid == w && ((near_w >> w) & 1)) {
-                const int pw = blockIdx.x * kRemapWaves + w;
-                s.nnear[pw] = min(near_total[w], kNearCap);
-                s.near_at[pw] = t + 1;
-            }
-        }
-    }
-    // the conversion momentum of each particle of the workgroup
-    if (mode == 0 && tid < kRemapWaves && (flagw[tid] & 1)) {
-        const int pw = blockIdx.x * kRemapWaves + tid;
-        for (int a = 0; a < 3; ++a) { s.Ph[3 * pw + a] = accw[tid][a]; s.Lh[3 * pw + a] = accw[tid][3 + a]; }
+        if (lane == 0) s.nnear[p] = min(near_total, kNearCap);
+        if (lane == 0)
+            for (int a = 0; a < 3; ++a) s.Xn[3 * p + a] = c.X[a];
     }
 }
 
@@ -3657,7 +3418,7 @@ void *remap_kernel_ptr_prec(int prec)
     default: return (void *)&k_remap<PREC_BF16DEV>;
     }
 }
-int links_grid(const DevSet &s) { return max(s.ptot * kChunks, 1); }
+int links_grid(const DevSet &s) { return max(2 * s.ptot, 1); }
 int refresh_grid(const DevSet &) { return kRefreshBlocks; }
 void *refresh_kernel_ptr(int prec)
 {
@@ -3683,29 +3444,6 @@ hipError_t launch_refresh(int prec, const DevSet &s, hipStream_t st)
 int motion_grid(const DevSet &s) { return max((s.ptot + kMotionWaves - 1) / kMotionWaves, 1); }
 int remap_grid(const DevSet &s) { return max((s.ptot + kRemapWaves - 1) / kRemapWaves + s.nprobe_total, 1); }
 
-template <bool CMP, bool NR>
-void *records_ptr(int prec)
-{
-    switch (prec) {
-    case PREC_FP64: return (void *)&k_records<PREC_FP64, CMP, NR>;
-    case PREC_FP32: return (void *)&k_records<PREC_FP32, CMP, NR>;
-    case PREC_FP16DEV: return (void *)&k_records<PREC_FP16DEV, CMP, NR>;
-    default: return (void *)&k_records<PREC_BF16DEV, CMP, NR>;
-    }
-}
-void *records_kernel_ptr(int prec, int compact, int narrow)
-{
-    if (narrow) return compact ? records_ptr<true, true>(prec) : records_ptr<false, true>(prec);
-    return compact ? records_ptr<true, false>(prec) : records_ptr<false, false>(prec);
-}
-int records_grid(const DevSet &s) { return rebuild_blocks(s) + s.tiles_total; }
-hipError_t launch_records(int prec, const DevSet &s, hipStream_t st)
-{
-    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet)>(records_kernel_ptr(prec, s.compact, s.narrow)),
-                       dim3(records_grid(s)), dim3(256), 0, st, s);
-    return hipGetLastError();
-}
-
 hipError_t launch_fluid(int prec, const DevSet &s, hipStream_t st)
 {
     hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet)>(fluid_kernel_ptr(prec, s.compact, s.narrow)),
@@ -3713,13 +3451,13 @@ hipError_t launch_fluid(int prec, const DevSet &s, hipStream_t st)
     return hipGetLastError();
 }
 
-int links_block() { return kLinksBlock; }
+int links_block() { return 64 * kLinksWaves; }
 
 hipError_t launch_links(int prec, const DevSet &s, hipStream_t st)
 {
     const int mode = 0, only = -1;
     hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet, int, int)>(links_kernel_ptr(prec, s.narrow)),
-                       dim3(links_grid(s)), dim3(kLinksBlock), 0, st, s, mode, only);
+                       dim3(links_grid(s)), dim3(64 * kLinksWaves), 0, st, s, mode, only);
     return hipGetLastError();
 }
 
