@@ -500,6 +500,23 @@ int destroy_graph(lbdem_set *S)
     return LBDEM_OK;
 }
 
+// Whether a step of the set runs kernel k (0 links, 1 motion, 2 fluid, 3 re-projection with
+// the probe sums and the step counter, 4 refresh).  With the hydrodynamics switched off there
+// are no link forces and no fluid step.  A set that can hold no particles has no links, no
+// motion and no node changes; its refresh would only build node lists (each launch that finds
+// nothing to do still took 4.7 us of a 135 us step of a 96 x 96 x 384 pure fluid).
+bool step_runs(const lbdem_set *S, int k)
+{
+    const bool particles = S->G.ptot > 0, fluid = !S->G.fluid_off;
+    switch (k) {
+    case 0: return particles && fluid;
+    case 1: return particles;
+    case 2: return fluid;
+    case 4: return particles || S->G.listmode || !fluid;
+    default: return true;
+    }
+}
+
 int build_graph(lbdem_set *S, int steps)
 {
     destroy_graph(S);
@@ -508,45 +525,26 @@ int build_graph(lbdem_set *S, int steps)
     void *fluid_args[] = {(void *)&S->ds};
     void *part_args[] = {(void *)&S->ds, (void *)&mode0, (void *)&only_all};
     hipGraphNode_t prev = nullptr;
+    // refresh -> link pass -> motion -> fluid -> re-projection, less what the set has no use for
+    const bool on[kKernels] = {step_runs(S, 0), step_runs(S, 1), step_runs(S, 2), step_runs(S, 3), step_runs(S, 4)};
     for (int k = 0; k < steps; ++k) {
-        hipKernelNodeParams kp{};
-        hipGraphNode_t n0, n1, n2, n3, n4;
-        kp.blockDim = dim3(256);
-        kp.sharedMemBytes = 0;
-        kp.extra = nullptr;
-        // refresh -> link pass -> motion -> fluid -> re-projection
-        kp.func = refresh_kernel_ptr(S->G.prec);
-        kp.gridDim = dim3(refresh_grid(S->ds));
-        kp.kernelParams = fluid_args;
-        HIPCHK(hipGraphAddKernelNode(&n4, S->graph, prev ? &prev : nullptr, prev ? 1 : 0, &kp));
-        if (S->G.fluid_off) {
-            // hydrodynamics switched off: no link pass and no fluid step
-            n0 = n4;
-        } else {
-            kp.func = links_kernel_ptr(S->G.prec, S->ds.narrow);
-            kp.gridDim = dim3(links_grid(S->ds));
-            kp.blockDim = dim3(links_block());
-            kp.kernelParams = part_args;
-            HIPCHK(hipGraphAddKernelNode(&n0, S->graph, &n4, 1, &kp));
-        }
-        kp.blockDim = dim3(256);
-        kp.kernelParams = part_args;
-        kp.func = motion_kernel_ptr();
-        kp.gridDim = dim3(motion_grid(S->ds));
-        HIPCHK(hipGraphAddKernelNode(&n1, S->graph, &n0, 1, &kp));
-        if (S->G.fluid_off) {
-            n2 = n1;
-        } else {
-            kp.func = fluid_kernel_ptr(S->G.prec, S->G.compact, S->ds.narrow);
-            kp.gridDim = dim3(S->ds.tiles_total);
-            kp.kernelParams = fluid_args;
-            HIPCHK(hipGraphAddKernelNode(&n2, S->graph, &n1, 1, &kp));
-        }
-        kp.func = remap_kernel_ptr_prec(S->G.prec);
-        kp.gridDim = dim3(remap_grid(S->ds));
-        kp.kernelParams = part_args;
-        HIPCHK(hipGraphAddKernelNode(&n3, S->graph, &n2, 1, &kp));
-        prev = n3;
+        auto add = [&](bool run, void *func, int grid, int block, void **args) -> hipError_t {
+            if (!run) return hipSuccess;
+            hipKernelNodeParams kp{};
+            kp.func = func;
+            kp.gridDim = dim3(grid);
+            kp.blockDim = dim3(block);
+            kp.kernelParams = args;
+            hipGraphNode_t node;
+            hipError_t e = hipGraphAddKernelNode(&node, S->graph, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
+            prev = node;
+            return e;
+        };
+        HIPCHK(add(on[4], refresh_kernel_ptr(S->G.prec), refresh_grid(S->ds), 256, fluid_args));
+        HIPCHK(add(on[0], links_kernel_ptr(S->G.prec, S->ds.narrow), links_grid(S->ds), links_block(), part_args));
+        HIPCHK(add(on[1], motion_kernel_ptr(), motion_grid(S->ds), 256, part_args));
+        HIPCHK(add(on[2], fluid_kernel_ptr(S->G.prec, S->G.compact, S->ds.narrow), S->ds.tiles_total, 256, fluid_args));
+        HIPCHK(add(on[3], remap_kernel_ptr_prec(S->G.prec), remap_grid(S->ds), 256, part_args));
     }
     HIPCHK(hipGraphInstantiate(&S->gexec, S->graph, nullptr, nullptr, 0));
     S->graph_steps = steps;
@@ -576,7 +574,7 @@ int launch_step_eager(lbdem_set *S)
     static const int order[kKernels] = {4, 0, 1, 2, 3};
     for (int o = 0; o < kKernels; ++o) {
         const int k = order[o];
-        if (S->G.fluid_off && (k == 0 || k == 2)) continue;  // no link forces, no fluid step
+        if (!step_runs(S, k)) continue;
         int e0 = -1, e1 = -1;
         if (S->timing) {
             if (S->ev_next + 2 > S->ev_pool.size()) {

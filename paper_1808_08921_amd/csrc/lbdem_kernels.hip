@@ -82,9 +82,8 @@ template <> struct Prec<PREC_BF16DEV> { using S = uint16_t; using C = float; };
 
 __device__ __forceinline__ uint16_t f32_to_bf16(float x)
 {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u); // round to nearest even (finite inputs)
-    return (uint16_t)(u >> 16);
+    // round to nearest even, one instruction (v_cvt_pk_bf16_f32)
+    return __builtin_bit_cast(uint16_t, (__bf16)x);
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -514,6 +513,14 @@ __device__ __forceinline__ void move_values(const char *src, long long from, cha
     for (int d = 0; d < kQ; ++d) b[d * stride + to] = a[d * stride + from];
 }
 
+// First link word of a solid node (no link directions); the compact copy of a listed node's
+// word is the word itself without its overflow bit.
+constexpr unsigned long long kSolidWord = 1ull << 63;
+__device__ __forceinline__ unsigned long long compact_word(unsigned long long w0)
+{
+    return w0 == kSolidWord ? w0 : (w0 & ~kSolidWord);
+}
+
 // Link words of node (i, j, k) of lattice M from the node map own (this lattice's part):
 // for a fluid node x, the directions e whose source x - c_e lies inside a particle and the
 // slot (0..3, in the order the particles are met) of the particle owning each source; on
@@ -525,7 +532,10 @@ __device__ void link_words(const MemberDev *M, const int *own, const double *X, 
     const int nx = M->nx, ny = M->ny, nz = M->nz;
     w0 = 0ull;
     w1 = 0ull;
-    if (own[(k * ny + j) * nx + i] >= 0) return;
+    if (own[(k * ny + j) * nx + i] >= 0) {
+        w0 = kSolidWord;
+        return;
+    }
     unsigned mask = 0u, lo = 0u, hi = 0u;
     int id[4] = {-1, -1, -1, -1}, img[4] = {0, 0, 0, 0};
     int nid = 0;
@@ -573,14 +583,6 @@ __device__ __forceinline__ unsigned slot_dirs(unsigned long long w0, unsigned lo
     id = (g == 0) ? (int)(w0 >> 36) & 0x1fff : (g == 1) ? (int)(w0 >> 49) & 0x1fff
        : (g == 2) ? (int)(w1 >> 18) & 0x1fff : (int)(w1 >> 31) & 0x1fff;
     return mask & ((g & 1) ? lo : ~lo) & ((g & 2) ? hi : ~hi);
-}
-
-// Compact copy of a listed node's first link word: the word without its overflow bit for
-// a fluid node, kSolidWord for a solid one.
-constexpr unsigned long long kSolidWord = 1ull << 63;
-__device__ __forceinline__ unsigned long long compact_word(unsigned long long w0, bool solid)
-{
-    return solid ? kSolidWord : (w0 & ~kSolidWord);
 }
 
 // Marks the chunk of q whose z-slab holds plane z.
@@ -769,7 +771,7 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
             if (o0 != w0 || o1 != w1) mark_words(s, M, o0, o1, w0, w1, k, t - 1);
             s.lw[c] = w0;
             s.lw[s.ncell_total + c] = w1;
-            over |= (w0 >> 63) != 0ull;
+            over |= (w0 & kSolidWord) != 0ull && w0 != kSolidWord;
         }
     } else {
         const int *lst = s.chg[par ^ 1];
@@ -827,7 +829,7 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
                     if (sl & 2) shi |= 1u << e;
                 }
             }
-            unsigned long long w0 = 0ull, w1 = 0ull;
+            unsigned long long w0 = self >= 0 ? kSolidWord : 0ull, w1 = 0ull;
             if (mask != 0u || ov) {
                 w0 = (unsigned long long)mask | ((unsigned long long)slo << 18) |
                      ((unsigned long long)(max(id0, 0) & 0x1fff) << 36) |
@@ -850,7 +852,7 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
             if (lane == 0) {
                 s.lw[gc] = w0;
                 s.lw[s.ncell_total + gc] = w1;
-                if (ns >= 0) s.lwc[M->cell_off + ns] = compact_word(w0, self >= 0);
+                if (ns >= 0) s.lwc[M->cell_off + ns] = compact_word(w0);
                 over |= ov;
             }
         }
@@ -1001,6 +1003,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
 
     const long long t = *s.tstep;
     const int par = (int)(t & 1);
+    // (a set without particles runs no refresh: the re-projection kernel of this step, which
+    // advances the step counter, reads the step from here)
+    if (blockIdx.x == 0 && threadIdx.x == 0) *s.tcopy = t;
 
     const int g = xcd_swizzle(blockIdx.x, gridDim.x);
     const MemberDev *M = member_of_tile(s, g);
@@ -1013,7 +1018,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
     const int pz_off = uni(M->pz_off);
     const S *A = (const S *)(par ? s.popB : s.popA) + pop_off;
     S *B = (S *)(par ? s.popA : s.popB) + pop_off;
-    const int *own = s.own[par] + cell_off;
     const double rho_fd = uni(M->rho_f);
     const C omega = (C)uni(M->omega);
     const int bc4 = uni(M->bc[4]), bc5 = uni(M->bc[5]);
@@ -1034,16 +1038,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
     const bool lists = CMP || s.listmode != 0;
     constexpr bool compact = CMP;
 
-    // one chunk of the work: the nodes (i, j) of planes z0 .. z1-1 (dense tiles), or one
-    // listed node of plane z0 at slot me0 (node lists); accum adds the probe partial sums
-    // to those of an earlier chunk of the same workgroup
+    // the collision of a fluid node's pulled deviations f, stored at slot me; the node's probe
+    // terms and the watchdog: a fluid node whose density is not a positive finite number
+    // (status 0x400; NaN fails the first comparison)
+    auto collide = [&](const C (&f)[kQ], bool fl, double (&pr)[4], auto &&put) {
+        C drho, jx, jy, jz;
+        moments<C>(f, drho, jx, jy, jz);
+        const C rho = (C)rho_fd + drho;
+        if (fl && !(rho > C(0) && rho < C(1e30))) atomicOr(s.flags, 0x400u);
+        if (fl) {
+            pr[0] = 1.0;
+            pr[1] = (double)drho;
+            pr[2] = (double)jz;
+            pr[3] = rho_fd + (double)drho;
+        }
+        C ux, uy, uz, uu;
+        if constexpr (sizeof(C) == 8) {
+            ux = jx / rho; uy = jy / rho; uz = jz / rho;
+            uu = ux * ux + uy * uy + uz * uz;
+        } else {
+            const C ir = C(1) / rho;
+            ux = jx * ir; uy = jy * ir; uz = jz * ir;
+            uu = __builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, uz * uz));
+        }
+#pragma unroll
+        for (int d = 0; d < kQ; ++d) {
+            const C fe = feq_dev<C>(d, drho, rho, ux, uy, uz, uu);
+            C post;
+            if constexpr (sizeof(C) == 8) post = f[d] + omega * (fe - f[d]);
+            else post = __builtin_fmaf(omega, fe - f[d], f[d]);
+            put(d, post);
+        }
+    };
+    // the workgroup's probe sums of plane z0 + dz of its tile; accum adds them to those of an
+    // earlier chunk of the same workgroup
+    auto probes = [&](int z, int dz, bool accum, double (&v)[4]) {
+        if (s.pzmap[pz_off + z] < 0) return;
+        block_sum<4>(v, red);
+        if (threadIdx.x == 0) {
+            double *o = s.pprt + ((long long)g * s.nzt + dz) * 4;
+            if (accum) { o[0] += v[0]; o[1] += v[1]; o[2] += v[2]; o[3] += v[3]; }
+            else { o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3]; }
+        }
+    };
+
+    // one node (i, j, z) of a dense tile or a node list, at slot me0 under compact storage; word
+    // is its first link word
     // compact storage: the row-table words of the workgroup's source rows, staged in LDS
     // (rows j0 - 1 .. j1 + 1 of planes z - 1, z, z + 1 for the chunk's nodes in rows j0 .. j1)
     __shared__ uint2 rt_lds[kRtLds];
     __shared__ int jr[2];
 
-    auto run = [&](int i, int j, int z0, int z1, int me0, bool vij, bool accum, const uint2 *lrt, int jb,
-                   int nrows, unsigned long long wcl) {
+    auto node = [&](int i, int j, int z, int me0, bool vij, const uint2 *lrt, int jb, int nrows,
+                    unsigned long long word, double (&pr)[4]) {
         // offsets to the x-1 / x+1 / y-1 / y+1 neighbours (wrapped on periodic axes) and the
         // kind of face crossed to reach them (0 inside or periodic, 1 wall, 2 density face)
         int oxm = (i > 0) ? -1 : (nx - 1), oxp = (i < nx - 1) ? 1 : -(nx - 1);
@@ -1051,21 +1098,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
         int oym = (j > 0) ? -nx : (ny - 1) * nx, oyp = (j < ny - 1) ? nx : -(ny - 1) * nx;
         int kym = (j > 0) ? 0 : bc2, kyp = (j < ny - 1) ? 0 : bc3;
 
-        for (int z = z0; z < z1; ++z) {
+        {
             // keep the 18 per-direction offsets from being hoisted out of the loop: they are
             // cheap to recompute and would otherwise stay live in 36 registers
             asm volatile("" : "+v"(oxm), "+v"(oxp), "+v"(oym), "+v"(oyp), "+v"(kxm), "+v"(kxp), "+v"(kym), "+v"(kyp));
             const int cell = (z * ny + j) * nx + i;
-            bool fl = false;
-            unsigned long long wc = 0ull;
-            if constexpr (CMP) {
-                // the node's compact word, at its slot (loaded with the node's cell)
-                wc = wcl;
-                fl = vij && !(wc & kSolidWord);
-            } else {
-                if (vij) fl = ldo(own, (unsigned)cell) < 0;
-            }
-            double pr0 = 0.0, pr1 = 0.0, pr2 = 0.0, pr3 = 0.0;
+            const bool fl = vij && word != kSolidWord;
             // Dense tiles with 4- and 8-byte storage write every node of a row, so each store
             // covers whole cache lines: a solid node loads nothing and stores the rest state
             // w_d, a value that is never read (a node is refilled on uncovering).  16-bit
@@ -1077,13 +1115,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
                 const int kzm = (z > 0) ? 0 : bc4, kzp = (z < nz - 1) ? 0 : bc5;
                 // Loads are issued for every lane, a solid lane reading the first element of the
                 // array (one shared line) instead of branching around each load.
-                unsigned long long lwv;
-                if constexpr (CMP) {
-                    lwv = fl ? wc : 0ull;
-                } else {
-                    const unsigned long long lwr = s.lw[fl ? cell_off + cell : 0];
-                    lwv = fl ? lwr : 0ull;
-                }
+                const unsigned long long lwv = fl ? word : 0ull;
                 const unsigned lmask = (unsigned)lwv & 0x3ffffu;
                 // storage slot of this node: the node itself, or its rank in the plane's list
                 // (as an offset from the node that the compiler cannot see through: it keeps
@@ -1166,45 +1198,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
                 if (z == 0 && bc4 == BC_PRESSURE) zou_he<C>(f, drho_in, false);
                 if (z == nz - 1 && bc5 == BC_PRESSURE) zou_he<C>(f, C(0), true);
 
-                C drho, jx, jy, jz;
-                moments<C>(f, drho, jx, jy, jz);
-                const C rho = (C)rho_fd + drho;
-                // watchdog: a fluid node whose density is not a positive finite number
-                // (status 0x400; NaN fails the first comparison)
-                if (fl && !(rho > C(0) && rho < C(1e30))) atomicOr(s.flags, 0x400u);
-                if (fl) {
-                    pr0 = 1.0;
-                    pr1 = (double)drho;
-                    pr2 = (double)jz;
-                    pr3 = rho_fd + (double)drho;
-                }
-                C ux, uy, uz, uu;
-                if constexpr (sizeof(C) == 8) {
-                    ux = jx / rho; uy = jy / rho; uz = jz / rho;
-                    uu = ux * ux + uy * uy + uz * uz;
-                } else {
-                    const C ir = C(1) / rho;
-                    ux = jx * ir; uy = jy * ir; uz = jz * ir;
-                    uu = __builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, uz * uz));
-                }
-    #pragma unroll
-                for (int d = 0; d < kQ; ++d) {
-                    const C fe = feq_dev<C>(d, drho, rho, ux, uy, uz, uu);
-                    C post;
-                    if constexpr (sizeof(C) == 8) post = f[d] + omega * (fe - f[d]);
-                    else post = __builtin_fmaf(omega, fe - f[d], f[d]);
+                collide(f, fl, pr, [&](int d, C post) {
                     store_dev<P>(B, (unsigned)(d * nc) + (unsigned)me, d, post, rho_fd);
-                }
-            }
-            const int pidx = s.pzmap[pz_off + z];
-            if (pidx >= 0) {
-                double v[4] = {pr0, pr1, pr2, pr3};
-                block_sum<4>(v, red);
-                if (threadIdx.x == 0) {
-                    double *o = s.pprt + ((long long)g * s.nzt + (z - z0)) * 4;
-                    if (accum) { o[0] += v[0]; o[1] += v[1]; o[2] += v[2]; o[3] += v[3]; }
-                    else { o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3]; }
-                }
+                });
             }
         }
     };
@@ -1225,12 +1221,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
             const int kk = lbx * 256 + (int)threadIdx.x;
             const bool v = kk < cnt;
             const int c = v ? s.clist[cell_off + (long long)z * nxy + kk] - z * nxy : 0;
-            // compact storage: the node's first link word (or the solid marker) at its slot
-            unsigned long long wcl = (CMP && v) ? s.lwc[cell_off + (long long)z * nxy + kk] : 0ull;
-            if (CMP && full_compact && v) {
-                const int cell = z * nxy + c;
-                wcl = compact_word(s.lw[cell_off + cell], own[cell] >= 0);
-                s.lwc[cell_off + (long long)z * nxy + kk] = wcl;
+            // the node's first link word: under compact storage the copy at its slot
+            unsigned long long word = kSolidWord;
+            if (v) {
+                const long long slot = cell_off + (long long)z * nxy + kk;
+                if constexpr (CMP) {
+                    word = s.lwc[slot];
+                    if (full_compact) {
+                        word = compact_word(s.lw[cell_off + z * nxy + c]);
+                        s.lwc[slot] = word;
+                    }
+                } else {
+                    word = s.lw[cell_off + z * nxy + c];
+                }
             }
             const int jj = c / nx;
             const uint2 *lrt = nullptr;
@@ -1258,8 +1261,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
                 }
                 __syncthreads();
             }
-            // the node's slot under compact storage
-            run(c - jj * nx, jj, z, z + 1, z * nxy + kk, v, lbx != lb, lrt, jb, nrows, wcl);
+            double pr[4] = {0.0, 0.0, 0.0, 0.0};
+            node(c - jj * nx, jj, z, z * nxy + kk, v, lrt, jb, nrows, word, pr);
+            probes(z, 0, lbx != lb, pr);
             // (the next chunk stages its own rows once every thread is done with these)
             if constexpr (CMP) __syncthreads();
         }
@@ -1269,8 +1273,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
         const int tx = tl % ntx, trem = tl / ntx, ty = trem % nty, tz = trem / nty;
         const int i = (tx << bxl) + lx;
         const int j = ty * uni(M->by) + ly;
-        const int z0 = tz * s.nzt;
-        run(i, j, z0, min(z0 + s.nzt, nz), 0, (i < nx) && (j < ny), false, nullptr, 0, 0, 0ull);
+        const int z0 = tz * s.nzt, z1 = min(z0 + s.nzt, nz);
+        const bool vij = (i < nx) && (j < ny);
+        // Away from walls, density faces, particles and solid nodes a node pulls each direction
+        // from a fixed offset: nine offsets within a plane per column, the planes' and the
+        // directions' offsets in scalar registers.  A wave whose nodes are all of that kind
+        // takes this path, about half the vector instructions of the general one, which bound
+        // the 16-bit storage (pure fluid 96 x 96 x 384, us per launch: BF16 112 -> 64,
+        // FP16 84 -> 66, FP32 117 -> 109 of 105 at the rate of a device copy).
+        const bool edge = (i == 0 && bc0 != 0) || (i == nx - 1 && bc1 != 0) || (j == 0 && bc2 != 0) ||
+                          (j == ny - 1 && bc3 != 0);
+        for (int z = z0; z < z1; ++z) {
+            double pr[4] = {0.0, 0.0, 0.0, 0.0};
+            // (a set without particles has no link words to read)
+            unsigned long long word = 0ull;
+            if (s.ptot > 0 && vij) word = s.lw[cell_off + (z * ny + j) * nx + i];
+            const bool face = (z == 0 && bc4 != 0) || (z == nz - 1 && bc5 != 0);
+            if (face || __ballot(vij && (edge || word != 0ull)) != 0ull) {
+                node(i, j, z, 0, vij, nullptr, 0, 0, word, pr);
+            } else if (vij) {
+                const int zs[3] = {z > 0 ? z - 1 : nz - 1, z, z < nz - 1 ? z + 1 : 0};
+                // (recomputed per plane: kept across the general path they would spill)
+                int ic = i, jc = j;
+                asm volatile("" : "+v"(ic), "+v"(jc));
+                const int xs[3] = {ic > 0 ? ic - 1 : nx - 1, ic, ic < nx - 1 ? ic + 1 : 0};
+                const int ys[3] = {jc > 0 ? jc - 1 : ny - 1, jc, jc < ny - 1 ? jc + 1 : 0};
+                unsigned vo[9]; // source (x - c_x, y - c_y) at [3 (1 - c_y) + 1 - c_x]
+#pragma unroll
+                for (int q = 0; q < 9; ++q) vo[q] = (unsigned)(ys[q / 3] * nx + xs[q % 3]);
+                C f[kQ];
+                S raw[kQ];
+#pragma unroll
+                for (int e = 0; e < kQ; ++e)
+                    raw[e] = ldo(A + ((long long)e * nc + (long long)zs[1 - kCZ[e]] * nxy), vo[3 * (1 - kCY[e]) + 1 - kCX[e]]);
+#pragma unroll
+                for (int e = 0; e < kQ; ++e) f[e] = decode_dev<P>(raw[e], e, rho_fd);
+                collide(f, true, pr, [&](int d, C post) {
+                    store_dev<P>(B + ((long long)d * nc + (long long)z * nxy), vo[4], d, post, rho_fd);
+                });
+            }
+            probes(z, z - z0, false, pr);
+        }
     }
 }
 
