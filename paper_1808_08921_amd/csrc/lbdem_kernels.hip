@@ -622,71 +622,70 @@ __device__ __forceinline__ void pack_state(float *o, const double *X, const doub
     o[3] = o[7] = o[11] = 0.0f;
 }
 
-__device__ __forceinline__ float mimg_f(float dx, int per, float n)
+// A lattice's periods as the fluid kernel's moving walls use them, in scalar registers: the
+// length of a periodic axis and half of it, infinity on a bounded one (no image is nearer).
+// Read from the lattice's constants where they are used, these were six loads waited for one
+// after the other in every wave with links.
+template <typename C> struct Periods {
+    C n[3], half[3];
+    int p_off;
+};
+template <typename C>
+__device__ __forceinline__ Periods<C> load_periods(const MemberDev *M)
 {
-    if (per) {
-        if (dx > 0.5f * n) dx -= n;
-        else if (dx < -0.5f * n) dx += n;
+    Periods<C> p;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const bool per = uni(M->per[a]) != 0;
+        p.n[a] = per ? (C)uni(M->box[a]) : C(0);
+        p.half[a] = per ? C(0.5) * p.n[a] : (C)__builtin_inf();
     }
+    p.p_off = uni(M->p_off);
+    return p;
+}
+template <typename C>
+__device__ __forceinline__ C image_of(C dx, C n, C half)
+{
+    if (dx > half) dx -= n;
+    else if (dx < -half) dx += n;
     return dx;
 }
 
-// V_b = V + Omega x r at node (i, j, k) from a packed FP32 state q (X, V, Omega), r the
-// node's position relative to the image of the particle that holds link group grp (the
-// minimum image, or from a link's midpoint in a set with a narrow lattice, as group_arm)
-template <bool NR>
-__device__ __forceinline__ void wall_velocity_f(const MemberDev *M, const float4 (&q)[3], unsigned grp, int i, int j,
-                                                int k, float &u0, float &u1, float &u2)
+// V_b = V + Omega x r for the links of group grp at node (i, j, k) of particle q (a global
+// index), in the collision precision C; r is the node's position relative to the image of the
+// particle that holds the group (the minimum image, or from a link's midpoint in a set with a
+// narrow lattice, as group_arm).  Used with c_d . V_b for the link (x, d), which equals c_d .
+// V_b at the link's midpoint since c_d . (Omega x c_d) = 0.  X is the position at time t, V and
+// Omega the velocities of the step: the packed FP32 copy (FP32 and 16-bit storage), or the
+// FP64 state (written by the motion kernel at the other parity).
+template <typename C, bool NR>
+__device__ __forceinline__ void slot_velocity(const DevSet &s, const Periods<C> &pd, int q, unsigned grp, int i, int j,
+                                              int k, int par, C &u0, C &u1, C &u2)
 {
-    float r0, r1, r2;
+    C x[3], v[3], w[3];
+    if constexpr (sizeof(C) == 4) {
+        const float4 *pq = reinterpret_cast<const float4 *>(s.pf[par] + 12 * q);
+        const float4 a = pq[0], b = pq[1], c = pq[2];
+        x[0] = a.x; x[1] = a.y; x[2] = a.z;
+        v[0] = b.x; v[1] = b.y; v[2] = b.z;
+        w[0] = c.x; w[1] = c.y; w[2] = c.z;
+    } else {
+        const double *X = s.X[par] + 3 * q, *V = s.V[par ^ 1] + 3 * q, *W = s.W[par ^ 1] + 3 * q;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) { x[a] = X[a]; v[a] = V[a]; w[a] = W[a]; }
+    }
+    C h[3] = {C(0), C(0), C(0)};
     if constexpr (NR) {
         const int e = __ffs(grp) - 1;
-        const float h0 = 0.5f * (float)kCXd[e], h1 = 0.5f * (float)kCYd[e], h2 = 0.5f * (float)kCZd[e];
-        r0 = mimg_f(((float)i - h0) - q[0].x, M->per[0], (float)M->box[0]) + h0;
-        r1 = mimg_f(((float)j - h1) - q[0].y, M->per[1], (float)M->box[1]) + h1;
-        r2 = mimg_f(((float)k - h2) - q[0].z, M->per[2], (float)M->box[2]) + h2;
-    } else {
-        r0 = mimg_f((float)i - q[0].x, M->per[0], (float)M->box[0]);
-        r1 = mimg_f((float)j - q[0].y, M->per[1], (float)M->box[1]);
-        r2 = mimg_f((float)k - q[0].z, M->per[2], (float)M->box[2]);
+        h[0] = C(0.5) * (C)dir_x(e); h[1] = C(0.5) * (C)dir_y(e); h[2] = C(0.5) * (C)dir_z(e);
     }
-    u0 = q[1].x + (q[2].y * r2 - q[2].z * r1);
-    u1 = q[1].y + (q[2].z * r0 - q[2].x * r2);
-    u2 = q[1].z + (q[2].x * r1 - q[2].y * r0);
-}
-
-// Velocity of particle q's surface for the links of group grp at node (i, j, k), V_b = V +
-// Omega x r with r = x - X (the image that holds the group, as group_arm), in the
-// collision precision C; used with c_d . V_b for the link (x, d), which equals c_d . V_b
-// at the link's midpoint since c_d . (Omega x c_d) = 0.  X is the position at time t, V
-// and Omega the velocities of the step (written by the motion kernel at the other parity).
-template <typename C, bool NR>
-__device__ __forceinline__ void wall_velocity(const DevSet &s, const MemberDev *M, int q, unsigned grp, int i, int j,
-                                              int k, int par, C &u0, C &u1, C &u2)
-{
-    const double *X = s.X[par] + 3 * q, *V = s.V[par ^ 1] + 3 * q, *W = s.W[par ^ 1] + 3 * q;
-    double a0, a1, a2;
-    group_arm<NR>(M, grp, i, j, k, X[0], X[1], X[2], a0, a1, a2);
-    const C r0 = (C)a0, r1 = (C)a1, r2 = (C)a2;
-    const C w0 = (C)W[0], w1 = (C)W[1], w2 = (C)W[2];
-    u0 = (C)V[0] + (w1 * r2 - w2 * r1);
-    u1 = (C)V[1] + (w2 * r0 - w0 * r2);
-    u2 = (C)V[2] + (w0 * r1 - w1 * r0);
-}
-
-// Wall velocity of particle q for the link group grp at node (i, j, k), from the packed
-// FP32 state (FP32 and 16-bit storage) or the FP64 state.
-template <typename C, bool NR>
-__device__ __forceinline__ void slot_velocity(const DevSet &s, const MemberDev *M, int q, unsigned grp, int i, int j,
-                                              int k, int par, C &u0, C &u1, C &u2)
-{
-    if constexpr (sizeof(C) == 4) {
-        const float4 *pq = reinterpret_cast<const float4 *>(s.pf[par] + 12 * (M->p_off + q));
-        const float4 qq[3] = {pq[0], pq[1], pq[2]};
-        wall_velocity_f<NR>(M, qq, grp, i, j, k, u0, u1, u2);
-    } else {
-        wall_velocity<C, NR>(s, M, M->p_off + q, grp, i, j, k, par, u0, u1, u2);
-    }
+    C r0 = image_of(((C)i - h[0]) - x[0], pd.n[0], pd.half[0]);
+    C r1 = image_of(((C)j - h[1]) - x[1], pd.n[1], pd.half[1]);
+    C r2 = image_of(((C)k - h[2]) - x[2], pd.n[2], pd.half[2]);
+    if constexpr (NR) { r0 += h[0]; r1 += h[1]; r2 += h[2]; }
+    u0 = v[0] + (w[1] * r2 - w[2] * r1);
+    u1 = v[1] + (w[2] * r0 - w[0] * r2);
+    u2 = v[2] + (w[0] * r1 - w[1] * r0);
 }
 
 // Eq. (mem) for the links of a fluid node: f_e = f~_d(x,t) - 2 (w_d / c_s^2) rho_f V_b . c_d,
@@ -695,7 +694,7 @@ __device__ __forceinline__ void slot_velocity(const DevSet &s, const MemberDev *
 // from the particle's position at t and its velocities of the step; the momentum these
 // links exchange was accounted for by the link pass and the motion kernel.
 template <typename C, bool NR>
-__device__ __forceinline__ void moving_wall(const DevSet &s, const MemberDev *M, C (&f)[kQ], unsigned long long w0,
+__device__ __forceinline__ void moving_wall(const DevSet &s, const Periods<C> &pd, C (&f)[kQ], unsigned long long w0,
                                             int i, int j, int k, int par, double rho_f, long long gc)
 {
     const unsigned mask = (unsigned)w0 & 0x3ffffu, lo = (unsigned)(w0 >> 18) & 0x3ffffu;
@@ -705,16 +704,17 @@ __device__ __forceinline__ void moving_wall(const DevSet &s, const MemberDev *M,
     // takes the velocity of its slot without a branch
     const unsigned g0 = mask & ~lo & ~hi, g1 = mask & lo & ~hi;
     C a0, a1, a2, b0, b1, b2;
-    slot_velocity<C, NR>(s, M, (int)(w0 >> 36) & 0x1fff, g0 ? g0 : 1u, i, j, k, par, a0, a1, a2);
-    slot_velocity<C, NR>(s, M, (int)(w0 >> 49) & 0x1fff, g1 ? g1 : 1u, i, j, k, par, b0, b1, b2);
+    slot_velocity<C, NR>(s, pd, pd.p_off + ((int)(w0 >> 36) & 0x1fff), g0 ? g0 : 1u, i, j, k, par, a0, a1, a2);
+    slot_velocity<C, NR>(s, pd, pd.p_off + ((int)(w0 >> 49) & 0x1fff), g1 ? g1 : 1u, i, j, k, par, b0, b1, b2);
+    // (the two directions of a pair share 2 (w / c_s^2) rho_f c . V_b up to its sign)
 #pragma unroll
     for (int e = 0; e < kQ - 1; ++e) {
         const int d = kOPP[e];
-        const bool one = (lo >> e) & 1u;
-        const C u0 = one ? b0 : a0, u1 = one ? b1 : a1, u2 = one ? b2 : a2;
-        const C cu = cdot(d, u0, u1, u2);
-        const C m = (((mask & ~hi) >> e) & 1u) ? (C)(kMW[d] * rho_f) : C(0);
-        f[e] = f[e] - m * cu;
+        if (d < e) continue;
+        const C m = (C)(kMW[d] * rho_f);
+        const C ta = m * cdot(d, a0, a1, a2), tb = m * cdot(d, b0, b1, b2);
+        f[e] = f[e] - (((mask & ~hi) >> e) & 1u ? (((lo >> e) & 1u) ? tb : ta) : C(0));
+        f[d] = f[d] + (((mask & ~hi) >> d) & 1u ? (((lo >> d) & 1u) ? tb : ta) : C(0));
     }
     // slots 2 and 3 (nodes bordering more than two particles)
     if (hi != 0u) {
@@ -724,7 +724,7 @@ __device__ __forceinline__ void moving_wall(const DevSet &s, const MemberDev *M,
             const unsigned grp = slot_dirs(w0, w1, g, q);
             if (grp == 0u) continue;
             C u0, u1, u2;
-            slot_velocity<C, NR>(s, M, q, grp, i, j, k, par, u0, u1, u2);
+            slot_velocity<C, NR>(s, pd, pd.p_off + q, grp, i, j, k, par, u0, u1, u2);
 #pragma unroll
             for (int e = 0; e < kQ - 1; ++e) {
                 const int d = kOPP[e];
@@ -1003,10 +1003,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
 
     const long long t = *s.tstep;
     const int par = (int)(t & 1);
-    // (a set without particles runs no refresh: the re-projection kernel of this step, which
-    // advances the step counter, reads the step from here)
-    if (blockIdx.x == 0 && threadIdx.x == 0) *s.tcopy = t;
-
     const int g = xcd_swizzle(blockIdx.x, gridDim.x);
     const MemberDev *M = member_of_tile(s, g);
     const int tl = g - uni(M->tile_off);
@@ -1030,6 +1026,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
     long long ti = t + 1;
     if (ti > t_n + 1) ti = t_n + 1;
     const C drho_in = (C)(s.wave[uni(M->wave_off) + ti] - rho_fd);
+    const Periods<C> pd = load_periods<C>(M);
     // compact storage: every listed node's compact word is written here after a list rebuild
     // or a full copy of the node map, and read from its slot otherwise
     const bool full_compact = CMP && (*s.relist_at == t || *s.lwc_bad == t);
@@ -1154,7 +1151,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
     #pragma unroll
                     for (int e = 0; e < kQ - 1; ++e) {
                         const int r = (1 - kCY[e]) * 3 + (1 - kCZ[e]);
-                        const int zb = wrapc(z - kCZ[e], nz) * nxy;
+                        // (the staged words hold slots, the tables ranks within the plane)
+                        const int zb = lrt ? 0 : wrapc(z - kCZ[e], nz) * nxy;
                         const int rk = zb + (int)wv[r].y + __popc(wv[r].x & (b - 1u));
                         const int rwr = zb + (int)ww[r].y + __popc(ww[r].x & (bw - 1u));
                         int v;
@@ -1193,7 +1191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
     #pragma unroll
                 for (int e = 0; e < kQ; ++e)
                     f[e] = (fl && !((unk >> e) & 1u)) ? decode_dev<P>(raw[e], e, rho_fd) : C(0);
-                if (lmask != 0u) moving_wall<C, NR>(s, M, f, lwv, i, j, z, par, rho_fd, cell_off + cell);
+                if (lmask != 0u) moving_wall<C, NR>(s, pd, f, lwv, i, j, z, par, rho_fd, cell_off + cell);
 
                 if (z == 0 && bc4 == BC_PRESSURE) zou_he<C>(f, drho_in, false);
                 if (z == nz - 1 && bc5 == BC_PRESSURE) zou_he<C>(f, C(0), true);
@@ -1203,6 +1201,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
                 });
             }
         }
+    };
+
+    // compact storage, a node away from walls and density faces (periodic faces included) with
+    // its source rows staged: along a source row the slots of x - 1, x and x + 1 are the number
+    // of listed nodes before x, less one, itself, and with x counted, so a row costs two
+    // bit counts, and a wave that holds nodes at a periodic x face reads the row's other end.
+    // Fewer vector instructions than the general path, which bound 16-bit storage (FCC wave
+    // case, FP16, 35.0 -> 33.0 us per launch); FP32 and FP64 are bound by their traffic (38
+    // and 79 us either way, 85 % of the rate of a device copy; an ensemble of 16 lattices in
+    // FP32 256 us without and 260 us with it), so they take the general path.
+    auto compact_node = [&](int i, int j, int z, int me, bool v, const uint2 *lrt, int jb, int nrows,
+                            unsigned long long word, double (&pr)[4]) {
+        const bool fl = v && word != kSolidWord;
+        // (a lane without a fluid node reads its own slot in every direction)
+        const unsigned lmask = fl ? (unsigned)word & 0x3ffffu : 0u, back = fl ? lmask : 0x3ffffu;
+        const unsigned below = (1u << (i & 31)) - 1u, upto = 2u * below + 1u;
+        const uint2 *row = lrt + (j - 1 - jb) * nw;
+        int rk[9], rm[9], rp[9]; // slots of the sources at x, x - 1 and x + 1
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            const uint2 w = row[((r % 3) * nrows + r / 3) * nw + (i >> 5)];
+            rk[r] = (int)w.y + __popc(w.x & below);
+            if (r % 3 != 1 && r / 3 != 1) continue; // (no direction has c_x, c_y and c_z)
+            rm[r] = rk[r] - 1;
+            rp[r] = (int)w.y + __popc(w.x & upto);
+        }
+        if (per_x && __ballot(i == 0 || i == nx - 1) != 0ull) {
+            const int wx = (i == 0) ? nx - 1 : 0;
+            const unsigned bw = (1u << (wx & 31)) - 1u;
+#pragma unroll
+            for (int r = 0; r < 9; ++r) {
+                if (r % 3 != 1 && r / 3 != 1) continue;
+                const uint2 w = row[((r % 3) * nrows + r / 3) * nw + (wx >> 5)];
+                const int rw = (int)w.y + __popc(w.x & bw);
+                rm[r] = (i == 0) ? rw : rm[r];
+                rp[r] = (i == nx - 1) ? rw : rp[r];
+            }
+        }
+        C f[kQ];
+        S raw[kQ];
+#pragma unroll
+        for (int e = 0; e < kQ - 1; ++e) {
+            const int r = (1 - kCY[e]) * 3 + (1 - kCZ[e]);
+            const int from = kCX[e] == 0 ? rk[r] : (kCX[e] > 0 ? rm[r] : rp[r]);
+            raw[e] = ldo(A, ((back >> e) & 1u) ? (unsigned)(kOPP[e] * nc + me) : (unsigned)(e * nc + from));
+        }
+        raw[18] = ldo(A, (unsigned)(18 * nc + me));
+#pragma unroll
+        for (int e = 0; e < kQ; ++e) f[e] = decode_dev<P>(raw[e], e, rho_fd);
+        if (lmask != 0u)
+            moving_wall<C, NR>(s, pd, f, word, i, j, z, par, rho_fd, cell_off + (z * ny + j) * nx + i);
+        if (!fl) return;
+        collide(f, true, pr, [&](int d, C post) {
+            store_dev<P>(B, (unsigned)(d * nc + me), d, post, rho_fd);
+        });
     };
 
     if (lists) {
@@ -1255,14 +1308,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
                         const int pz = w / (nrows * nw), rem = w - pz * (nrows * nw);
                         const int u = rem / nw, wq = rem - u * nw;
                         const int zz = wrapc(z + pz - 1, nz), jg = wrapc(jb + u, ny);
-                        rt_lds[w] = rtab[((long long)zz * ny + jg) * nw + wq];
+                        const uint2 rw = rtab[((long long)zz * ny + jg) * nw + wq];
+                        rt_lds[w] = make_uint2(rw.x, rw.y + (unsigned)(zz * nxy));
                     }
                     lrt = rt_lds;
                 }
                 __syncthreads();
             }
             double pr[4] = {0.0, 0.0, 0.0, 0.0};
-            node(c - jj * nx, jj, z, z * nxy + kk, v, lrt, jb, nrows, word, pr);
+            const int i = c - jj * nx;
+            bool general = true;
+            if constexpr (CMP && sizeof(S) == 2) {
+                const bool edge = (i == 0 && bc0 != 0) || (i == nx - 1 && bc1 != 0) || (jj == 0 && bc2 != 0) ||
+                                  (jj == ny - 1 && bc3 != 0);
+                general = !lrt || (z == 0 && bc4 != 0) || (z == nz - 1 && bc5 != 0) || __ballot(v && edge) != 0ull;
+                // (a lane past the plane's list takes the slot of the workgroup's first node)
+                if (!general)
+                    compact_node(i, v ? jj : jb + 1, z, z * nxy + (v ? kk : lbx * 256), v, lrt, jb, nrows, word, pr);
+            }
+            if (general) node(i, jj, z, z * nxy + kk, v, lrt, jb, nrows, word, pr);
             probes(z, 0, lbx != lb, pr);
             // (the next chunk stages its own rows once every thread is done with these)
             if constexpr (CMP) __syncthreads();
@@ -1314,6 +1378,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == PREC_F
             }
             probes(z, z - z0, false, pr);
         }
+        // (a set without particles runs no refresh: the re-projection kernel of this step, which
+        // advances the step counter, reads the step from here.  At the end of the kernel: after
+        // a store the compiler reads the lattice's constants with vector loads, which cost the
+        // FCC wave case 4 of 43 us)
+        if (s.ptot == 0 && blockIdx.x == 0 && threadIdx.x == 0) *s.tcopy = t;
     }
 }
 
