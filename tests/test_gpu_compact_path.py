@@ -35,3 +35,27 @@ def test_compact_storage_matches_node_lists(precision, shape, bc, y):
     own = got[0][0]
     assert np.array_equal(got[1][0], own) and (own >= 0).any()
     assert np.array_equal(got[0][1][:, own < 0], got[1][1][:, own < 0])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("shape", [(33, 41, 20), (32, 32, 18), (65, 31, 16), (30, 20, 24)])
+def test_moving_sphere_rebuilds_compact_planes(precision, shape):
+    """Lists rebuilt under a sphere that crosses the whole lattice, in planes of more than, of
+    exactly, of twice less one and of less than the 1024 cells a workgroup scans at a time:
+    nodes behind the first change of a plane's list change slots and keep their values."""
+    from paper_1808_08921_amd.lbdem import LatticeSet
+
+    nx, ny, nz = shape
+    f0 = inputs.random_populations(shape, seed=12)
+    params = dict(nx=nx, ny=ny, nz=nz, tau=0.8, rho_f=1.0, bc=(0,) * 6, rho_p=1e4, max_radius=4.5, max_particles=1)
+    got = []
+    for node_lists in (1, 2):
+        with LatticeSet([params], precision=precision, node_lists=node_lists, graph_steps=4) as gs:
+            gs.particles_set(0, np.array([[4.3, ny / 2 - 0.4, nz - 1.8]]), np.array([4.1]), v=np.array([[0.08, 0.03, 0.05]]))
+            gs.set_populations(0, f0)
+            gs.step(240)
+            gs.check()
+            got.append((gs.owner(0), gs.populations(0)))
+    own = got[0][0]
+    assert np.array_equal(got[1][0], own) and (own >= 0).any()
+    assert np.array_equal(got[0][1][:, own < 0], got[1][1][:, own < 0])
