@@ -917,9 +917,24 @@ int lbdem_particles_get(lbdem_set *S, int32_t lattice, int32_t n, double *x, dou
     if (rc) return rc;
     const MemberDev &M = S->G.mem[lattice];
     if (n != M.np) return fail(LBDEM_EINVAL, "lattice %d has %d particles, asked for %d", lattice, M.np, n);
+    if (n == 0) return sync_set(S);
+    // one gather into the node scratch and one copy, unless they do not fit it (fewer than two
+    // nodes a particle)
+    const size_t n3 = 3 * (size_t)n;
+    if (5 * n3 * sizeof(double) <= 64 * (size_t)S->G.cells) {
+        std::vector<double> host(5 * n3);
+        double *dev = reinterpret_cast<double *>(S->ds.scratch);
+        HIPCHK(launch_particles_out(S->ds, M.p_off, n, dev, S->stream));
+        HIPCHK(hipMemcpyAsync(host.data(), dev, sizeof(double) * host.size(), hipMemcpyDeviceToHost, S->stream));
+        rc = sync_set(S);
+        if (rc) return rc;
+        double *out[5] = {x, v, w, force, torque};
+        for (int q = 0; q < 5; ++q)
+            if (out[q]) std::memcpy(out[q], host.data() + q * n3, sizeof(double) * n3);
+        return LBDEM_OK;
+    }
     rc = sync_set(S);
     if (rc) return rc;
-    if (n == 0) return LBDEM_OK;
     long long t = 0;
     HIPCHK(hipMemcpy(&t, S->ds.tstep, sizeof(long long), hipMemcpyDeviceToHost));
     const int par = (int)(t & 1);
@@ -955,10 +970,11 @@ int lbdem_step(lbdem_set *S, int64_t nsteps)
 int lbdem_time(lbdem_set *S, int64_t *t)
 {
     if (!S || !t) return fail(LBDEM_EINVAL, "null argument");
+    // (a copy on the set's stream: one wait)
+    long long tt = 0;
+    HIPCHK(hipMemcpyAsync(&tt, S->ds.tstep, sizeof(long long), hipMemcpyDeviceToHost, S->stream));
     int rc = sync_set(S);
     if (rc) return rc;
-    long long tt = 0;
-    HIPCHK(hipMemcpy(&tt, S->ds.tstep, sizeof(long long), hipMemcpyDeviceToHost));
     *t = tt;
     return LBDEM_OK;
 }
@@ -1270,21 +1286,14 @@ int lbdem_fields_get(lbdem_set *S, int32_t lattice, double *rho, double *u, int3
         if (rc) return rc;
     }
     if (!rho && !u) return LBDEM_OK;
-    rc = node_layout(S);
-    if (rc) return rc;
-    const MemberDev &M = S->G.mem[lattice];
-    double *dev = nullptr;
-    hipError_t e = hipMalloc(&dev, sizeof(double) * 4 * (size_t)M.ncell);
-    if (e != hipSuccess) return fail(LBDEM_ENOMEM, "hipMalloc of the field scratch: %s", hipGetErrorString(e));
-    std::vector<double> host(4 * (size_t)M.ncell);
-    e = launch_fields(S->G.prec, S->ds, lattice, M.ncell, dev, S->stream);
+    // (the fields take 32 of the node scratch's 64 bytes a node; they go straight to the caller)
+    const size_t n = (size_t)S->G.mem[lattice].ncell;
+    double *dev = reinterpret_cast<double *>(S->ds.scratch);
+    hipError_t e = launch_fields(S->G.prec, S->ds, lattice, (long long)n, dev, S->stream);
+    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, dev, sizeof(double) * n, hipMemcpyDeviceToHost, S->stream);
+    if (e == hipSuccess && u) e = hipMemcpyAsync(u, dev + n, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, S->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(S->stream);
-    if (e == hipSuccess) e = hipMemcpy(host.data(), dev, sizeof(double) * host.size(), hipMemcpyDeviceToHost);
-    (void)hipFree(dev);
     if (e != hipSuccess) return fail(LBDEM_EDEVICE, "fields: %s", hipGetErrorString(e));
-    const size_t n = (size_t)M.ncell;
-    if (rho) std::memcpy(rho, host.data(), sizeof(double) * n);
-    if (u) std::memcpy(u, host.data() + n, sizeof(double) * 3 * n);
     return LBDEM_OK;
 }
 

@@ -217,6 +217,7 @@ hipError_t launch_fluid(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_remap_prec(int prec, const DevSet &s, int mode, int only_member, hipStream_t st);
 hipError_t launch_init_pops(int prec, const DevSet &s, long long total_cells, hipStream_t st);
 hipError_t launch_expand(int prec, const DevSet &s, hipStream_t st);
+hipError_t launch_particles_out(const DevSet &s, int p0, int n, double *out, hipStream_t st);
 hipError_t launch_fields(int prec, const DevSet &s, int m, long long ncell, double *out, hipStream_t st);
 // kernel entry points and grid sizes, for building HIP graphs
 void *refresh_kernel_ptr(int prec);
