@@ -336,9 +336,9 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.pf[1] = c.take<float>(12 * (size_t)P);
     s.fixed = c.take<int>(P);
     s.pmem = c.take<int>(P);
-    s.ppart = c.take<double>((size_t)P * kChunks * kLinkComp);
     s.pv_ring = G.pv_ring;
     s.pvring = c.take<double>(G.pv_ring > 0 ? (size_t)G.pv_ring * P * 3 : 1);
+    s.ppart = c.take<double>((size_t)P * kChunks * kLinkComp);
     s.zcache = c.take<double>((size_t)P * kChunks * kZComp);
     s.nearl = c.take<int>((size_t)P * kNearCap);
     s.nnear = c.take<int>(P);
@@ -500,9 +500,9 @@ int destroy_graph(lbdem_set *S)
     return LBDEM_OK;
 }
 
-// Whether a step of the set runs kernel k (0 links, 1 motion, 2 fluid, 3 re-projection with
-// the probe sums and the step counter, 4 refresh).  With the hydrodynamics switched off there
-// are no link forces and no fluid step.  A set that can hold no particles has no links, no
+// Whether a step of the set runs kernel k (0 links, with the motion in a set of few
+// particles, 1 motion, 2 fluid, 3 re-projection with the probe sums and the step counter, 4
+// refresh).  With the hydrodynamics switched off there are no link forces and no fluid step.  A set that can hold no particles has no links, no
 // motion and no node changes; its refresh would only build node lists (each launch that finds
 // nothing to do still took 4.7 us of a 135 us step of a 96 x 96 x 384 pure fluid).
 bool step_runs(const lbdem_set *S, int k)
@@ -510,7 +510,7 @@ bool step_runs(const lbdem_set *S, int k)
     const bool particles = S->G.ptot > 0, fluid = !S->G.fluid_off;
     switch (k) {
     case 0: return particles && fluid;
-    case 1: return particles;
+    case 1: return particles && !(fluid && links_fused(S->ds));
     case 2: return fluid;
     case 4: return particles || S->G.listmode || !fluid;
     default: return true;
@@ -541,7 +541,7 @@ int build_graph(lbdem_set *S, int steps)
             return e;
         };
         HIPCHK(add(on[4], refresh_kernel_ptr(S->G.prec), refresh_grid(S->ds), 256, fluid_args));
-        HIPCHK(add(on[0], links_kernel_ptr(S->G.prec, S->ds.narrow), links_grid(S->ds), links_block(), part_args));
+        HIPCHK(add(on[0], links_kernel_ptr(S->G.prec, S->ds), links_grid(S->ds), links_block(S->ds), fluid_args));
         HIPCHK(add(on[1], motion_kernel_ptr(), motion_grid(S->ds), 256, part_args));
         HIPCHK(add(on[2], fluid_kernel_ptr(S->G.prec, S->G.compact, S->ds.narrow), S->ds.tiles_total, 256, fluid_args));
         HIPCHK(add(on[3], remap_kernel_ptr_prec(S->G.prec), remap_grid(S->ds), 256, part_args));

@@ -221,13 +221,14 @@ hipError_t launch_particles_out(const DevSet &s, int p0, int n, double *out, hip
 hipError_t launch_fields(int prec, const DevSet &s, int m, long long ncell, double *out, hipStream_t st);
 // kernel entry points and grid sizes, for building HIP graphs
 void *refresh_kernel_ptr(int prec);
-void *links_kernel_ptr(int prec, int narrow);
+bool links_fused(const DevSet &s); // the link kernel moves the particles too
+void *links_kernel_ptr(int prec, const DevSet &s);
 void *motion_kernel_ptr();
 void *fluid_kernel_ptr(int prec, int compact, int narrow);
 void *remap_kernel_ptr_prec(int prec);
 int refresh_grid(const DevSet &s);
 int links_grid(const DevSet &s);
-int links_block();
+int links_block(const DevSet &s);
 int motion_grid(const DevSet &s);
 int remap_grid(const DevSet &s);
 // adjoint window kernels (lbdem_kernels.hip)

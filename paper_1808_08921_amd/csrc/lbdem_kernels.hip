@@ -20,7 +20,8 @@
 //   k_motion     one wave per particle: contacts (Eqs. fdLawn, fdLaws) at X(t), then the
 //                velocities of the step from (M + Z)(V', Omega') = M (V, Omega) + F0 + contacts
 //                + F_g + the conversion impulses of the previous re-projection (Eqs. translate,
-//                rotate, coupleF, coupleT; implicit in the exchanged momentum), X(t+1).
+//                rotate, coupleF, coupleT; implicit in the exchanged momentum), X(t+1).  In a set
+//                of few particles a wave of k_links does this.
 //   k_fluid      one thread per listed node of a z plane (compact storage, the default), or
 //                per node of a dense tile: pull streaming (Eq. stream) with stationary walls,
 //                moving half-way bounce-back at the particles' new velocities (Eq. mem), the
@@ -608,6 +609,7 @@ __device__ __forceinline__ void mark_words(const DevSet &s, const MemberDev *M, 
 // FP32 copy of a particle's wall state for the fluid kernel: X, V, Omega, padding
 __device__ __forceinline__ void pack_state(float *o, const double *X, const double *V, const double *W)
 {
+#pragma unroll
     for (int a = 0; a < 3; ++a) { o[a] = (float)X[a]; o[4 + a] = (float)V[a]; o[8 + a] = (float)W[a]; }
     o[3] = o[7] = o[11] = 0.0f;
 }
@@ -1448,7 +1450,6 @@ __device__ __forceinline__ int div_uni(int n, int d, double inv)
     return q;
 }
 
-constexpr int kLinksWaves = 4;   // chunks per workgroup of the link pass
 constexpr int kLinkScan = 2;     // candidate cells per lane per scan round of a rebuilt chunk
 constexpr int kLinkLds = 320;    // entries of a rebuilt chunk kept in LDS for its link-set sums
 constexpr int kCellLds = kLinkLds; // candidate cells of a rebuilt chunk listed at a time
@@ -1534,7 +1535,7 @@ __device__ __forceinline__ double row_margin(double R) { return 2e-5 + 1e-6 * R;
 // Returns the number of entries.
 template <bool NR>
 __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M, int p, int chunk, double X0, double X1,
-                                              double X2, int *cells, int2 *segs, int *lc, unsigned *lg)
+                                              double X2, int *cells, int2 *segs, int *lc, unsigned *lg, double *zl)
 {
     const int lane = threadIdx.x & 63;
     const int pl = p - uni(M->p_off);
@@ -1874,18 +1875,19 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
             }
             double *zc = s.zcache + ((long long)p * kChunks + chunk) * kZComp;
             int z = 0;
+            auto put = [&](double v) { zc[z] = v; if (zl) zl[z] = v; ++z; };
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
-                for (int c = a; c < 3; ++c) zc[z++] = z36 * Ss[a][c];
+                for (int c = a; c < 3; ++c) put(z36 * Ss[a][c]);
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
-                for (int c = 0; c < 3; ++c) zc[z++] = z36 * (Qs[a][c] - FS[a][c]);
+                for (int c = 0; c < 3; ++c) put(z36 * (Qs[a][c] - FS[a][c]));
 #pragma unroll
             for (int a = 0; a < 3; ++a)
 #pragma unroll
-                for (int c = a; c < 3; ++c) zc[z++] = z36 * (((Ws[a][c] - T[a][c]) - T[c][a]) + FSF[a][c]);
+                for (int c = a; c < 3; ++c) put(z36 * (((Ws[a][c] - T[a][c]) - T[c][a]) + FSF[a][c]));
         }
     }
     if (NR) {
@@ -1941,10 +1943,355 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
         if (lane == 0) {
             double *zc = s.zcache + ((long long)p * kChunks + chunk) * kZComp;
 #pragma unroll
-            for (int c = 0; c < 21; ++c) zc[c] = zs[c];
+            for (int c = 0; c < 21; ++c) { zc[c] = zs[c]; if (zl) zl[c] = zs[c]; }
         }
     }
     return cntx;
+}
+
+// ---------------------------------------------------------------------------
+// motion: contacts and the implicit update of a particle, by one wave
+// ---------------------------------------------------------------------------
+
+// Hertz / Mindlin contacts (Eqs. fdLawn, fdLaws) of particle p with the particles of its near
+// list at X(t), V(t), summed over the wave (lane c < 6 returns component c of force and
+// torque; mode 0), with the contact histories of the next step; or the near-list build: every particle within R_p + R_q +
+// kNearMargin (mode 1).
+__device__ __forceinline__ double contact_pass(const DevSet &s, const MemberDev *M, int p, int par, int mode)
+{
+    const int lane = threadIdx.x & 63;
+    const double *Xo = s.X[par], *Vo = s.V[par], *Wo = s.W[par];
+    const double X0 = Xo[3 * p], X1 = Xo[3 * p + 1], X2 = Xo[3 * p + 2];
+    const double R = s.R[p];
+    const int nn_ld = s.nnear[p];
+    const int nl_ld = s.nearl[(long long)p * kNearCap + (lane & (kNearCap - 1))];
+    const int hno = s.hn[par][p];
+    const int per0 = M->per[0], per1 = M->per[1], per2 = M->per[2];
+    const double box0 = M->box[0], box1 = M->box[1], box2 = M->box[2];
+
+    // contacts over the near list (mode 0) or the near-list build (mode 1)
+    const int q0 = M->p_off, nq = M->np;
+    const double E = M->E, nu = M->nu, mu = M->mu;
+    const int *hjo = s.hj[par] + (long long)p * kHistCap;
+    const double *hfo = s.hf[par] + (long long)p * kHistCap * 3;
+    int *hjn = s.hj[par ^ 1] + (long long)p * kHistCap;
+    double *hfn = s.hf[par ^ 1] + (long long)p * kHistCap * 3;
+    double con[6] = {0, 0, 0, 0, 0, 0};
+    int near_total = 0, hist_total = 0;
+    const bool build = mode != 0;
+    const int ncand = build ? nq : min(nn_ld, kNearCap);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    static_assert(kNearCap <= 64, "a near list fits one wave");
+    for (int base = 0; base < ncand; base += 64) {
+        const int jj = base + lane;
+        // (a near list has at most kNearCap <= 64 entries: lane jj < ncand took entry jj)
+        const int q = (jj < ncand) ? (build ? q0 + jj : nl_ld) : -1;
+        bool isnear = false, keep = false;
+        double ftn[3] = {0, 0, 0};
+        if (jj < ncand && q != p) {
+            const double Y0 = Xo[3 * q], Y1 = Xo[3 * q + 1], Y2 = Xo[3 * q + 2], Rq = s.R[q];
+            const double d0 = mimg(Y0 - X0, per0, box0);
+            const double d1 = mimg(Y1 - X1, per1, box1);
+            const double d2 = mimg(Y2 - X2, per2, box2);
+            const double dist = sqrt((d0 * d0 + d1 * d1) + d2 * d2);
+            isnear = dist <= R + Rq + kNearMargin;
+            const double un = R + Rq - dist;
+            if (mode == 0 && un > 0.0) {
+                // Eq. (fdLawn): Hertz normal force, pushing p away from q
+                const double n0 = d0 / dist, n1 = d1 / dist, n2 = d2 / dist;
+                const double rstar = 1.0 / (1.0 / R + 1.0 / Rq);
+                const double fn = 2.0 * E * un * sqrt(rstar * un) / (3.0 * (1.0 - nu * nu));
+                con[0] += -fn * n0; con[1] += -fn * n1; con[2] += -fn * n2;
+                if (mu > 0.0) {
+                    // Eq. (fdLaws): incremental Mindlin spring, Coulomb cap
+                    double fo[3] = {0, 0, 0};
+                    for (int h = 0; h < hno; ++h)
+                        if (hjo[h] == q) { fo[0] = hfo[3 * h]; fo[1] = hfo[3 * h + 1]; fo[2] = hfo[3 * h + 2]; }
+                    const double a0 = (R - 0.5 * un) * n0, a1 = (R - 0.5 * un) * n1, a2 = (R - 0.5 * un) * n2;
+                    const double b0 = -(Rq - 0.5 * un) * n0, b1 = -(Rq - 0.5 * un) * n1, b2 = -(Rq - 0.5 * un) * n2;
+                    const double *Vq = Vo + 3 * q, *Wq = Wo + 3 * q, *Vp = Vo + 3 * p, *Wp = Wo + 3 * p;
+                    const double wa0 = Wp[1] * a2 - Wp[2] * a1, wa1 = Wp[2] * a0 - Wp[0] * a2, wa2 = Wp[0] * a1 - Wp[1] * a0;
+                    const double wb0 = Wq[1] * b2 - Wq[2] * b1, wb1 = Wq[2] * b0 - Wq[0] * b2, wb2 = Wq[0] * b1 - Wq[1] * b0;
+                    const double v0 = (Vp[0] + wa0) - (Vq[0] + wb0);
+                    const double v1 = (Vp[1] + wa1) - (Vq[1] + wb1);
+                    const double v2 = (Vp[2] + wa2) - (Vq[2] + wb2);
+                    const double vn = v0 * n0 + v1 * n1 + v2 * n2;
+                    const double fon = fo[0] * n0 + fo[1] * n1 + fo[2] * n2;
+                    const double kt = 2.0 * E * sqrt(rstar * un) / ((1.0 + nu) * (2.0 - nu));
+                    ftn[0] = (fo[0] - fon * n0) - kt * (v0 - vn * n0);
+                    ftn[1] = (fo[1] - fon * n1) - kt * (v1 - vn * n1);
+                    ftn[2] = (fo[2] - fon * n2) - kt * (v2 - vn * n2);
+                    const double fm = sqrt(ftn[0] * ftn[0] + ftn[1] * ftn[1] + ftn[2] * ftn[2]);
+                    if (fm > mu * fn) { const double sc = mu * fn / fm; ftn[0] *= sc; ftn[1] *= sc; ftn[2] *= sc; }
+                    con[0] += ftn[0]; con[1] += ftn[1]; con[2] += ftn[2];
+                    con[3] += a1 * ftn[2] - a2 * ftn[1];
+                    con[4] += a2 * ftn[0] - a0 * ftn[2];
+                    con[5] += a0 * ftn[1] - a1 * ftn[0];
+                    keep = true;
+                }
+            }
+        }
+        if (build) {
+            const unsigned long long bal = __ballot(isnear);
+            if (isnear) {
+                const int slot = near_total + __popcll(bal & below);
+                if (slot < kNearCap) s.nearl[(long long)p * kNearCap + slot] = q;
+                else atomicOr(s.flags, 0x2u);
+            }
+            near_total += __popcll(bal);
+        }
+        if (mode == 0 && mu > 0.0) {
+            const unsigned long long bal = __ballot(keep);
+            if (keep) {
+                const int slot = hist_total + __popcll(bal & below);
+                if (slot < kHistCap) {
+                    hjn[slot] = q;
+                    hfn[3 * slot] = ftn[0]; hfn[3 * slot + 1] = ftn[1]; hfn[3 * slot + 2] = ftn[2];
+                } else {
+                    atomicOr(s.flags, 0x8u);
+                }
+            }
+            hist_total += __popcll(bal);
+        }
+    }
+    if (lane == 0) {
+        if (build) {
+            s.nnear[p] = min(near_total, kNearCap);
+        }
+        if (mode == 0) s.hn[par ^ 1][p] = min(hist_total, kHistCap);
+    }
+    double mine = 0.0;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        const double v = wave_sum(con[c]);
+        mine = lane == c ? v : mine;
+    }
+    return mine;
+}
+
+// The lane's own share of a particle's update: lanes 0..2 the force rows, 3..5 the torque rows
+// (loaded before the link sums are known).
+struct MotionRow {
+    double mi, vel, pend, fg; // mass or inertia, V or Omega, the pending impulse, F_g or nothing
+    double X[3], Xr[3];
+    int fixed;
+};
+__device__ __forceinline__ MotionRow motion_row(const DevSet &s, int p, int par)
+{
+    const int lane = threadIdx.x & 63, a = lane % 3;
+    const bool rot = lane >= 3;
+    const bool hyd = !s.fluid_off; // (otherwise there are no conversion momenta)
+    MotionRow r;
+    r.mi = rot ? s.I[p] : s.m[p];
+    r.vel = (rot ? s.W[par] : s.V[par])[3 * p + a];
+    r.pend = hyd ? (rot ? s.Lh : s.Ph)[3 * p + a] : 0.0;
+    r.fg = s.Fg[3 * p + a];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) { r.X[c] = s.X[par][3 * p + c]; r.Xr[c] = s.Xref[3 * p + c]; }
+    r.fixed = s.fixed[p];
+    return r;
+}
+
+// Eqs. (translate), (rotate) over the step with symplectic Euler, dt = 1: contacts, the external
+// force, the conversion impulses of the previous re-projection, and the momentum exchanged
+// with the fluid in this step, F0 - Z (V', Omega') from the link sums lp (F0, sum xr x G, S,
+// Qx, Wx, in LDS), solved for the velocities of the step, (M + Z)(V', Omega') = M (V, Omega) +
+// F0 + the rest; X(t+1) = X(t) + V'.  F_h, T_h of Eqs. (coupleF), (coupleT) are reported.  Fixed
+// particles stay.  The fluid kernel's wall state (X(t), V', Omega') is written in FP32.
+// Latency-bound: Z is assembled one element per lane (work: 45 values in LDS), the system is
+// factored as L D L^T one row per lane, one division per pivot (the motion kernel of the FCC
+// wave case with all of it in one lane, 203 registers: 12.0 us, now 8.7).
+__device__ __forceinline__ void motion_update(const DevSet &s, const MemberDev *M, int p, int par, long long t,
+                                              const MotionRow &row, double con, double *lp, double *work)
+{
+    const int lane = threadIdx.x & 63;
+    double *DS = work, *Z = work + 9;
+    const double box[3] = {M->box[0], M->box[1], M->box[2]};
+    const int per[3] = {M->per[0], M->per[1], M->per[2]};
+    // delta = X - X_ref: the torque arm of a link node is xr - delta
+    double dl[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) dl[a] = mimg(row.X[a] - row.Xr[a], per[a], box[a]);
+    auto dsel = [&](int a) { return a == 0 ? dl[0] : (a == 1 ? dl[1] : dl[2]); };
+    const int a1 = (lane + 1) % 3, a2 = (lane + 2) % 3;
+    // T0 = sum xr x G - delta x F0
+    double f0 = lp[min(lane, 5)];
+    if (lane >= 3) f0 -= dsel(a1) * lp[a2] - dsel(a2) * lp[a1];
+    // Z: Z_VV = S, Z_OmegaV = Qx - [delta] S, Z_OmegaOmega = Wx - Qx [delta]^T - [delta] Qx^T
+    // + [delta] S [delta]^T, with [delta] v = delta x v; lane 3 a + c takes element (a, c)
+    const int l9 = min(lane, 8), ra = l9 / 3, rc = l9 - 3 * ra;
+    auto sym = [](int a, int c) { const int lo = min(a, c); return lo * (5 - lo) / 2 + max(a, c); };
+    const double *Sp = lp + kLinkComp, *Qp = Sp + 6, *Wp = Qp + 9;
+    double Da[3], Dc[3];
+    {
+        const double v1 = dsel((ra + 1) % 3), v2 = dsel((ra + 2) % 3);
+        const double u1 = dsel((rc + 1) % 3), u2 = dsel((rc + 2) % 3);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            Da[k] = k == ra ? 0.0 : (k == (ra + 1) % 3 ? -v2 : v1);
+            Dc[k] = k == rc ? 0.0 : (k == (rc + 1) % 3 ? -u2 : u1);
+        }
+    }
+    double ds = 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ds += Da[k] * Sp[sym(k, rc)];
+    const double zov = Qp[3 * ra + rc] - ds;
+    if (lane < 9) {
+        DS[lane] = ds;
+        Z[6 * ra + rc] = Sp[sym(ra, rc)];
+        Z[6 * rc + 3 + ra] = zov;
+        Z[6 * (3 + ra) + rc] = zov;
+    }
+    wave_fence();
+    {
+        double qd = 0.0, dq = 0.0, dsd = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            qd += Qp[3 * ra + k] * Dc[k];
+            dq += Da[k] * Qp[3 * rc + k];
+            dsd += DS[3 * ra + k] * Dc[k];
+        }
+        const double zoo = ((Wp[sym(ra, rc)] - qd) - dq) + dsd;
+        if (lane < 9 && ra <= rc) {
+            Z[6 * (3 + ra) + 3 + rc] = zoo;
+            Z[6 * (3 + rc) + 3 + ra] = zoo;
+        }
+    }
+    wave_fence();
+    // (M + Z)(V', Omega') = M (V, Omega) + F0 + contacts + F_g + pending impulses
+    const int i6 = min(lane, 5);
+    double r[6], L[6], x[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        r[c] = Z[6 * i6 + c];
+        if (c == i6) r[c] += row.mi;
+    }
+    double b;
+    {
+        double sum = f0 + row.pend;
+        if (lane < 3) sum += row.fg;
+        b = row.mi * row.vel + (sum + con);
+    }
+    double iD = 0.0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const double id = 1.0 / readlane_d(r[j], j);
+        if (i6 == j) iD = id;
+        L[j] = r[j] * id;
+#pragma unroll
+        for (int c = j + 1; c < 6; ++c) r[c] -= L[j] * readlane_d(r[j], c);
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const double bk = readlane_d(b, k);
+        if (i6 > k) b -= L[k] * bk;
+    }
+    b *= iD;
+#pragma unroll
+    for (int i = 5; i >= 0; --i) {
+        double v = readlane_d(b, i);
+#pragma unroll
+        for (int k = i + 1; k < 6; ++k) v -= readlane_d(L[i], k) * x[k];
+        x[i] = v;
+    }
+    if (row.fixed) {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) x[a] = 0.0;
+    } else {
+        // a step beyond 0.25 lu (or a non-finite state) is an error (status 0x10); the
+        // particle is then held to a step of 0.25 lu and inside the lattice, so that
+        // every index derived from its position stays in range
+        const double v2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
+        const bool fin = isfinite(v2) && isfinite(x[3]) && isfinite(x[4]) && isfinite(x[5]);
+        if (!fin || !(v2 <= 0.0625)) {
+            if (lane == 0) atomicOr(s.flags, 0x10u);
+            if (!fin) {
+#pragma unroll
+                for (int a = 0; a < 6; ++a) x[a] = 0.0;
+            } else {
+                const double sc = 0.25 / sqrt(v2);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) x[a] *= sc;
+            }
+        }
+    }
+    // F_h, T_h: the momentum exchanged with the fluid over the step, F0 - Z (V', Omega'), plus
+    // the pending impulses used here (Eqs. coupleF, coupleT)
+    double zx = 0.0, xl = x[0];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+        zx += Z[6 * i6 + c] * x[c];
+        xl = lane == c ? x[c] : xl;
+    }
+    if (lane < 3) {
+        const int a = lane;
+        const double bx = a == 0 ? box[0] : (a == 1 ? box[1] : box[2]);
+        const int pr = a == 0 ? per[0] : (a == 1 ? per[1] : per[2]);
+        const double xc = a == 0 ? row.X[0] : (a == 1 ? row.X[1] : row.X[2]);
+        s.Fh[3 * p + a] = (f0 - zx) + row.pend;
+        if (s.pv_ring > 0) s.pvring[((t % s.pv_ring) * (long long)s.ptot + p) * 3 + a] = xl;
+        s.V[par ^ 1][3 * p + a] = xl;
+        double xa = xc + xl;
+        if (row.fixed) {
+            xa = xc;
+        } else if (pr) {
+            if (xa >= bx) xa -= bx;
+            else if (xa < 0.0) xa += bx;
+        } else {
+            if (xa < 0.0 || xa > bx - 1.0) atomicOr(s.flags, 0x10u);
+            xa = fmin(fmax(xa, 0.0), bx - 1.0);
+        }
+        s.X[par ^ 1][3 * p + a] = xa;
+    } else if (lane < 6) {
+        const int a = lane - 3;
+        s.Th[3 * p + a] = (f0 - zx) + row.pend;
+        s.W[par ^ 1][3 * p + a] = xl;
+    }
+    // the fluid kernel's wall state of this step: X(t) and the new velocities
+    if (lane == 0) pack_state(s.pf[par] + 12 * p, row.X, x, x + 3);
+}
+
+// One wave per particle: mode 1, the near list and the FP32 state copy of a set-up (later lists
+// are built by the re-projection kernel); mode 0, the step's contacts and motion, unless a wave
+// of the link kernel does both.
+constexpr int kMotionWaves = 4;
+constexpr int kMotionWork = 45;
+__global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode, int only)
+{
+    __shared__ double lp[kMotionWaves][kLinkComp + kZComp], work[kMotionWaves][kMotionWork];
+    const long long t = *s.tstep;
+    const int par = (int)(t & 1);
+    const int lane = threadIdx.x & 63, wv = (int)(threadIdx.x >> 6);
+    const int p = blockIdx.x * kMotionWaves + wv;
+    if (p >= s.ptot) return; // the whole wave: waves never synchronise here
+    const int m = s.pmem[p];
+    const MotionRow row = motion_row(s, p, par);
+    // the link pass's sums (with the hydrodynamics switched off there are none)
+    if (mode == 0 && lane < kLinkComp + kZComp) {
+        double v = 0.0;
+        if (!s.fluid_off) {
+            const bool part = lane < kLinkComp;
+            const int stride = part ? kLinkComp : kZComp;
+            const double *pp = part ? s.ppart + (long long)p * kChunks * kLinkComp + lane
+                                    : s.zcache + (long long)p * kChunks * kZComp + (lane - kLinkComp);
+            double ch[kChunks];
+#pragma unroll
+            for (int q = 0; q < kChunks; ++q) ch[q] = pp[q * stride];
+#pragma unroll
+            for (int q = 0; q < kChunks; ++q) v += ch[q];
+        }
+        lp[wv][lane] = v;
+    }
+    const MemberDev *M = s.mem + m;
+    if (p - M->p_off >= M->np) return;
+    if (only >= 0 && m != only) return;
+    const double con = contact_pass(s, M, p, par, mode);
+    if (mode != 0) {
+        if (lane == 0) pack_state(s.pf[par] + 12 * p, s.X[par] + 3 * p, s.V[par] + 3 * p, s.W[par] + 3 * p);
+        return;
+    }
+    wave_fence();
+    motion_update(s, M, p, par, t, row, con, lp[wv], work[wv]);
 }
 
 // Link pass, one wave per (particle p, chunk of p's link entries).  A link of p is a fluid
@@ -1966,26 +2313,55 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
 // slot, written by a kernel over every listed node and gathered here, cost 30 + 18 us on the
 // FCC wave case (FP64 45 + 25) against 31 us (48) for this kernel, 23 us without stale slabs: the records
 // took a pass over the link words of every node and 16 bytes per link node each way.)
-template <int P, bool NR>
-__global__ __launch_bounds__(64 * kLinksWaves) void k_links(DevSet s, int mode, int only)
+// FUSED: one workgroup per particle, a wave per chunk and a ninth for p's contacts meanwhile
+// and its motion (motion_update) after the workgroup's barrier.  This saves the motion kernel's
+// launch and its loads, but a workgroup holds its place until the motion is done, so it pays
+// while every workgroup has a CU of its own (FCC packings, FP32, us for links and motion, fused
+// | apart: 256 particles 19 | 25, 384 28 | 28, 512 32 | 30, 768 41 | 34; 60 in a chain, FP64,
+// 14 | 19).  Otherwise two workgroups per particle, first the equatorial slabs of every
+// particle, which hold most of the entries, then the polar ones (in slab order the long waves
+// of the last workgroups ran alone: 39 us instead of 36 on the FCC wave case), and the motion
+// kernel after.
+constexpr int kFusedParticles = 256;
+constexpr int links_waves(bool fused) { return fused ? kChunks : kChunks / 2; }
+template <int P, bool NR, bool FUSED>
+__global__ __launch_bounds__(64 * (links_waves(FUSED) + (FUSED ? 1 : 0))) __attribute__((amdgpu_waves_per_eu(NR ? 3 : 5)))
+void k_links(DevSet s)
 {
     using S = typename Prec<P>::S;
     using C = typename Prec<P>::C;
-    __shared__ int l_cells[kLinksWaves][kCellLds], l_c[kLinksWaves][kLinkLds];
-    __shared__ unsigned l_g[kLinksWaves][kLinkLds];
-    __shared__ int2 l_segs[kLinksWaves][256];
+    constexpr int kWaves = links_waves(FUSED);
+    __shared__ int l_cells[kWaves][kCellLds], l_c[kWaves][kLinkLds];
+    __shared__ unsigned l_g[kWaves][kLinkLds];
+    __shared__ int2 l_segs[kWaves][256];
+    // FUSED: the sums of the chunks (F0, sum xr x G, then the link-set sums), added in chunk order
+    __shared__ double l_sum[FUSED ? kChunks : 1][kLinkComp + kZComp], l_lp[kLinkComp + kZComp], l_work[kMotionWork];
+    static_assert(kLinkComp + kZComp <= 64, "one lane per component");
     const long long t = *s.tstep;
     const int par = (int)(t & 1);
     const int lane = threadIdx.x & 63, wv = (int)(threadIdx.x >> 6);
-    // two workgroups per particle: first the equatorial slabs of every particle, which hold
-    // most of the entries, then the polar ones (in slab order the long waves of the last
-    // workgroups ran alone: 39 us instead of 36 on the FCC wave case); particles in XCD order,
-    // neighbours sharing lines of the populations (45 us in launch order)
-    static_assert(kChunks == 2 * kLinksWaves, "two workgroups per particle");
-    if (s.ptot == 0 || mode != 0) return;
-    const int half = (int)blockIdx.x >= s.ptot ? 1 : 0;
+    if (s.ptot == 0) return;
+    // particles in XCD order, neighbours sharing lines of the populations (45 us in launch
+    // order on the FCC wave case, then 32)
+    const int half = !FUSED && (int)blockIdx.x >= s.ptot ? 1 : 0;
     const int p = uni(xcd_swizzle((int)blockIdx.x - half * s.ptot, s.ptot));
-    const int chunk = uni(half ? (wv < kLinksWaves / 2 ? wv : wv + kLinksWaves) : wv + kLinksWaves / 2);
+    const int chunk = uni(FUSED ? wv : (half ? (wv < kWaves / 2 ? wv : wv + kWaves) : wv + kWaves / 2));
+    if (FUSED && wv == kWaves) {
+        const MemberDev *M = s.mem + uni(s.pmem[p]);
+        if (p - uni(M->p_off) >= uni(M->np)) return; // (every wave of the workgroup)
+        const MotionRow row = motion_row(s, p, par);
+        const double con = contact_pass(s, M, p, par, 0);
+        __syncthreads();
+        if (lane < kLinkComp + kZComp) {
+            double v = 0.0;
+#pragma unroll
+            for (int q = 0; q < kChunks; ++q) v += l_sum[FUSED ? q : 0][lane];
+            l_lp[lane] = v;
+        }
+        wave_fence();
+        motion_update(s, M, p, par, t, row, con, l_lp, l_work);
+        return;
+    }
     // the chunk's state is loaded together with p's lattice, before the checks that need
     // the lattice (everything here is indexed by p < ptot)
     const int m = uni(s.pmem[p]);
@@ -1999,8 +2375,12 @@ __global__ __launch_bounds__(64 * kLinksWaves) void k_links(DevSet s, int mode, 
     const MemberDev *M = s.mem + m;
     const int pl = p - uni(M->p_off);
     if (pl >= uni(M->np)) return;
-    if (only >= 0 && m != only) return;
-    if (stale) cntx = rebuild_chunk<NR>(s, M, p, chunk, X0, X1, X2, l_cells[wv], l_segs[wv], l_c[wv], l_g[wv]);
+    double *sums = FUSED ? l_sum[chunk] : s.ppart + ((long long)p * kChunks + chunk) * kLinkComp;
+    if (stale)
+        cntx = rebuild_chunk<NR>(s, M, p, chunk, X0, X1, X2, l_cells[wv], l_segs[wv], l_c[wv], l_g[wv],
+                                 FUSED ? sums + kLinkComp : nullptr);
+    else if (FUSED && lane < kZComp)
+        sums[kLinkComp + lane] = s.zcache[((long long)p * kChunks + chunk) * kZComp + lane];
     const bool in_lds = stale && cntx <= kLinkLds; // (the wave's own LDS)
 
     const int nx = uni(M->nx), ny = uni(M->ny);
@@ -2102,349 +2482,11 @@ __global__ __launch_bounds__(64 * kLinksWaves) void k_links(DevSet s, int mode, 
 #pragma unroll
     for (int c = 0; c < kLinkComp; ++c) acc[c] = wave_sum(acc[c]);
     if (lane == 0) {
-        double *pp = s.ppart + ((long long)p * kChunks + chunk) * kLinkComp;
 #pragma unroll
-        for (int c = 0; c < kLinkComp; ++c) pp[c] = acc[c];
+        for (int c = 0; c < kLinkComp; ++c) sums[c] = acc[c];
     }
+    if constexpr (FUSED) __syncthreads();
 }
-
-// Solves A x = b for a symmetric positive definite 6 x 6 A (upper triangle given) by the
-// factorisation A = L D L^T (L unit lower triangular, D diagonal), with one division per
-// pivot; b is overwritten by x.
-__device__ __forceinline__ void ldl_solve6(double (&A)[6][6], double (&b)[6])
-{
-    double L[6][6], E[6][6], iD[6]; // E[i][j] = L[i][j] D[j]
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        double d = A[j][j];
-#pragma unroll
-        for (int k = 0; k < j; ++k) d -= L[j][k] * E[j][k];
-        iD[j] = 1.0 / d;
-#pragma unroll
-        for (int i = j + 1; i < 6; ++i) {
-            double v = A[j][i];
-#pragma unroll
-            for (int k = 0; k < j; ++k) v -= L[i][k] * E[j][k];
-            E[i][j] = v;
-            L[i][j] = v * iD[j];
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        double v = b[i];
-#pragma unroll
-        for (int k = 0; k < i; ++k) v -= L[i][k] * b[k];
-        b[i] = v;
-    }
-#pragma unroll
-    for (int i = 0; i < 6; ++i) b[i] *= iD[i];
-#pragma unroll
-    for (int i = 5; i >= 0; --i) {
-        double v = b[i];
-#pragma unroll
-        for (int k = i + 1; k < 6; ++k) v -= L[k][i] * b[k];
-        b[i] = v;
-    }
-}
-
-// One wave per particle, kMotionWaves particles per workgroup.
-// mode 0: Eqs. (translate), (rotate) over the step with symplectic Euler, dt = 1: Hertz /
-//         Mindlin contacts (Eqs. fdLawn, fdLaws) with the particles of the near list at
-//         X(t), V(t), the external force, the conversion impulses of the previous
-//         re-projection, and the momentum exchanged with the fluid in this step, F0 - Z
-//         (V', Omega') from the link pass (chunk partials summed in chunk order), solved
-//         for the velocities of the step, (M + Z)(V', Omega') = M (V, Omega) + F0 + the
-//         rest; X(t+1) = X(t) + V'.  F_h, T_h of Eqs. (coupleF), (coupleT) are reported.
-//         Fixed particles stay.  The fluid kernel's wall state (X(t), V', Omega') is
-//         written in FP32.
-// mode 1: near-neighbour list (every particle within R_p + R_q + kNearMargin) and the FP32
-//         state copy (set-up); later lists are built by the re-projection kernel.
-constexpr int kMotionWaves = 4;
-__global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode, int only)
-{
-    const long long t = *s.tstep;
-    const int par = (int)(t & 1);
-    const int lane = threadIdx.x & 63;
-    const int p = blockIdx.x * kMotionWaves + (int)(threadIdx.x >> 6);
-    if (p >= s.ptot) return; // the whole wave: waves never synchronise here
-    // p's state, its link-pass sums and its near list are loaded together, before the
-    // checks that need its lattice (everything here is indexed by p < ptot)
-    const int m = s.pmem[p];
-    const double *Xo = s.X[par], *Vo = s.V[par], *Wo = s.W[par];
-    const double X0 = Xo[3 * p], X1 = Xo[3 * p + 1], X2 = Xo[3 * p + 2];
-    const double R = s.R[p];
-    // the link pass's sums (lane c < kLinkComp adds component c of the partials over the
-    // chunks, lane kLinkComp + c component c of the cached link-set sums, in chunk order)
-    // and the rest of p's state for the update, loaded up front
-    static_assert(kLinkComp + kZComp <= 64, "one lane per link-pass component");
-    // (with the hydrodynamics switched off there are neither link forces nor conversion
-    // momenta)
-    const bool hyd = !s.fluid_off;
-    double ppv = 0.0;
-    if (mode == 0 && hyd && lane < kLinkComp + kZComp) {
-        const bool part = lane < kLinkComp;
-        const int stride = part ? kLinkComp : kZComp;
-        const double *pp = part ? s.ppart + (long long)p * kChunks * kLinkComp + lane
-                                : s.zcache + (long long)p * kChunks * kZComp + (lane - kLinkComp);
-        double ch[kChunks];
-#pragma unroll
-        for (int q = 0; q < kChunks; ++q) ch[q] = pp[q * stride];
-#pragma unroll
-        for (int q = 0; q < kChunks; ++q) ppv += ch[q];
-    }
-    const double Xr0 = s.Xref[3 * p], Xr1 = s.Xref[3 * p + 1], Xr2 = s.Xref[3 * p + 2];
-    double Phv[3], Lhv[3], Fgv[3], Vpv[3], Wpv[3];
-    for (int a = 0; a < 3; ++a) {
-        Phv[a] = hyd ? s.Ph[3 * p + a] : 0.0;
-        Lhv[a] = hyd ? s.Lh[3 * p + a] : 0.0;
-        Fgv[a] = s.Fg[3 * p + a];
-        Vpv[a] = Vo[3 * p + a];
-        Wpv[a] = Wo[3 * p + a];
-    }
-    const double mass = s.m[p], inert = s.I[p];
-    const int fixed_p = s.fixed[p];
-    const int nn_ld = s.nnear[p];
-    const int *nl = s.nearl + (long long)p * kNearCap;
-    const int nl_ld = nl[lane & (kNearCap - 1)];
-    const int hno = s.hn[par][p];
-    const MemberDev *M = s.mem + m;
-    if (p - M->p_off >= M->np) return;
-    if (only >= 0 && m != only) return;
-    const int per0 = M->per[0], per1 = M->per[1], per2 = M->per[2];
-    const double box0 = M->box[0], box1 = M->box[1], box2 = M->box[2];
-
-    // contacts over the near list (mode 0) or the near-list build (mode 1)
-    const int q0 = M->p_off, nq = M->np;
-    const double E = M->E, nu = M->nu, mu = M->mu;
-    const int *hjo = s.hj[par] + (long long)p * kHistCap;
-    const double *hfo = s.hf[par] + (long long)p * kHistCap * 3;
-    int *hjn = s.hj[par ^ 1] + (long long)p * kHistCap;
-    double *hfn = s.hf[par ^ 1] + (long long)p * kHistCap * 3;
-    double con[6] = {0, 0, 0, 0, 0, 0};
-    int near_total = 0, hist_total = 0;
-    const bool build = mode != 0;
-    const int ncand = build ? nq : min(nn_ld, kNearCap);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    static_assert(kNearCap <= 64, "a near list fits one wave");
-    for (int base = 0; base < ncand; base += 64) {
-        const int jj = base + lane;
-        // (a near list has at most kNearCap <= 64 entries: lane jj < ncand took entry jj)
-        const int q = (jj < ncand) ? (build ? q0 + jj : nl_ld) : -1;
-        bool isnear = false, keep = false;
-        double ftn[3] = {0, 0, 0};
-        if (jj < ncand && q != p) {
-            const double Y0 = Xo[3 * q], Y1 = Xo[3 * q + 1], Y2 = Xo[3 * q + 2], Rq = s.R[q];
-            const double d0 = mimg(Y0 - X0, per0, box0);
-            const double d1 = mimg(Y1 - X1, per1, box1);
-            const double d2 = mimg(Y2 - X2, per2, box2);
-            const double dist = sqrt((d0 * d0 + d1 * d1) + d2 * d2);
-            isnear = dist <= R + Rq + kNearMargin;
-            const double un = R + Rq - dist;
-            if (mode == 0 && un > 0.0) {
-                // Eq. (fdLawn): Hertz normal force, pushing p away from q
-                const double n0 = d0 / dist, n1 = d1 / dist, n2 = d2 / dist;
-                const double rstar = 1.0 / (1.0 / R + 1.0 / Rq);
-                const double fn = 2.0 * E * un * sqrt(rstar * un) / (3.0 * (1.0 - nu * nu));
-                con[0] += -fn * n0; con[1] += -fn * n1; con[2] += -fn * n2;
-                if (mu > 0.0) {
-                    // Eq. (fdLaws): incremental Mindlin spring, Coulomb cap
-                    double fo[3] = {0, 0, 0};
-                    for (int h = 0; h < hno; ++h)
-                        if (hjo[h] == q) { fo[0] = hfo[3 * h]; fo[1] = hfo[3 * h + 1]; fo[2] = hfo[3 * h + 2]; }
-                    const double a0 = (R - 0.5 * un) * n0, a1 = (R - 0.5 * un) * n1, a2 = (R - 0.5 * un) * n2;
-                    const double b0 = -(Rq - 0.5 * un) * n0, b1 = -(Rq - 0.5 * un) * n1, b2 = -(Rq - 0.5 * un) * n2;
-                    const double *Vq = Vo + 3 * q, *Wq = Wo + 3 * q, *Vp = Vo + 3 * p, *Wp = Wo + 3 * p;
-                    const double wa0 = Wp[1] * a2 - Wp[2] * a1, wa1 = Wp[2] * a0 - Wp[0] * a2, wa2 = Wp[0] * a1 - Wp[1] * a0;
-                    const double wb0 = Wq[1] * b2 - Wq[2] * b1, wb1 = Wq[2] * b0 - Wq[0] * b2, wb2 = Wq[0] * b1 - Wq[1] * b0;
-                    const double v0 = (Vp[0] + wa0) - (Vq[0] + wb0);
-                    const double v1 = (Vp[1] + wa1) - (Vq[1] + wb1);
-                    const double v2 = (Vp[2] + wa2) - (Vq[2] + wb2);
-                    const double vn = v0 * n0 + v1 * n1 + v2 * n2;
-                    const double fon = fo[0] * n0 + fo[1] * n1 + fo[2] * n2;
-                    const double kt = 2.0 * E * sqrt(rstar * un) / ((1.0 + nu) * (2.0 - nu));
-                    ftn[0] = (fo[0] - fon * n0) - kt * (v0 - vn * n0);
-                    ftn[1] = (fo[1] - fon * n1) - kt * (v1 - vn * n1);
-                    ftn[2] = (fo[2] - fon * n2) - kt * (v2 - vn * n2);
-                    const double fm = sqrt(ftn[0] * ftn[0] + ftn[1] * ftn[1] + ftn[2] * ftn[2]);
-                    if (fm > mu * fn) { const double sc = mu * fn / fm; ftn[0] *= sc; ftn[1] *= sc; ftn[2] *= sc; }
-                    con[0] += ftn[0]; con[1] += ftn[1]; con[2] += ftn[2];
-                    con[3] += a1 * ftn[2] - a2 * ftn[1];
-                    con[4] += a2 * ftn[0] - a0 * ftn[2];
-                    con[5] += a0 * ftn[1] - a1 * ftn[0];
-                    keep = true;
-                }
-            }
-        }
-        if (build) {
-            const unsigned long long bal = __ballot(isnear);
-            if (isnear) {
-                const int slot = near_total + __popcll(bal & below);
-                if (slot < kNearCap) s.nearl[(long long)p * kNearCap + slot] = q;
-                else atomicOr(s.flags, 0x2u);
-            }
-            near_total += __popcll(bal);
-        }
-        if (mode == 0 && mu > 0.0) {
-            const unsigned long long bal = __ballot(keep);
-            if (keep) {
-                const int slot = hist_total + __popcll(bal & below);
-                if (slot < kHistCap) {
-                    hjn[slot] = q;
-                    hfn[3 * slot] = ftn[0]; hfn[3 * slot + 1] = ftn[1]; hfn[3 * slot + 2] = ftn[2];
-                } else {
-                    atomicOr(s.flags, 0x8u);
-                }
-            }
-            hist_total += __popcll(bal);
-        }
-    }
-    if (lane == 0) {
-        if (build) {
-            s.nnear[p] = min(near_total, kNearCap);
-        }
-        if (mode == 0) s.hn[par ^ 1][p] = min(hist_total, kHistCap);
-    }
-    if (mode != 0) {
-        if (lane == 0) pack_state(s.pf[par] + 12 * p, Xo + 3 * p, Vo + 3 * p, Wo + 3 * p);
-        return;
-    }
-#pragma unroll
-    for (int c = 0; c < 6; ++c) con[c] = wave_sum(con[c]);
-
-    // the link pass's sums (every lane takes the same values): F0, sum xr x G, then the
-    // link-set sums S, Qx, Wx
-    double lp[kLinkComp + kZComp];
-#pragma unroll
-    for (int c = 0; c < kLinkComp + kZComp; ++c) lp[c] = readlane_d(ppv, c);
-    if (lane == 0) {
-        double *Xn = s.X[par ^ 1], *Vn = s.V[par ^ 1], *Wn = s.W[par ^ 1];
-        const double Xc[3] = {X0, X1, X2};
-        const int per[3] = {per0, per1, per2};
-        const double box[3] = {box0, box1, box2};
-        // delta = X - X_ref: the torque arm of a link node is xr - delta
-        const double dl[3] = {mimg(X0 - Xr0, per0, box0), mimg(X1 - Xr1, per1, box1), mimg(X2 - Xr2, per2, box2)};
-        // T0 = sum xr x G - delta x F0
-        lp[3] -= dl[1] * lp[2] - dl[2] * lp[1];
-        lp[4] -= dl[2] * lp[0] - dl[0] * lp[2];
-        lp[5] -= dl[0] * lp[1] - dl[1] * lp[0];
-        // Z: Z_VV = S, Z_OmegaV = Qx - [delta] S, Z_OmegaOmega = Wx - Qx [delta]^T - [delta] Qx^T
-        // + [delta] S [delta]^T, with [delta] v = delta x v
-        double Sm[3][3], Qm[3][3], Wm[3][3];
-        {
-            const double *zz = lp + kLinkComp;
-            int z = 0;
-            for (int a = 0; a < 3; ++a)
-                for (int c = a; c < 3; ++c) { Sm[a][c] = zz[z]; Sm[c][a] = zz[z]; ++z; }
-            for (int a = 0; a < 3; ++a)
-                for (int c = 0; c < 3; ++c) Qm[a][c] = zz[z++];
-            for (int a = 0; a < 3; ++a)
-                for (int c = a; c < 3; ++c) { Wm[a][c] = zz[z]; Wm[c][a] = zz[z]; ++z; }
-        }
-        const double Dm[3][3] = {{0.0, -dl[2], dl[1]}, {dl[2], 0.0, -dl[0]}, {-dl[1], dl[0], 0.0}};
-        double DS[3][3], ZOV[3][3], ZOO[3][3];
-        for (int a = 0; a < 3; ++a)
-            for (int c = 0; c < 3; ++c) {
-                double v = 0.0;
-                for (int k = 0; k < 3; ++k) v += Dm[a][k] * Sm[k][c];
-                DS[a][c] = v;
-                ZOV[a][c] = Qm[a][c] - v;
-            }
-        for (int a = 0; a < 3; ++a)
-            for (int c = 0; c < 3; ++c) {
-                double qd = 0.0, dq = 0.0, dsd = 0.0;
-                for (int k = 0; k < 3; ++k) {
-                    qd += Qm[a][k] * Dm[c][k];
-                    dq += Dm[a][k] * Qm[c][k];
-                    dsd += DS[a][k] * Dm[c][k];
-                }
-                ZOO[a][c] = ((Wm[a][c] - qd) - dq) + dsd;
-            }
-        // (M + Z)(V', Omega') = M (V, Omega) + F0 + contacts + F_g + pending impulses; Z's
-        // upper triangle: rows 0-2 (V) S and Z_VOmega = Z_OmegaV^T, rows 3-5 Z_OmegaOmega
-        double A[6][6], b[6];
-        double zup[21];
-        {
-            int z = 0;
-            for (int a = 0; a < 3; ++a) {
-                for (int c = a; c < 3; ++c) A[a][c] = Sm[a][c];
-                for (int c = 0; c < 3; ++c) A[a][3 + c] = ZOV[c][a];
-            }
-            for (int a = 0; a < 3; ++a)
-                for (int c = a; c < 3; ++c) A[3 + a][3 + c] = ZOO[a][c];
-            for (int a = 0; a < 6; ++a)
-                for (int c = a; c < 6; ++c) zup[z++] = A[a][c];
-        }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            A[a][a] += mass;
-            A[3 + a][3 + a] += inert;
-            b[a] = mass * Vpv[a] + (((lp[a] + Phv[a]) + Fgv[a]) + con[a]);
-            b[3 + a] = inert * Wpv[a] + ((lp[3 + a] + Lhv[a]) + con[3 + a]);
-        }
-        double x[6] = {b[0], b[1], b[2], b[3], b[4], b[5]};
-        ldl_solve6(A, x);
-        double v[3] = {x[0], x[1], x[2]}, w[3] = {x[3], x[4], x[5]};
-        if (fixed_p) {
-            for (int a = 0; a < 3; ++a) { v[a] = 0.0; w[a] = 0.0; }
-        } else {
-            // a step beyond 0.25 lu (or a non-finite state) is an error (status 0x10); the
-            // particle is then held to a step of 0.25 lu and inside the lattice, so that
-            // every index derived from its position stays in range
-            const double v2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
-            const bool fin = isfinite(v2) && isfinite(w[0]) && isfinite(w[1]) && isfinite(w[2]);
-            if (!fin || !(v2 <= 0.0625)) {
-                atomicOr(s.flags, 0x10u);
-                if (!fin) {
-                    for (int a = 0; a < 3; ++a) { v[a] = 0.0; w[a] = 0.0; }
-                } else {
-                    const double sc = 0.25 / sqrt(v2);
-                    for (int a = 0; a < 3; ++a) v[a] *= sc;
-                }
-            }
-        }
-        // F_h, T_h: the momentum exchanged with the fluid over the step, F0 - Z (V', Omega'),
-        // plus the pending impulses used here (Eqs. coupleF, coupleT)
-        const double xv[6] = {v[0], v[1], v[2], w[0], w[1], w[2]};
-        double zx[6] = {0, 0, 0, 0, 0, 0};
-        {
-            int z = 0;
-#pragma unroll
-            for (int a = 0; a < 6; ++a)
-#pragma unroll
-                for (int c = a; c < 6; ++c) {
-                    const double zz = zup[z++];
-                    zx[a] += zz * xv[c];
-                    if (c != a) zx[c] += zz * xv[a];
-                }
-        }
-        for (int a = 0; a < 3; ++a) {
-            s.Fh[3 * p + a] = (lp[a] - zx[a]) + Phv[a];
-            s.Th[3 * p + a] = (lp[3 + a] - zx[3 + a]) + Lhv[a];
-        }
-        if (s.pv_ring > 0) {
-            double *pv = s.pvring + ((t % s.pv_ring) * (long long)s.ptot + p) * 3;
-            pv[0] = v[0]; pv[1] = v[1]; pv[2] = v[2];
-        }
-        for (int a = 0; a < 3; ++a) {
-            Vn[3 * p + a] = v[a];
-            Wn[3 * p + a] = w[a];
-            double xa = Xc[a] + v[a];
-            if (fixed_p) {
-                xa = Xc[a];
-            } else if (per[a]) {
-                if (xa >= box[a]) xa -= box[a];
-                else if (xa < 0.0) xa += box[a];
-            } else {
-                if (xa < 0.0 || xa > box[a] - 1.0) atomicOr(s.flags, 0x10u);
-                xa = fmin(fmax(xa, 0.0), box[a] - 1.0);
-            }
-            Xn[3 * p + a] = xa;
-        }
-        // the fluid kernel's wall state of this step: X(t) and the new velocities
-        pack_state(s.pf[par] + 12 * p, Xo + 3 * p, v, w);
-    }
-}
-
 
 // ---------------------------------------------------------------------------
 // re-projection kernel
@@ -3578,17 +3620,22 @@ void *fluid_kernel_ptr(int prec, int compact, int narrow)
     if (narrow) return compact ? fluid_ptr<true, true>(prec) : fluid_ptr<false, true>(prec);
     return compact ? fluid_ptr<true, false>(prec) : fluid_ptr<false, false>(prec);
 }
-template <bool NR>
+template <bool NR, bool FUSED>
 void *links_ptr(int prec)
 {
     switch (prec) {
-    case PREC_FP64: return (void *)&k_links<PREC_FP64, NR>;
-    case PREC_FP32: return (void *)&k_links<PREC_FP32, NR>;
-    case PREC_FP16DEV: return (void *)&k_links<PREC_FP16DEV, NR>;
-    default: return (void *)&k_links<PREC_BF16DEV, NR>;
+    case PREC_FP64: return (void *)&k_links<PREC_FP64, NR, FUSED>;
+    case PREC_FP32: return (void *)&k_links<PREC_FP32, NR, FUSED>;
+    case PREC_FP16DEV: return (void *)&k_links<PREC_FP16DEV, NR, FUSED>;
+    default: return (void *)&k_links<PREC_BF16DEV, NR, FUSED>;
     }
 }
-void *links_kernel_ptr(int prec, int narrow) { return narrow ? links_ptr<true>(prec) : links_ptr<false>(prec); }
+bool links_fused(const DevSet &s) { return s.ptot <= kFusedParticles; }
+void *links_kernel_ptr(int prec, const DevSet &s)
+{
+    if (s.narrow) return links_fused(s) ? links_ptr<true, true>(prec) : links_ptr<true, false>(prec);
+    return links_fused(s) ? links_ptr<false, true>(prec) : links_ptr<false, false>(prec);
+}
 void *motion_kernel_ptr() { return (void *)&k_motion; }
 void *remap_kernel_ptr_prec(int prec)
 {
@@ -3599,7 +3646,7 @@ void *remap_kernel_ptr_prec(int prec)
     default: return (void *)&k_remap<PREC_BF16DEV>;
     }
 }
-int links_grid(const DevSet &s) { return max(2 * s.ptot, 1); }
+int links_grid(const DevSet &s) { return max(links_fused(s) ? s.ptot : 2 * s.ptot, 1); }
 int refresh_grid(const DevSet &) { return kRefreshBlocks; }
 void *refresh_kernel_ptr(int prec)
 {
@@ -3632,13 +3679,12 @@ hipError_t launch_fluid(int prec, const DevSet &s, hipStream_t st)
     return hipGetLastError();
 }
 
-int links_block() { return 64 * kLinksWaves; }
+int links_block(const DevSet &s) { return links_fused(s) ? 64 * (links_waves(true) + 1) : 64 * links_waves(false); }
 
 hipError_t launch_links(int prec, const DevSet &s, hipStream_t st)
 {
-    const int mode = 0, only = -1;
-    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet, int, int)>(links_kernel_ptr(prec, s.narrow)),
-                       dim3(links_grid(s)), dim3(64 * kLinksWaves), 0, st, s, mode, only);
+    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet)>(links_kernel_ptr(prec, s)), dim3(links_grid(s)),
+                       dim3(links_block(s)), 0, st, s);
     return hipGetLastError();
 }
 
