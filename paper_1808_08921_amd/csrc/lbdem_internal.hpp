@@ -244,8 +244,10 @@ int adj_blocks(const AdjDev &a);
 
 // dispersion analysis (lbdem_analysis.hip)
 struct DftPlan {
-    int nwb, nzb, threads, nchunk;   // frequency blocks of 64, column blocks, threads per block, time chunks
-    long long chunk;                  // steps per time chunk
+    int nwb, ztiles, nzb, nchunk;     // frequency blocks, column tiles per block, column blocks, time chunks
+    long long seg;                    // steps per wave of the time stage (four a chunk)
+    int nslice;                       // slices of the fit's sums
+    long long slice;                  // steps per slice
     size_t part_bytes, g_bytes, e_bytes;  // workspace: chunk partials, time-stage sums, phase table
 };
 DftPlan dft_plan(long long nt, int nz, int nw, int nk);
