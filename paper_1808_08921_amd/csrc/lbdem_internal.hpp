@@ -49,7 +49,10 @@ constexpr int kEmpty = 0x7fffffff;
 // used, bit 63 when more than four particles border x.  Word 1: bits 0-17 the high slot
 // bit per direction, bits 18-30 and 31-43 the local indices in slots 2 and 3.
 constexpr int kMaxLocal = 8191;     // particles per lattice (13-bit local indices)
-constexpr int kRefreshBlocks = 512; // workgroups of the start-of-step refresh kernel
+// workgroups of the start-of-step refresh kernel: as many as are resident at once at its 123
+// registers (512 | 1024 | 2048: 17.0 | 11.6 | 11.7 us a step for 16 FCC lattices, 3.36 | 2.26 |
+// 2.25 ms for their first lists; 135 | 115 | 114 us per rebuild of a settling suspension)
+constexpr int kRefreshBlocks = 1024;
 constexpr int kMaxPlaneWords = 8192; // row-table words of one x-y plane held in LDS (compact storage)
 constexpr int kRtLds = 1536;        // row-table words a fluid-kernel workgroup stages in LDS (compact storage)
 
@@ -123,7 +126,7 @@ struct DevSet {
     int *own[2];
     unsigned long long *lw;   // link words, two per node (all lattices) [2*ncell_total]
     // compact storage: the first link word of each listed node at its storage slot, or
-    // kSolidWord for a listed solid node (the fluid and record kernels read these in slot
+    // kSolidWord for a listed solid node (the fluid kernel reads these in slot
     // order), and the step at which a full copy of the node map made them all stale
     unsigned long long *lwc;  // [ncell_total]
     long long *lwc_bad;

@@ -746,10 +746,10 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
     const long long stride = (long long)gridDim.x * blockDim.x;
     const long long t0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     bool over = false;
-    // (a step that rebuilds the node lists rewrites every compact word in the record kernel)
+    // (a step that rebuilds the node lists rewrites every compact word in the fluid kernel)
     const bool fix_compact = s.compact && !relist;
     if (cnt > s.chg_cap) {
-        // (every link word may change: the record kernel rewrites every compact word)
+        // (every link word may change: the fluid kernel rewrites every compact word)
         if (t0 == 0) *s.lwc_bad = t;
         for (long long c = t0; c < s.ncell_total; c += stride) {
             s.own[par ^ 1][c] = s.own[par][c];
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
         // scans kScanCells cells at a time with their loads together and one barrier, a node's
         // 19 values are loaded before the first is stored, nodes ahead of the first change of
         // the list stay where they are, and the row tables' running counts come from one scan
-        // over the workgroup (settling suspension, FP32, 340 -> 137 us per rebuild; two or four
+        // over the workgroup (settling suspension, FP32, 340 -> 115 us per rebuild; two or four
         // nodes' values in flight per thread 237 and 191 us, for their registers).
         constexpr int kScanCells = 4;
         using U = typename std::conditional<sizeof(S) == 8, unsigned long long,
