@@ -254,7 +254,7 @@ int lbdem_owner_get(lbdem_set *set, int32_t lattice, int32_t *owner);
  * = sum_d f_d c_d; the collision keeps both, so they are also the moments the step's
  * collision used): rho [ncell], u [3][ncell] (component-major), owner [ncell] as for
  * lbdem_owner_get.  At solid nodes rho and u are 0.  Any output may be NULL.  Host arrays;
- * synchronises.  Errors: LBDEM_EINVAL, LBDEM_ENOMEM (device scratch), LBDEM_EDEVICE. */
+ * synchronises.  Errors: LBDEM_EINVAL, LBDEM_EDEVICE. */
 int lbdem_fields_get(lbdem_set *set, int32_t lattice, double *rho, double *u, int32_t *owner);
 
 /* ---- Checkpoint and resume ----
@@ -282,7 +282,9 @@ int lbdem_state_load(lbdem_set *set, const void *buf, size_t size);
  * kernels one by one and brackets every launch with a pair of events.  lbdem_timing_read
  * synchronises and returns, for kernel k = 0 (links), 1 (particle motion), 2 (fluid),
  * 3 (re-projection), 4 (start-of-step node-map refresh), the summed milliseconds ms[k] and
- * the number of launches count[k] since enabling (ms and count hold 5 entries). */
+ * the number of launches count[k] since enabling (ms and count hold 5 entries).  A kernel
+ * that a set has no use for counts 0 launches: the motion in a set of at most 256 particles,
+ * whose link kernel does it, links, motion and refresh in a set without particles. */
 int lbdem_timing_enable(lbdem_set *set, int enable);
 int lbdem_timing_read(lbdem_set *set, double *ms, int64_t *count);
 
