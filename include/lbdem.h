@@ -24,6 +24,8 @@
  *     call synchronises the library's stream before returning when it copies data.
  *   - Device work is queued on the HIP stream given to lbdem_create (or later to
  *     lbdem_set_stream); lbdem_step is asynchronous with respect to the host.
+ *   - lbdem_particles_get and lbdem_fields_get may be called for one set from several host
+ *     threads at once (the set's device scratch serves them one after the other).
  *   - Particle indices are per lattice, in the caller's order, 0..n-1.
  *   - Populations are exchanged as double, [19][nz][ny][nx], direction d = 0..18 being
  *     the paper's d = 1..19 of Eq. (3d19q) (d = 18 is the rest population).

@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -400,6 +401,9 @@ struct lbdem_set {
     // compact storage: populations currently held at their nodes (after creation or an
     // expansion, until the next step's list rebuild compacts them again)
     bool node_layout = true;
+    // held by a read from its launch into the node scratch until its copies are done (reads
+    // may come from several host threads at once)
+    std::mutex scratch_mu;
     // graph
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
@@ -924,6 +928,7 @@ int lbdem_particles_get(lbdem_set *S, int32_t lattice, int32_t n, double *x, dou
     if (5 * n3 * sizeof(double) <= 64 * (size_t)S->G.cells) {
         std::vector<double> host(5 * n3);
         double *dev = reinterpret_cast<double *>(S->ds.scratch);
+        std::lock_guard<std::mutex> lock(S->scratch_mu);
         HIPCHK(launch_particles_out(S->ds, M.p_off, n, dev, S->stream));
         HIPCHK(hipMemcpyAsync(host.data(), dev, sizeof(double) * host.size(), hipMemcpyDeviceToHost, S->stream));
         rc = sync_set(S);
@@ -1289,6 +1294,7 @@ int lbdem_fields_get(lbdem_set *S, int32_t lattice, double *rho, double *u, int3
     // (the fields take 32 of the node scratch's 64 bytes a node; they go straight to the caller)
     const size_t n = (size_t)S->G.mem[lattice].ncell;
     double *dev = reinterpret_cast<double *>(S->ds.scratch);
+    std::lock_guard<std::mutex> lock(S->scratch_mu);
     hipError_t e = launch_fields(S->G.prec, S->ds, lattice, (long long)n, dev, S->stream);
     if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, dev, sizeof(double) * n, hipMemcpyDeviceToHost, S->stream);
     if (e == hipSuccess && u) e = hipMemcpyAsync(u, dev + n, sizeof(double) * 3 * n, hipMemcpyDeviceToHost, S->stream);

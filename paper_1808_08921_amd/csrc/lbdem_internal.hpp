@@ -131,7 +131,8 @@ struct DevSet {
     unsigned long long *lwc;  // [ncell_total]
     long long *lwc_bad;
     long long ncell_total;
-    // 64 bytes per node that hold nothing between calls (fields of lbdem_fields_get)
+    // 64 bytes per node that hold nothing between calls (the reads of particles and fields
+    // gather into it, one at a time)
     void *scratch;
     int *chg[2];
     int chg_cap;
