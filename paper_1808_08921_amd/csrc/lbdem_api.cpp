@@ -11,6 +11,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -923,19 +924,20 @@ int lbdem_particles_get(lbdem_set *S, int32_t lattice, int32_t n, double *x, dou
     if (n != M.np) return fail(LBDEM_EINVAL, "lattice %d has %d particles, asked for %d", lattice, M.np, n);
     if (n == 0) return sync_set(S);
     // one gather into the node scratch and one copy, unless they do not fit it (fewer than two
-    // nodes a particle)
+    // nodes a particle) or the host has no memory for them
     const size_t n3 = 3 * (size_t)n;
-    if (5 * n3 * sizeof(double) <= 64 * (size_t)S->G.cells) {
-        std::vector<double> host(5 * n3);
+    std::unique_ptr<double[]> host;
+    if (5 * n3 * sizeof(double) <= 64 * (size_t)S->G.cells) host.reset(new (std::nothrow) double[5 * n3]);
+    if (host) {
         double *dev = reinterpret_cast<double *>(S->ds.scratch);
         std::lock_guard<std::mutex> lock(S->scratch_mu);
         HIPCHK(launch_particles_out(S->ds, M.p_off, n, dev, S->stream));
-        HIPCHK(hipMemcpyAsync(host.data(), dev, sizeof(double) * host.size(), hipMemcpyDeviceToHost, S->stream));
+        HIPCHK(hipMemcpyAsync(host.get(), dev, sizeof(double) * 5 * n3, hipMemcpyDeviceToHost, S->stream));
         rc = sync_set(S);
         if (rc) return rc;
         double *out[5] = {x, v, w, force, torque};
         for (int q = 0; q < 5; ++q)
-            if (out[q]) std::memcpy(out[q], host.data() + q * n3, sizeof(double) * n3);
+            if (out[q]) std::memcpy(out[q], host.get() + q * n3, sizeof(double) * n3);
         return LBDEM_OK;
     }
     rc = sync_set(S);

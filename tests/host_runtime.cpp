@@ -2,7 +2,7 @@
 // (lbdem_api.cpp) runs without a device: device memory is host memory, every queued operation
 // completes at once, and a launcher writes recognisable values instead of running a kernel.
 // Test switches: host_hold(ms) makes the first read launch wait until another one follows or
-// the time is over; host_fail_new(bytes) makes operator new throw from that size on.
+// the time is over; host_fail_new(bytes) makes operator new fail from that size on.
 #include <chrono>
 #include <condition_variable>
 #include <cstdlib>
@@ -20,6 +20,11 @@ void *operator new(size_t n)
     if (!p) throw std::bad_alloc();
     return p;
 }
+void *operator new[](size_t n, const std::nothrow_t &) noexcept
+{
+    return (g_fail_new && n >= g_fail_new) ? nullptr : std::malloc(n ? n : 1);
+}
+void operator delete[](void *p) noexcept { std::free(p); }
 void operator delete(void *p) noexcept { std::free(p); }
 void operator delete(void *p, size_t) noexcept { std::free(p); }
 

@@ -99,3 +99,28 @@ def test_readers_of_one_set_on_two_threads(host, first, second):
     for out, want in checks:
         assert np.array_equal(out, want)
     host.lbdem_destroy(h)
+
+
+def test_read_without_host_memory(host):
+    """No exception crosses the interface when the host has no memory for a staging copy: the
+    read then copies array by array (run in a process of its own, which an exception ends)."""
+    code = f"""
+import ctypes, sys
+sys.path.insert(0, {ROOT!r}); sys.path.insert(0, {os.path.join(ROOT, "tests")!r})
+import numpy as np
+import test_host_readers as t
+from paper_1808_08921_amd import lbdem
+L = ctypes.CDLL({host.path!r})
+L.lb = lbdem
+n = 50
+h = t.make_set(L, [(20, 20, 20)], n)
+t.place(L, h, 0, n)
+out = np.full((5, n, 3), 7.0)
+L.host_fail_new(ctypes.c_size_t(1024))
+rc = L.lbdem_particles_get(h, 0, n, *[t.doubles(out[q]) for q in range(5)])
+L.host_fail_new(ctypes.c_size_t(0))
+assert rc == 0, rc
+assert (out[0] == 4.0).all() and not out[1:].any()
+"""
+    r = subprocess.run([os.sys.executable, "-c", code], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
