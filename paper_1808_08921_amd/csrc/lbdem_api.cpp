@@ -1514,7 +1514,7 @@ static size_t adj_layout(lbdem_adj *J, const MemberDev &M, int nprobe, int64_t n
     const size_t st = (size_t)kQ * cap, np1 = (size_t)std::max(M.np, 1), npr = (size_t)std::max(nprobe, 1);
     const int nck = (int)((nsteps + ck - 1) / ck);
     char *f0 = c.take<char>(es * st);
-    char *ckp = c.take<char>(es * st * (size_t)std::max(nck - 1, 1));
+    char *ckp = c.take<char>(es * st * (size_t)(nck - 1)); // (the first segment starts from f0)
     char *seg = c.take<char>(es * st * (size_t)std::max(ck, 2));
     char *lam0 = c.take<char>(cs * st), *lam1 = c.take<char>(cs * st);
     a.wall = c.take<char>(cs * (size_t)(kQ - 1) * cap);

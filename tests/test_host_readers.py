@@ -124,3 +124,24 @@ assert (out[0] == 4.0).all() and not out[1:].any()
 """
     r = subprocess.run([os.sys.executable, "-c", code], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("precision,es,cs", [("fp64", 8, 8), ("fp32", 4, 4), ("fp16", 2, 4)])
+def test_adjoint_workspace_of_one_segment(host, precision, es, cs):
+    """A window of one segment starts from the window's start state and keeps no checkpoint:
+    per node (rounded up to a wave) the start and one state per step, two adjoint fields, per
+    direction a wall term and an FP64 gradient sum, the node map and the slot tables (at most
+    32 bytes); then tables by plane, step and workgroup, here below 8 KB."""
+    lb = host.lb
+    lat = (lb.Params * 1)(lb.make_params(40, 40, 40))
+    cfg = lb.Config()
+    host.lbdem_default_config(ctypes.byref(cfg))
+    cfg.graph_steps, cfg.precision = 0, lb.PRECISIONS[precision]
+    h = ctypes.c_void_p()
+    assert host.lbdem_create(1, lat, ctypes.byref(cfg), None, ctypes.c_size_t(0), None, ctypes.byref(h)) == lb.OK
+    need = ctypes.c_size_t()
+    steps = 5
+    assert host.lbdem_adj_workspace_size(h, 0, ctypes.c_int64(steps), steps, ctypes.byref(need)) == lb.OK
+    node = 19 * es * (1 + steps) + 2 * 19 * cs + 18 * (cs + 8) + 32
+    assert need.value <= node * 40 ** 3 + 8192
+    host.lbdem_destroy(h)
