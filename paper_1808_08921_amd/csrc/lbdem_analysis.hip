@@ -25,7 +25,9 @@ namespace {
 
 constexpr int kAnchor = 64;   // rotations between exact phases
 constexpr int kMT = 2;        // tiles of 16 frequencies per wave in the time stage
-constexpr int kTimeBlocks = 512; // two workgroups a CU
+constexpr int kCus = 256;
+constexpr int kTimeBlocks = 2 * kCus; // two workgroups a CU
+constexpr long long kSplitRow = 131072; // elements of E a row reads from which it is split
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -239,18 +241,51 @@ __global__ __launch_bounds__(256) void k_dft_sum(const double2 *__restrict__ par
     E[i] = make_double2(c, s);
 }
 
-// F[m][n] = sum_z G[m][z] E[z][n] for MR rows m and every n, and ridge[m], the first n of the
-// largest re^2 + im^2 in row m (-1 if none compares).  One workgroup per MR rows: an element of
-// E serves MR rows, and a row's maximum needs no second pass over F (1024 x 1024 x 24: 17 + 7 us
-// one row and 256 n at a time with a kernel for the ridge, 12 us).
+// ridge[m0 + r], the first n of the largest |F|^2 in row m0 + r (-1 if none compares), from each
+// thread's largest and its n
 template <int MR>
-__global__ __launch_bounds__(1024) void k_dft_space(const double2 *__restrict__ G, const double2 *__restrict__ E,
-                                                    int nz, int nw, int nk, double2 *__restrict__ F,
-                                                    int *__restrict__ ridge)
+__device__ inline void store_ridge(const double (&best)[MR], const int (&first)[MR], int m0, int nw,
+                                   int *__restrict__ ridge)
 {
     __shared__ double s_p[16][MR];
     __shared__ int s_n[16][MR];
-    const int m0 = blockIdx.x * MR;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nwv = blockDim.x >> 6;
+#pragma unroll
+    for (int r = 0; r < MR; ++r) {
+        const double top = wave_max(best[r]);
+        const int n = wave_min(best[r] == top ? first[r] : 0x7fffffff);
+        if (lane == 0) {
+            s_p[wv][r] = top;
+            s_n[wv][r] = n;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < MR && m0 + (int)threadIdx.x < nw) {
+        double b = s_p[0][threadIdx.x];
+        int n = s_n[0][threadIdx.x];
+        for (int w = 1; w < nwv; ++w) {
+            const double ob = s_p[w][threadIdx.x];
+            const int on = s_n[w][threadIdx.x];
+            if (ob > b || (ob == b && on < n)) {
+                b = ob;
+                n = on;
+            }
+        }
+        ridge[m0 + threadIdx.x] = n == 0x7fffffff ? -1 : n;
+    }
+}
+
+// F[m][n] = sum_z G[m][z] E[z][n] for MR rows m and the n of this workgroup (all of them, or
+// one of `parts` parts), and with ridge the rows' ridge, for which the workgroup has to hold
+// every n.  (Workgroups of neighbouring numbers take the parts of the same rows: with a multiple
+// of 8 of them each XCD keeps to its parts of E, which then stay in its L2.)  An element of E serves MR rows, and a row's maximum needs no second pass over F
+// (1024 x 1024 x 24: 17 + 7 us one row and 256 n at a time with a kernel for the ridge, 12 us).
+template <int MR, int UZ>
+__global__ __launch_bounds__(1024) void k_dft_space(const double2 *__restrict__ G, const double2 *__restrict__ E,
+                                                    int nz, int nw, int nk, double2 *__restrict__ F,
+                                                    int *__restrict__ ridge, int parts)
+{
+    const int m0 = (int)(blockIdx.x / (unsigned)parts) * MR, part = (int)(blockIdx.x % (unsigned)parts);
     double best[MR];
     int bi[MR];
     const double2 *g[MR];
@@ -260,11 +295,11 @@ __global__ __launch_bounds__(1024) void k_dft_space(const double2 *__restrict__ 
         bi[r] = 0x7fffffff;
         g[r] = G + (size_t)min(m0 + r, nw - 1) * nz;
     }
-    for (int n = threadIdx.x; n < nk; n += blockDim.x) {
+    for (int n = part * (int)blockDim.x + (int)threadIdx.x; n < nk; n += parts * (int)blockDim.x) {
         double2 acc[MR];
 #pragma unroll
         for (int r = 0; r < MR; ++r) acc[r] = make_double2(0.0, 0.0);
-#pragma unroll 4
+#pragma unroll UZ
         for (int z = 0; z < nz; ++z) {
             const double2 e = E[(size_t)z * nk + n];
 #pragma unroll
@@ -280,31 +315,24 @@ __global__ __launch_bounds__(1024) void k_dft_space(const double2 *__restrict__ 
             }
         }
     }
-    if (!ridge) return;
-    auto take = [](double &b, int &n, double ob, int on) {
-        if (ob > b || (ob == b && on < n)) {
-            b = ob;
-            n = on;
-        }
-    };
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nwv = blockDim.x >> 6;
-#pragma unroll
-    for (int r = 0; r < MR; ++r) {
-        const double top = wave_max(best[r]);
-        bi[r] = wave_min(best[r] == top ? bi[r] : 0x7fffffff);
-        best[r] = top;
-        if (lane == 0) {
-            s_p[wv][r] = best[r];
-            s_n[wv][r] = bi[r];
+    if (ridge) store_ridge<MR>(best, bi, m0, nw, ridge);
+}
+
+// The ridge of one row per workgroup, where the rows are split over workgroups.
+__global__ __launch_bounds__(1024) void k_ridge(const double2 *__restrict__ F, int nw, int nk, int *__restrict__ ridge)
+{
+    double best[1] = {-1.0};
+    int bi[1] = {0x7fffffff};
+    const double2 *f = F + (size_t)blockIdx.x * nk;
+    for (int n = threadIdx.x; n < nk; n += blockDim.x) {
+        const double2 v = f[n];
+        const double p = v.x * v.x + v.y * v.y;
+        if (p > best[0]) {
+            best[0] = p;
+            bi[0] = n;
         }
     }
-    __syncthreads();
-    if (threadIdx.x < MR && m0 + (int)threadIdx.x < nw) {
-        double b = s_p[0][threadIdx.x];
-        int n = s_n[0][threadIdx.x];
-        for (int w = 1; w < nwv; ++w) take(b, n, s_p[w][threadIdx.x], s_n[w][threadIdx.x]);
-        ridge[m0 + threadIdx.x] = n == 0x7fffffff ? -1 : n;
-    }
+    store_ridge<1>(best, bi, (int)blockIdx.x, nw, ridge);
 }
 
 // partial sums of x[t][z] exp(-j omega (t0 + t)) over the steps of slice s: one wave per
@@ -515,12 +543,29 @@ hipError_t launch_st_dft(const DftPlan &p, const double *x, long long nt, int nz
     const unsigned sum_blocks = (unsigned)ceil_div(nmz, 256);
     hipLaunchKernelGGL(k_dft_sum, dim3(sum_blocks + (unsigned)ceil_div((long long)nz * nk, 256)), dim3(256), 0, st,
                        (const double2 *)part, nmz, p.nchunk, G, sum_blocks, zpos, nz, k0, dk, nk, E);
-    // (rows per workgroup: as many as leave a workgroup for every CU)
-    const dim3 sblock((unsigned)std::min<long long>(1024, ceil_div(nk, 64) * 64));
-    auto space = nw >= 1024 ? k_dft_space<4> : (nw >= 512 ? k_dft_space<2> : k_dft_space<1>);
-    const int mr = nw >= 1024 ? 4 : (nw >= 512 ? 2 : 1);
-    hipLaunchKernelGGL(space, dim3((unsigned)ceil_div(nw, mr)), sblock, 0, st, (const double2 *)G, (const double2 *)E,
-                       nz, nw, nk, (double2 *)F, ridge);
+    // One workgroup per row leaves CUs without one where rows are few: once a row keeps a CU
+    // longer than the launch of a kernel for the ridge takes, it is split over workgroups of 256 n
+    // (us per call, one workgroup a row | split: 64 x 1024 x 24 20.5 | 23.7, 16 x 4096 x 24
+    // 31.9 | 24.6, 16 x 4096 x 64 57 | 25, 1 x 4096 x 4096 2712 | 285, 1 x 2^20 x 24 7417 | 642;
+    // sizes nw x nk x nz).  With few columns a row costs little more than F, which the ridge's
+    // kernel would read again: 203 x 71856 x 2 74 | 97.
+    // Rows share a load of E as long as a workgroup is left for every CU and enough waves to hide
+    // each other's chains of loads (1, 2, 4 rows: 1024 x 64 x 1000 84, 125, 141 us; 600 x 300 x
+    // 4096 634, 445, -; 1024 x 256 x 1000 177, 133, 147; 1024 x 1024 x 1000 553, 321, 243).
+    const bool split = nw < 2 * kCus && nk > 256 && nz >= 8 && (long long)nz * nk > kSplitRow;
+    const dim3 sblock(split ? 256u : (unsigned)std::min<long long>(1024, ceil_div(nk, 64) * 64));
+    const long long waves = nw * ceil_div(nk, 64);
+    const int mr = (split || nw >= 4 * kCus) && waves >= 64 * kCus ? 4
+                 : (split || nw >= 2 * kCus) && waves >= 10 * kCus ? 2 : 1;
+    // (with many columns a chain of loads: one row leaves the registers for eight in flight, 16 x
+    // 16 x 4096 322 us with four, 200 with eight)
+    auto space = mr == 4 ? k_dft_space<4, 4> : (mr == 2 ? k_dft_space<2, 4>
+                                                        : (nz >= 32 ? k_dft_space<1, 8> : k_dft_space<1, 4>));
+    const int parts = split ? (int)ceil_div(nk, 256) : 1;
+    hipLaunchKernelGGL(space, dim3((unsigned)(ceil_div(nw, mr) * parts)), sblock, 0, st, (const double2 *)G,
+                       (const double2 *)E, nz, nw, nk, (double2 *)F, split ? nullptr : ridge, parts);
+    if (split && ridge)
+        hipLaunchKernelGGL(k_ridge, dim3(nw), dim3(1024), 0, st, (const double2 *)F, nw, nk, ridge);
     return hipGetLastError();
 }
 
