@@ -82,6 +82,7 @@ struct Geometry {
     int ring_len = 1;
     int pv_ring = 0;
     int chg_cap = 0;
+    int chunks = kChunks;
     int xcap = 1;
     int prec = PREC_FP32;
 };
@@ -263,7 +264,14 @@ void build_geometry(int32_t n, const lbdem_params *lat, const lbdem_config *cfg,
             if (G.mem[m].narrow) images = 2;
         }
     if (rmax > 0.0) {
-        const int hz = ((int)std::ceil(2.0 * (rmax + kSlabReach + kSlabLens + 1e-9)) + 4 + kChunks - 1) / kChunks;
+        // The planes around the largest particle, and the chunks they are cut into.  A wave takes a
+        // chunk, so a set of one sphere has 8 waves for its link pass: from a radius of 15 on the
+        // chunks are halved while the chip has room for their waves (one sphere at rest, FP32, us
+        // for links and motion, 8 chunks in one kernel | as here: radius 15 27 | 27, 20 39 | 29,
+        // 40 161 | 52, 60 412 | 96, 100 1014 | 148).
+        const int ext = (int)std::ceil(2.0 * (rmax + kSlabReach + kSlabLens + 1e-9)) + 4;
+        while (ext > kSlabPlanes * G.chunks && G.chunks < kMaxChunks && 2LL * G.chunks * pt <= 4096) G.chunks *= 2;
+        const int hz = (ext + G.chunks - 1) / G.chunks;
         G.xcap = images * hz * ((int)std::ceil(M_PI * (2.0 * rmax + std::sqrt(2.0)) * 2.0 * std::sqrt(2.0)) + 4);
     }
 }
@@ -340,19 +348,20 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.pmem = c.take<int>(P);
     s.pv_ring = G.pv_ring;
     s.pvring = c.take<double>(G.pv_ring > 0 ? (size_t)G.pv_ring * P * 3 : 1);
-    s.ppart = c.take<double>((size_t)P * kChunks * kLinkComp);
-    s.zcache = c.take<double>((size_t)P * kChunks * kZComp);
+    s.chunks = G.chunks;
+    s.ppart = c.take<double>((size_t)P * s.chunks * kLinkComp);
+    s.zcache = c.take<double>((size_t)P * s.chunks * kZComp);
     s.nearl = c.take<int>((size_t)P * kNearCap);
     s.nnear = c.take<int>(P);
     s.near_due = c.take<long long>(G.mem.size());
     s.Xn = c.take<double>(3 * (size_t)P);
     s.xcap = G.xcap;
-    s.xcell = c.take<int>((size_t)P * kChunks * G.xcap);
-    s.xslot = c.take<int>((size_t)P * kChunks * G.xcap);
-    s.xgrp = c.take<unsigned>((size_t)P * kChunks * G.xcap);
-    s.xcnt = c.take<int>((size_t)P * kChunks);
+    s.xcell = c.take<int>((size_t)P * s.chunks * G.xcap);
+    s.xslot = c.take<int>((size_t)P * s.chunks * G.xcap);
+    s.xgrp = c.take<unsigned>((size_t)P * s.chunks * G.xcap);
+    s.xcnt = c.take<int>((size_t)P * s.chunks);
     s.lreb = c.take<long long>(P);
-    s.ldirty = c.take<long long>((size_t)P * kChunks);
+    s.ldirty = c.take<long long>((size_t)P * s.chunks);
     s.lzr = c.take<int>(2 * (size_t)P);
     for (int k = 0; k < 2; ++k) {
         s.hj[k] = c.take<int>((size_t)P * kHistCap);
@@ -533,11 +542,11 @@ int build_graph(lbdem_set *S, int steps)
     // refresh -> link pass -> motion -> fluid -> re-projection, less what the set has no use for
     const bool on[kKernels] = {step_runs(S, 0), step_runs(S, 1), step_runs(S, 2), step_runs(S, 3), step_runs(S, 4)};
     for (int k = 0; k < steps; ++k) {
-        auto add = [&](bool run, void *func, int grid, int block, void **args) -> hipError_t {
+        auto add = [&](bool run, void *func, dim3 grid, int block, void **args) -> hipError_t {
             if (!run) return hipSuccess;
             hipKernelNodeParams kp{};
             kp.func = func;
-            kp.gridDim = dim3(grid);
+            kp.gridDim = grid;
             kp.blockDim = dim3(block);
             kp.kernelParams = args;
             hipGraphNode_t node;
@@ -547,7 +556,7 @@ int build_graph(lbdem_set *S, int steps)
         };
         HIPCHK(add(on[4], refresh_kernel_ptr(S->G.prec), refresh_grid(S->ds), 256, fluid_args));
         HIPCHK(add(on[0], links_kernel_ptr(S->G.prec, S->ds), links_grid(S->ds), links_block(S->ds), fluid_args));
-        HIPCHK(add(on[1], motion_kernel_ptr(), motion_grid(S->ds), 256, part_args));
+        HIPCHK(add(on[1], motion_kernel_ptr(S->ds), motion_grid(S->ds), 256, part_args));
         HIPCHK(add(on[2], fluid_kernel_ptr(S->G.prec, S->G.compact, S->ds.narrow), S->ds.tiles_total, 256, fluid_args));
         HIPCHK(add(on[3], remap_kernel_ptr_prec(S->G.prec), remap_grid(S->ds), 256, part_args));
     }
@@ -777,9 +786,9 @@ int lbdem_create(int32_t n_lat, const lbdem_params *lat, const lbdem_config *cfg
     CHK(hipMemsetAsync(s.pf[1], 0, sizeof(float) * 12 * P, st));
     CHK(hipMemsetAsync(s.nnear, 0, sizeof(int) * P, st));
     CHK(hipMemsetAsync(s.near_due, 0xff, sizeof(long long) * S->G.mem.size(), st)); // -1: none due
-    CHK(hipMemsetAsync(s.xcnt, 0, sizeof(int) * P * kChunks, st));
+    CHK(hipMemsetAsync(s.xcnt, 0, sizeof(int) * P * s.chunks, st));
     CHK(hipMemsetAsync(s.lreb, 0xff, sizeof(long long) * P, st));
-    CHK(hipMemsetAsync(s.ldirty, 0xff, sizeof(long long) * P * kChunks, st));
+    CHK(hipMemsetAsync(s.ldirty, 0xff, sizeof(long long) * P * s.chunks, st));
     CHK(hipMemsetAsync(s.lzr, 0, sizeof(int) * 2 * P, st));
     CHK(hipMemsetAsync(s.tstep, 0, sizeof(long long), st));
     CHK(hipMemsetAsync(s.tcopy, 0, sizeof(long long), st));

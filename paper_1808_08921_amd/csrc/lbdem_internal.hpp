@@ -35,7 +35,11 @@ constexpr double kListSkin = 0.25;
 constexpr double kSkinMin = 0.05;
 constexpr double kSkinSteps = 12.0;
 constexpr int kPendCap = 16384;     // refills of unlisted nodes awaiting the next list rebuild
-constexpr int kChunks = 8;          // z-slabs of the nodes around a particle: waves per particle in the link pass
+// z-slabs of the nodes around a particle, one wave of the link pass each; in sets of few large
+// particles up to kMaxChunks (DevSet::chunks), so that a slab keeps to about kSlabPlanes planes
+constexpr int kChunks = 8;
+constexpr int kMaxChunks = 64;
+constexpr int kSlabPlanes = 5;
 // components of a link-pass partial per (particle, chunk): F0 (3) and sum xr x G (3), xr the
 // node position relative to the particle's reference point
 constexpr int kLinkComp = 6;
@@ -154,19 +158,20 @@ struct DevSet {
     int *fixed, *pmem;
     double *pvring;           // particle velocities after each step [pv_ring][ptot][3] (0 steps: none)
     int pv_ring;
-    double *ppart;            // link-pass partials per (particle, chunk) [ptot*kChunks*kLinkComp]
-    double *zcache;           // link-set sums per (particle, chunk), rebuilt with its entries [ptot*kChunks*kZComp]
+    double *ppart;            // link-pass partials per (particle, chunk) [ptot*chunks*kLinkComp]
+    double *zcache;           // link-set sums per (particle, chunk), rebuilt with its entries [ptot*chunks*kZComp]
     int *nearl, *nnear;       // [ptot*kNearCap], [ptot]
     long long *near_due;      // step whose re-projection builds a lattice's near lists [nmem]
     double *Xn;               // particle positions when its near list was built [ptot*3]
     // link entries: the nodes with links of a particle, per chunk in list order (z, y, x), at
-    // [(p*kChunks + chunk)*xcap, + xcnt[p*kChunks + chunk])
+    // [(p*chunks + chunk)*xcap, + xcnt[p*chunks + chunk])
+    int chunks;               // chunks per particle, kChunks .. kMaxChunks (a multiple of kChunks)
     int xcap;
     int *xcell, *xcnt;
     int *xslot;               // storage slot of each cached entry's node
     unsigned *xgrp;           // the particle's link directions at each cached entry's node
     long long *lreb;          // step after which the particle's slabs were last laid out [ptot]
-    long long *ldirty;        // last step in which link words of a chunk's nodes changed [ptot*kChunks]
+    long long *ldirty;        // last step in which link words of a chunk's nodes changed [ptot*chunks]
     // chunks are z-slabs around X_ref: first z (unwrapped) and slab height [ptot*2]
     int *lzr;
     int *hj[2];               // tangential history partner ids [ptot*kHistCap]
@@ -227,11 +232,11 @@ hipError_t launch_fields(int prec, const DevSet &s, int m, long long ncell, doub
 void *refresh_kernel_ptr(int prec);
 bool links_fused(const DevSet &s); // the link kernel moves the particles too
 void *links_kernel_ptr(int prec, const DevSet &s);
-void *motion_kernel_ptr();
+void *motion_kernel_ptr(const DevSet &s);
 void *fluid_kernel_ptr(int prec, int compact, int narrow);
 void *remap_kernel_ptr_prec(int prec);
 int refresh_grid(const DevSet &s);
-int links_grid(const DevSet &s);
+dim3 links_grid(const DevSet &s);
 int links_block(const DevSet &s);
 int motion_grid(const DevSet &s);
 int remap_grid(const DevSet &s);

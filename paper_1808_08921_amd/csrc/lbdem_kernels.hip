@@ -10,7 +10,7 @@
 //                changes, refreshes the link words of the changed nodes and their
 //                neighbours, and rebuilds the node lists (moving the populations of changed
 //                planes under compact storage) once a particle may have crossed their skin.
-//   k_links      kChunks waves per particle, each for a z-slab of the nodes around it: the
+//   k_links      8 or more waves per particle, each for a z-slab of the nodes around it: the
 //                link pass.  A slab whose link words changed has its link entries found
 //                again first, with their link-set sums (the 6 x 6 matrix Z of the motion
 //                kernel comes from them).  With Eq. (mem) substituted, the link force of Eq.
@@ -586,7 +586,7 @@ __device__ __forceinline__ void mark_dirty(const DevSet &s, const MemberDev *M, 
     if (M->per[2]) dz = ((dz % M->nz) + M->nz) % M->nz;
     if (dz < 0) return;
     const int c = dz / hz;
-    if (c < kChunks) s.ldirty[q * kChunks + c] = t;
+    if (c < s.chunks) s.ldirty[q * s.chunks + c] = t;
 }
 
 // Link words of a node changed (re-projection of the previous step): the cached link
@@ -1534,8 +1534,8 @@ __device__ __forceinline__ double row_margin(double R) { return 2e-5 + 1e-6 * R;
 // chunk (about 190 candidates at R = 8.5), then the slots of the nodes that have links.
 // Returns the number of entries.
 template <bool NR>
-__device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M, int p, int chunk, double X0, double X1,
-                                              double X2, int *cells, int2 *segs, int *lc, unsigned *lg, double *zl)
+__device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M, int p, int chunk, int chunks,
+                                              double X0, double X1, double X2, int *cells, int2 *segs, int *lc, unsigned *lg, double *zl)
 {
     const int lane = threadIdx.x & 63;
     const int pl = p - uni(M->p_off);
@@ -1545,7 +1545,7 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
     const long long cell_off = uni(M->cell_off);
     const double rho_f = uni(M->rho_f);
     const int nxy = nx * ny;
-    const long long lbase = ((long long)p * kChunks + chunk) * s.xcap;
+    const long long lbase = ((long long)p * chunks + chunk) * s.xcap;
     int *xc = s.xcell + lbase;
     int *xs = s.xslot + lbase;
     unsigned *xg = s.xgrp + lbase;
@@ -1763,7 +1763,7 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
         }
     }
     {
-        if (lane == 0) s.xcnt[p * kChunks + chunk] = cntx;
+        if (lane == 0) s.xcnt[p * chunks + chunk] = cntx;
         // (the link-set sums read the entries back, from LDS, or from memory for a chunk
         // with more than kLinkLds entries: the wave's writes are made visible to the wave
         // itself; the other waves of its workgroup rebuild other chunks)
@@ -1873,7 +1873,7 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
                 FSF[a][1] = f2 * FS[a][0] - f0 * FS[a][2];
                 FSF[a][2] = f0 * FS[a][1] - f1 * FS[a][0];
             }
-            double *zc = s.zcache + ((long long)p * kChunks + chunk) * kZComp;
+            double *zc = s.zcache + ((long long)p * chunks + chunk) * kZComp;
             int z = 0;
             auto put = [&](double v) { zc[z] = v; if (zl) zl[z] = v; ++z; };
 #pragma unroll
@@ -1941,7 +1941,7 @@ __device__ __forceinline__ int rebuild_chunk(const DevSet &s, const MemberDev *M
 #pragma unroll
         for (int c = 0; c < 21; ++c) zs[c] = wave_sum(zs[c]);
         if (lane == 0) {
-            double *zc = s.zcache + ((long long)p * kChunks + chunk) * kZComp;
+            double *zc = s.zcache + ((long long)p * chunks + chunk) * kZComp;
 #pragma unroll
             for (int c = 0; c < 21; ++c) { zc[c] = zs[c]; if (zl) zl[c] = zs[c]; }
         }
@@ -2253,9 +2253,11 @@ __device__ __forceinline__ void motion_update(const DevSet &s, const MemberDev *
 
 // One wave per particle: mode 1, the near list and the FP32 state copy of a set-up (later lists
 // are built by the re-projection kernel); mode 0, the step's contacts and motion, unless a wave
-// of the link kernel does both.
+// of the link kernel does both.  MANY: more than kChunks chunks a particle (the loop over them
+// costs the others 0.2 us a launch).
 constexpr int kMotionWaves = 4;
 constexpr int kMotionWork = 45;
+template <bool MANY>
 __global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode, int only)
 {
     __shared__ double lp[kMotionWaves][kLinkComp + kZComp], work[kMotionWaves][kMotionWork];
@@ -2272,13 +2274,15 @@ __global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode
         if (!s.fluid_off) {
             const bool part = lane < kLinkComp;
             const int stride = part ? kLinkComp : kZComp;
-            const double *pp = part ? s.ppart + (long long)p * kChunks * kLinkComp + lane
-                                    : s.zcache + (long long)p * kChunks * kZComp + (lane - kLinkComp);
+            const long long c0 = (long long)p * (MANY ? s.chunks : kChunks);
+            const double *pp = part ? s.ppart + c0 * kLinkComp + lane : s.zcache + c0 * kZComp + (lane - kLinkComp);
             double ch[kChunks];
 #pragma unroll
             for (int q = 0; q < kChunks; ++q) ch[q] = pp[q * stride];
 #pragma unroll
             for (int q = 0; q < kChunks; ++q) v += ch[q];
+            if constexpr (MANY)
+                for (int q = kChunks; q < s.chunks; ++q) v += pp[q * stride];
         }
         lp[wv][lane] = v;
     }
@@ -2318,10 +2322,10 @@ __global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode
 // launch and its loads, but a workgroup holds its place until the motion is done, so it pays
 // while every workgroup has a CU of its own (FCC packings, FP32, us for links and motion, fused
 // | apart: 256 particles 19 | 25, 384 28 | 28, 512 32 | 30, 768 41 | 34; 60 in a chain, FP64,
-// 14 | 19).  Otherwise two workgroups per particle, first the equatorial slabs of every
+// 14 | 19).  Otherwise a workgroup per four slabs, first the equatorial slabs of every
 // particle, which hold most of the entries, then the polar ones (in slab order the long waves
 // of the last workgroups ran alone: 39 us instead of 36 on the FCC wave case), and the motion
-// kernel after.
+// kernel after.  A set with more than kChunks chunks a particle is not fused.
 constexpr int kFusedParticles = 256;
 constexpr int links_waves(bool fused) { return fused ? kChunks : kChunks / 2; }
 template <int P, bool NR, bool FUSED>
@@ -2343,9 +2347,12 @@ void k_links(DevSet s)
     if (s.ptot == 0) return;
     // particles in XCD order, neighbours sharing lines of the populations (45 us in launch
     // order on the FCC wave case, then 32)
-    const int half = !FUSED && (int)blockIdx.x >= s.ptot ? 1 : 0;
-    const int p = uni(xcd_swizzle((int)blockIdx.x - half * s.ptot, s.ptot));
-    const int chunk = uni(FUSED ? wv : (half ? (wv < kWaves / 2 ? wv : wv + kWaves) : wv + kWaves / 2));
+    // (not fused: row `part` of the grid takes the two slabs next on either side of the ones of
+    // the rows before)
+    const int chunks = FUSED ? kChunks : s.chunks;
+    const int part = FUSED ? 0 : (int)blockIdx.y, mid = chunks / 2, side = kWaves / 2;
+    const int p = uni(xcd_swizzle((int)blockIdx.x, s.ptot));
+    const int chunk = uni(FUSED ? wv : (wv < side ? mid - side * (part + 1) + wv : mid + side * (part - 1) + wv));
     if (FUSED && wv == kWaves) {
         const MemberDev *M = s.mem + uni(s.pmem[p]);
         if (p - uni(M->p_off) >= uni(M->np)) return; // (every wave of the workgroup)
@@ -2369,18 +2376,18 @@ void k_links(DevSet s)
     const double X0 = Xo[3 * p], X1 = Xo[3 * p + 1], X2 = Xo[3 * p + 2];
     const double R0 = s.Xref[3 * p], R1 = s.Xref[3 * p + 1], R2 = s.Xref[3 * p + 2];
     // (a list rebuild under compact storage moves the nodes' storage slots)
-    const bool stale = (s.lreb[p] == t - 1) || (s.ldirty[p * kChunks + chunk] == t - 1) ||
+    const bool stale = (s.lreb[p] == t - 1) || (s.ldirty[p * chunks + chunk] == t - 1) ||
                        (s.compact && *s.relist_at == t);
-    int cntx = s.xcnt[p * kChunks + chunk];
+    int cntx = s.xcnt[p * chunks + chunk];
     const MemberDev *M = s.mem + m;
     const int pl = p - uni(M->p_off);
     if (pl >= uni(M->np)) return;
-    double *sums = FUSED ? l_sum[chunk] : s.ppart + ((long long)p * kChunks + chunk) * kLinkComp;
+    double *sums = FUSED ? l_sum[chunk] : s.ppart + ((long long)p * chunks + chunk) * kLinkComp;
     if (stale)
-        cntx = rebuild_chunk<NR>(s, M, p, chunk, X0, X1, X2, l_cells[wv], l_segs[wv], l_c[wv], l_g[wv],
+        cntx = rebuild_chunk<NR>(s, M, p, chunk, chunks, X0, X1, X2, l_cells[wv], l_segs[wv], l_c[wv], l_g[wv],
                                  FUSED ? sums + kLinkComp : nullptr);
     else if (FUSED && lane < kZComp)
-        sums[kLinkComp + lane] = s.zcache[((long long)p * kChunks + chunk) * kZComp + lane];
+        sums[kLinkComp + lane] = s.zcache[((long long)p * chunks + chunk) * kZComp + lane];
     const bool in_lds = stale && cntx <= kLinkLds; // (the wave's own LDS)
 
     const int nx = uni(M->nx), ny = uni(M->ny);
@@ -2391,7 +2398,7 @@ void k_links(DevSet s)
     const double rho_f = uni(M->rho_f);
     const bool rest_free = uni(M->rest_free) != 0;
     const int nxy = nx * ny;
-    const long long lbase = ((long long)p * kChunks + chunk) * s.xcap;
+    const long long lbase = ((long long)p * chunks + chunk) * s.xcap;
     const int *xc = s.xcell + lbase;
     const int *xs = s.xslot + lbase;
     const unsigned *xg = s.xgrp + lbase;
@@ -2874,7 +2881,7 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
             if (!c.per[2]) { lo = max(lo, 0); hi = min(hi, nz - 1); }
             const int ext = c.per[2] ? min(hi - lo + 1, nz) : max(hi - lo + 1, 0);
             s.lzr[2 * p] = lo;
-            s.lzr[2 * p + 1] = (ext + kChunks - 1) / kChunks;
+            s.lzr[2 * p + 1] = (ext + s.chunks - 1) / s.chunks;
             s.lreb[p] = (mode == 1) ? t - 1 : t;
             for (int a = 0; a < 3; ++a) s.Xref[3 * p + a] = c.X[a];
         }
@@ -3630,13 +3637,13 @@ void *links_ptr(int prec)
     default: return (void *)&k_links<PREC_BF16DEV, NR, FUSED>;
     }
 }
-bool links_fused(const DevSet &s) { return s.ptot <= kFusedParticles; }
+bool links_fused(const DevSet &s) { return s.ptot <= kFusedParticles && s.chunks == kChunks; }
 void *links_kernel_ptr(int prec, const DevSet &s)
 {
     if (s.narrow) return links_fused(s) ? links_ptr<true, true>(prec) : links_ptr<true, false>(prec);
     return links_fused(s) ? links_ptr<false, true>(prec) : links_ptr<false, false>(prec);
 }
-void *motion_kernel_ptr() { return (void *)&k_motion; }
+void *motion_kernel_ptr(const DevSet &s) { return s.chunks > kChunks ? (void *)&k_motion<true> : (void *)&k_motion<false>; }
 void *remap_kernel_ptr_prec(int prec)
 {
     switch (prec) {
@@ -3646,7 +3653,7 @@ void *remap_kernel_ptr_prec(int prec)
     default: return (void *)&k_remap<PREC_BF16DEV>;
     }
 }
-int links_grid(const DevSet &s) { return max(links_fused(s) ? s.ptot : 2 * s.ptot, 1); }
+dim3 links_grid(const DevSet &s) { return dim3(max(s.ptot, 1), links_fused(s) ? 1 : s.chunks / links_waves(false)); }
 int refresh_grid(const DevSet &) { return kRefreshBlocks; }
 void *refresh_kernel_ptr(int prec)
 {
@@ -3683,14 +3690,15 @@ int links_block(const DevSet &s) { return links_fused(s) ? 64 * (links_waves(tru
 
 hipError_t launch_links(int prec, const DevSet &s, hipStream_t st)
 {
-    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet)>(links_kernel_ptr(prec, s)), dim3(links_grid(s)),
+    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet)>(links_kernel_ptr(prec, s)), links_grid(s),
                        dim3(links_block(s)), 0, st, s);
     return hipGetLastError();
 }
 
 hipError_t launch_motion(const DevSet &s, int mode, int only_member, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_motion, dim3(motion_grid(s)), dim3(256), 0, st, s, mode, only_member);
+    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet, int, int)>(motion_kernel_ptr(s)), dim3(motion_grid(s)),
+                       dim3(64 * kMotionWaves), 0, st, s, mode, only_member);
     return hipGetLastError();
 }
 

@@ -102,11 +102,11 @@ hipError_t launch_expand(int, const DevSet &, hipStream_t) { return hipSuccess; 
 void *refresh_kernel_ptr(int) { return nullptr; }
 bool links_fused(const DevSet &) { return true; }
 void *links_kernel_ptr(int, const DevSet &) { return nullptr; }
-void *motion_kernel_ptr() { return nullptr; }
+void *motion_kernel_ptr(const DevSet &) { return nullptr; }
 void *fluid_kernel_ptr(int, int, int) { return nullptr; }
 void *remap_kernel_ptr_prec(int) { return nullptr; }
 int refresh_grid(const DevSet &) { return 1; }
-int links_grid(const DevSet &) { return 1; }
+dim3 links_grid(const DevSet &) { return dim3(1); }
 int links_block(const DevSet &) { return 64; }
 int motion_grid(const DevSet &) { return 1; }
 int remap_grid(const DevSet &) { return 1; }
