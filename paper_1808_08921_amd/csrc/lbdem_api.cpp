@@ -82,6 +82,7 @@ struct Geometry {
     int ring_len = 1;
     int pv_ring = 0;
     int chg_cap = 0;
+    double rmax = 0.0; // largest max_radius of a lattice that may hold particles
     int chunks = kChunks;
     int xcap = 1;
     int prec = PREC_FP32;
@@ -263,6 +264,7 @@ void build_geometry(int32_t n, const lbdem_params *lat, const lbdem_config *cfg,
             rmax = std::max(rmax, lat[m].max_radius);
             if (G.mem[m].narrow) images = 2;
         }
+    G.rmax = rmax;
     if (rmax > 0.0) {
         // The planes around the largest particle, and the chunks they are cut into.  A wave takes a
         // chunk, so a set of one sphere has 8 waves for its link pass: from a radius of 15 on the
@@ -297,6 +299,8 @@ size_t carve(const Geometry &G, char *base, DevSet &s)
     s.rt = c.take<uint2>((size_t)std::max<long long>(G.compact ? G.rt_words : 1, 1));
     s.popC = c.take<char>(G.compact ? es * kQ * (size_t)G.cells : 1);
     s.scratch = c.take<char>(64 * (size_t)G.cells);
+    s.rest = base && G.rmax > kRestRadius && G.ptot <= G.cells
+                 ? reinterpret_cast<double *>(static_cast<char *>(s.scratch) + 32 * (size_t)G.cells) : nullptr;
     s.nplanes = (int)G.pz;
     s.clist = c.take<int>((size_t)G.cells);
     s.ccnt = c.take<int>((size_t)std::max<long long>(G.pz, 1));
@@ -558,7 +562,7 @@ int build_graph(lbdem_set *S, int steps)
         HIPCHK(add(on[0], links_kernel_ptr(S->G.prec, S->ds), links_grid(S->ds), links_block(S->ds), fluid_args));
         HIPCHK(add(on[1], motion_kernel_ptr(S->ds), motion_grid(S->ds), 256, part_args));
         HIPCHK(add(on[2], fluid_kernel_ptr(S->G.prec, S->G.compact, S->ds.narrow), S->ds.tiles_total, 256, fluid_args));
-        HIPCHK(add(on[3], remap_kernel_ptr_prec(S->G.prec), remap_grid(S->ds), 256, part_args));
+        HIPCHK(add(on[3], remap_kernel_ptr(S->G.prec, S->ds), remap_grid(S->ds), 256, part_args));
     }
     HIPCHK(hipGraphInstantiate(&S->gexec, S->graph, nullptr, nullptr, 0));
     S->graph_steps = steps;
@@ -604,7 +608,7 @@ int launch_step_eager(lbdem_set *S)
         else if (k == 0) err = launch_links(S->G.prec, S->ds, S->stream);
         else if (k == 1) err = launch_motion(S->ds, 0, -1, S->stream);
         else if (k == 2) err = launch_fluid(S->G.prec, S->ds, S->stream);
-        else err = launch_remap_prec(S->G.prec, S->ds, 0, -1, S->stream);
+        else err = launch_remap(S->G.prec, S->ds, 0, -1, S->stream);
         if (err != hipSuccess) return fail(LBDEM_EDEVICE, "kernel launch %d: %s", k, hipGetErrorString(err));
         if (S->timing) {
             HIPCHK(hipEventRecord(S->ev_pool[e1], S->stream));
@@ -790,6 +794,7 @@ int lbdem_create(int32_t n_lat, const lbdem_params *lat, const lbdem_config *cfg
     CHK(hipMemsetAsync(s.lreb, 0xff, sizeof(long long) * P, st));
     CHK(hipMemsetAsync(s.ldirty, 0xff, sizeof(long long) * P * s.chunks, st));
     CHK(hipMemsetAsync(s.lzr, 0, sizeof(int) * 2 * P, st));
+    if (s.rest) CHK(hipMemsetAsync(s.rest, 0, sizeof(double) * 4 * P, st));
     CHK(hipMemsetAsync(s.tstep, 0, sizeof(long long), st));
     CHK(hipMemsetAsync(s.tcopy, 0, sizeof(long long), st));
     CHK(hipMemsetAsync(s.flags, 0, sizeof(unsigned), st));
@@ -912,7 +917,7 @@ int lbdem_particles_set(lbdem_set *S, int32_t lattice, int32_t n, const double *
     if (rc) return rc;
     hipError_t e = launch_motion(s, 1, lattice, st);
     if (e != hipSuccess) return fail(LBDEM_EDEVICE, "near-list kernel: %s", hipGetErrorString(e));
-    e = launch_remap_prec(S->G.prec, s, 1, lattice, st);
+    e = launch_remap(S->G.prec, s, 1, lattice, st);
     if (e != hipSuccess) return fail(LBDEM_EDEVICE, "projection kernel: %s", hipGetErrorString(e));
     // both node maps of this lattice now agree; a pending change list may still name its
     // old cells, so the next fluid pass copies the current maps whole instead of applying it
@@ -932,11 +937,11 @@ int lbdem_particles_get(lbdem_set *S, int32_t lattice, int32_t n, double *x, dou
     const MemberDev &M = S->G.mem[lattice];
     if (n != M.np) return fail(LBDEM_EINVAL, "lattice %d has %d particles, asked for %d", lattice, M.np, n);
     if (n == 0) return sync_set(S);
-    // one gather into the node scratch and one copy, unless they do not fit it (fewer than two
+    // one gather into the node scratch and one copy, unless they do not fit it (fewer than four
     // nodes a particle) or the host has no memory for them
     const size_t n3 = 3 * (size_t)n;
     std::unique_ptr<double[]> host;
-    if (5 * n3 * sizeof(double) <= 64 * (size_t)S->G.cells) host.reset(new (std::nothrow) double[5 * n3]);
+    if (5 * n3 * sizeof(double) <= 32 * (size_t)S->G.cells) host.reset(new (std::nothrow) double[5 * n3]);
     if (host) {
         double *dev = reinterpret_cast<double *>(S->ds.scratch);
         std::lock_guard<std::mutex> lock(S->scratch_mu);
@@ -1302,7 +1307,7 @@ int lbdem_fields_get(lbdem_set *S, int32_t lattice, double *rho, double *u, int3
         if (rc) return rc;
     }
     if (!rho && !u) return LBDEM_OK;
-    // (the fields take 32 of the node scratch's 64 bytes a node; they go straight to the caller)
+    // (the fields take 32 bytes a node of the node scratch; they go straight to the caller)
     const size_t n = (size_t)S->G.mem[lattice].ncell;
     double *dev = reinterpret_cast<double *>(S->ds.scratch);
     std::lock_guard<std::mutex> lock(S->scratch_mu);
@@ -1320,7 +1325,7 @@ namespace {
 
 // Checkpoint layout: header, the host copy of the per-lattice constants, then the
 // workspace image without the scratch population buffer of compact storage and the node
-// scratch (they hold nothing between calls).
+// scratch (they hold nothing that a run depends on).
 struct CkptHeader {
     char magic[8];
     uint32_t version, n_lat;
@@ -1437,6 +1442,7 @@ int lbdem_state_load(lbdem_set *S, const void *buf, size_t size)
     in += h.skip_off;
     HIPCHK(hipMemcpy(ws + h.skip_off + h.skip_bytes, in, h.ws_bytes - h.skip_off - h.skip_bytes,
                      hipMemcpyHostToDevice));
+    if (S->ds.rest) HIPCHK(hipMemset(S->ds.rest, 0, sizeof(double) * 4 * (size_t)S->G.ptot));
     // the host's copy of the per-lattice constants (particle counts, fluid-kernel grid)
     S->G.mem = mem;
     int tiles = 0;

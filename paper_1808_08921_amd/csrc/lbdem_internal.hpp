@@ -40,6 +40,8 @@ constexpr int kPendCap = 16384;     // refills of unlisted nodes awaiting the ne
 constexpr int kChunks = 8;
 constexpr int kMaxChunks = 64;
 constexpr int kSlabPlanes = 5;
+// the re-projection watches particles beyond this radius that hardly move
+constexpr double kRestRadius = 12.0;
 // components of a link-pass partial per (particle, chunk): F0 (3) and sum xr x G (3), xr the
 // node position relative to the particle's reference point
 constexpr int kLinkComp = 6;
@@ -135,9 +137,13 @@ struct DevSet {
     unsigned long long *lwc;  // [ncell_total]
     long long *lwc_bad;
     long long ncell_total;
-    // 64 bytes per node that hold nothing between calls (the reads of particles and fields
-    // gather into it, one at a time)
+    // 64 bytes per node: the first half holds nothing between calls (the reads of particles and
+    // fields gather into it, one at a time); the second half, in a set that may hold particles
+    // beyond kRestRadius and where it has room for them, per particle the position of its last
+    // full search by the re-projection and how far it may move from there before a node can
+    // change (0: not known) [ptot*4], else null
     void *scratch;
+    double *rest;
     int *chg[2];
     int chg_cap;
     int *chgcnt;              // [2]
@@ -223,7 +229,7 @@ hipError_t launch_refresh(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_links(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_motion(const DevSet &s, int mode, int only_member, hipStream_t st);
 hipError_t launch_fluid(int prec, const DevSet &s, hipStream_t st);
-hipError_t launch_remap_prec(int prec, const DevSet &s, int mode, int only_member, hipStream_t st);
+hipError_t launch_remap(int prec, const DevSet &s, int mode, int only_member, hipStream_t st);
 hipError_t launch_init_pops(int prec, const DevSet &s, long long total_cells, hipStream_t st);
 hipError_t launch_expand(int prec, const DevSet &s, hipStream_t st);
 hipError_t launch_particles_out(const DevSet &s, int p0, int n, double *out, hipStream_t st);
@@ -234,7 +240,7 @@ bool links_fused(const DevSet &s); // the link kernel moves the particles too
 void *links_kernel_ptr(int prec, const DevSet &s);
 void *motion_kernel_ptr(const DevSet &s);
 void *fluid_kernel_ptr(int prec, int compact, int narrow);
-void *remap_kernel_ptr_prec(int prec);
+void *remap_kernel_ptr(int prec, const DevSet &s);
 int refresh_grid(const DevSet &s);
 dim3 links_grid(const DevSet &s);
 int links_block(const DevSet &s);

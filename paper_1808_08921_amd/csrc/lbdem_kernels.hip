@@ -2282,7 +2282,12 @@ __global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode
 #pragma unroll
             for (int q = 0; q < kChunks; ++q) v += ch[q];
             if constexpr (MANY)
-                for (int q = kChunks; q < s.chunks; ++q) v += pp[q * stride];
+                for (int q0 = kChunks; q0 < s.chunks; q0 += kChunks) {
+#pragma unroll
+                    for (int q = 0; q < kChunks; ++q) ch[q] = pp[(q0 + q) * stride];
+#pragma unroll
+                    for (int q = 0; q < kChunks; ++q) v += ch[q];
+                }
         }
         lp[wv][lane] = v;
     }
@@ -2511,6 +2516,10 @@ struct RemapCtx {
 
 constexpr int kRemapWaves = 4; // particles per workgroup of the re-projection kernel
 
+// Particles beyond kRestRadius are watched while they move less than kRestStep a step (a shell
+// of kRestShell on both sides of the surface holds 8 pi R^2 kRestShell nodes, 9 at R = 60).
+constexpr double kRestStep = 5e-5, kRestShell = 1e-4;
+
 // Re-projection (Sec. 2.3), one wave per particle.  The nodes whose owner the step can have
 // changed lie within the particle's displacement of its surface, or inside it within the
 // overlap depth with a neighbour; they are found row by row from the sphere's equation (a
@@ -2520,7 +2529,7 @@ constexpr int kRemapWaves = 4; // particles per workgroup of the re-projection k
 // once the particle had left its shell, cost 25 us per step on the FCC wave case and 370 us
 // on a suspension of 288 moving spheres, where some list was always being built, against
 // 16 and 26 us.)  Waves never synchronise; workgroups past the particles reduce the probe planes.
-template <int P>
+template <int P, bool WATCH>
 __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
 {
     using S = typename Prec<P>::S;
@@ -2577,6 +2586,8 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
     };
 
     // owner of one node after the motion; conversion of a covered node; opened: p uncovered it
+    bool watch = false;         // a large particle that hardly moves, see below
+    double gap = kRestShell;    // and the least distance of an evaluated node from its surface
     auto evaluate = [&](const RemapCtx &c, int ii, int jj, int kk, int cell, double (&acc)[6], int &conv,
                         bool &opened) {
         const MemberDev *M = c.M;
@@ -2584,6 +2595,7 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
         const int *cur = s.own[par] + M->cell_off;
         const int was = cur[cell];
         const double d2n = dist2c(c, ii, jj, kk, c.X[0], c.X[1], c.X[2]);
+        if (WATCH && watch) gap = fmin(gap, fabs(sqrt(d2n) - c.R));
         // owner: smallest d^2, then smallest index, among the spheres containing the node
         int best = -1;
         double bd = 0.0;
@@ -2792,7 +2804,21 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
     // <= the displacement; the order between p and an overlapping sphere changes only at
     // nodes of p within the overlap depth, before the motion (R - d <= depth + displacement)
     // or after it.  (At set-up every node inside p.)
-    const double mrg = row_margin(R);
+    // A large particle that hardly moves and overlaps no other is watched: its search takes in
+    // the nodes up to kRestShell off its surface and finds how far it may move before the first
+    // of them can change, and until it has there is nothing to search.  (64 rows cost a wave 0.33
+    // us; one sphere at rest, us per launch, searched | watched: radius 13 10.6 | 7.7, 18 14.6 |
+    // 8, 36 35 | 9, 60 83 | 11, 100 212 | 11.  Up to a radius of 12 the search is short: 1.5 us
+    // at 10.)
+    const bool large = WATCH && mode == 0 && R > kRestRadius;
+    double *rest = WATCH ? s.rest + 4 * (size_t)p : nullptr; // (the position of the last search and that distance)
+    watch = large && step < kRestStep;
+    bool quiet = false;
+    if (watch && dmax == 0.0) {
+        const double Xs0[3] = {rest[0], rest[1], rest[2]};
+        quiet = dist(c.X, Xs0) + 1e-9 < rest[3];
+    }
+    const double mrg = row_margin(R) + (watch ? kRestShell : 0.0);
     const double outer = R + step + mrg, inner = (mode == 1) ? -1.0 : R - (dmax + step) - mrg;
     const float outer2 = (float)(outer * outer), inner2 = inner > 0.0 ? (float)(inner * inner) : -1.0f;
     const int nx = M->nx, ny = M->ny, nz = M->nz;
@@ -2802,7 +2828,7 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
     near_range(c.X[2], outer, nz, c.per[2], z0, z1);
     const int ix = (int)floor(c.X[0]);
     const float fx = (float)(c.X[0] - (double)ix);
-    const int nj = max(y1 - y0 + 1, 0), nrow = nj * max(z1 - z0 + 1, 0);
+    const int nj = max(y1 - y0 + 1, 0), nrow = quiet ? 0 : nj * max(z1 - z0 + 1, 0);
     const double inv_nj = 1.0 / (double)max(nj, 1);
     const int dxy = nx * ny;
     const double inv_dxy = 1.0 / (double)dxy, inv_nx = 1.0 / (double)nx;
@@ -2864,6 +2890,12 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
         // (the queue is filled again once every lane has read its entries)
         wave_fence();
         qn = 0;
+    }
+    if (large && !quiet) {
+        const double g = watch ? wave_min_d(gap) : 0.0;
+        if (lane < 4) rest[lane] = lane == 0 ? c.X[0] : lane == 1 ? c.X[1] : lane == 2 ? c.X[2] : g;
+    } else if (WATCH && mode == 1 && lane == 0) {
+        rest[3] = 0.0;
     }
     // the wave's conversion momentum (summed only when a lane made a conversion)
     if (__ballot(conv) != 0ull) {
@@ -3644,15 +3676,17 @@ void *links_kernel_ptr(int prec, const DevSet &s)
     return links_fused(s) ? links_ptr<false, true>(prec) : links_ptr<false, false>(prec);
 }
 void *motion_kernel_ptr(const DevSet &s) { return s.chunks > kChunks ? (void *)&k_motion<true> : (void *)&k_motion<false>; }
-void *remap_kernel_ptr_prec(int prec)
+template <bool WATCH>
+void *remap_ptr(int prec)
 {
     switch (prec) {
-    case PREC_FP64: return (void *)&k_remap<PREC_FP64>;
-    case PREC_FP32: return (void *)&k_remap<PREC_FP32>;
-    case PREC_FP16DEV: return (void *)&k_remap<PREC_FP16DEV>;
-    default: return (void *)&k_remap<PREC_BF16DEV>;
+    case PREC_FP64: return (void *)&k_remap<PREC_FP64, WATCH>;
+    case PREC_FP32: return (void *)&k_remap<PREC_FP32, WATCH>;
+    case PREC_FP16DEV: return (void *)&k_remap<PREC_FP16DEV, WATCH>;
+    default: return (void *)&k_remap<PREC_BF16DEV, WATCH>;
     }
 }
+void *remap_kernel_ptr(int prec, const DevSet &s) { return s.rest ? remap_ptr<true>(prec) : remap_ptr<false>(prec); }
 dim3 links_grid(const DevSet &s) { return dim3(max(s.ptot, 1), links_fused(s) ? 1 : s.chunks / links_waves(false)); }
 int refresh_grid(const DevSet &) { return kRefreshBlocks; }
 void *refresh_kernel_ptr(int prec)
@@ -3702,14 +3736,10 @@ hipError_t launch_motion(const DevSet &s, int mode, int only_member, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_remap_prec(int prec, const DevSet &s, int mode, int only_member, hipStream_t st)
+hipError_t launch_remap(int prec, const DevSet &s, int mode, int only_member, hipStream_t st)
 {
-    switch (prec) {
-    case PREC_FP64: hipLaunchKernelGGL(k_remap<PREC_FP64>, dim3(remap_grid(s)), dim3(256), 0, st, s, mode, only_member); break;
-    case PREC_FP32: hipLaunchKernelGGL(k_remap<PREC_FP32>, dim3(remap_grid(s)), dim3(256), 0, st, s, mode, only_member); break;
-    case PREC_FP16DEV: hipLaunchKernelGGL(k_remap<PREC_FP16DEV>, dim3(remap_grid(s)), dim3(256), 0, st, s, mode, only_member); break;
-    default: hipLaunchKernelGGL(k_remap<PREC_BF16DEV>, dim3(remap_grid(s)), dim3(256), 0, st, s, mode, only_member); break;
-    }
+    hipLaunchKernelGGL(reinterpret_cast<void (*)(DevSet, int, int)>(remap_kernel_ptr(prec, s)), dim3(remap_grid(s)),
+                       dim3(256), 0, st, s, mode, only_member);
     return hipGetLastError();
 }
 

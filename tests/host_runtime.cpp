@@ -96,7 +96,7 @@ hipError_t launch_refresh(int, const DevSet &, hipStream_t) { return hipSuccess;
 hipError_t launch_links(int, const DevSet &, hipStream_t) { return hipSuccess; }
 hipError_t launch_motion(const DevSet &, int, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_fluid(int, const DevSet &, hipStream_t) { return hipSuccess; }
-hipError_t launch_remap_prec(int, const DevSet &, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_remap(int, const DevSet &, int, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_init_pops(int, const DevSet &, long long, hipStream_t) { return hipSuccess; }
 hipError_t launch_expand(int, const DevSet &, hipStream_t) { return hipSuccess; }
 void *refresh_kernel_ptr(int) { return nullptr; }
@@ -104,7 +104,7 @@ bool links_fused(const DevSet &) { return true; }
 void *links_kernel_ptr(int, const DevSet &) { return nullptr; }
 void *motion_kernel_ptr(const DevSet &) { return nullptr; }
 void *fluid_kernel_ptr(int, int, int) { return nullptr; }
-void *remap_kernel_ptr_prec(int) { return nullptr; }
+void *remap_kernel_ptr(int, const DevSet &) { return nullptr; }
 int refresh_grid(const DevSet &) { return 1; }
 dim3 links_grid(const DevSet &) { return dim3(1); }
 int links_block(const DevSet &) { return 64; }
