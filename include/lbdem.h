@@ -286,7 +286,8 @@ int lbdem_state_load(lbdem_set *set, const void *buf, size_t size);
  * 3 (re-projection), 4 (start-of-step node-map refresh), the summed milliseconds ms[k] and
  * the number of launches count[k] since enabling (ms and count hold 5 entries).  A kernel
  * that a set has no use for counts 0 launches: the motion in a set of at most 256 particles
- * (of a max_radius below 15), whose link kernel does it, links, motion and refresh in a set without particles. */
+ * (of a max_radius below 15), whose link kernel does it, links, motion and refresh in a set
+ * without particles. */
 int lbdem_timing_enable(lbdem_set *set, int enable);
 int lbdem_timing_read(lbdem_set *set, double *ms, int64_t *count);
 

@@ -8,8 +8,8 @@
 //   sum x(t) exp(-j omega t) = exp(-j omega tc) (sum S cos(omega tau) - j sum D sin(omega tau)),
 // half the multiplications of the unfolded sum.  The two sums over tau are products of a
 // (frequency x tau) and a (tau x column) matrix and run on the matrix units in FP64.  Time is
-// split over waves and chunks whose partial sums are added in
-// a fixed order (deterministic), then the space stage multiplies by a table of exp(j kappa_n z).
+// split over waves and chunks whose partial sums are added in a fixed order (deterministic), then
+// the space stage multiplies by a table of exp(j kappa_n z).
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -275,11 +275,12 @@ __device__ inline void store_ridge(const double (&best)[MR], const int (&first)[
     }
 }
 
-// F[m][n] = sum_z G[m][z] E[z][n] for MR rows m and the n of this workgroup (all of them, or
-// one of `parts` parts), and with ridge the rows' ridge, for which the workgroup has to hold
-// every n.  (Workgroups of neighbouring numbers take the parts of the same rows: with a multiple
-// of 8 of them each XCD keeps to its parts of E, which then stay in its L2.)  An element of E serves MR rows, and a row's maximum needs no second pass over F
-// (1024 x 1024 x 24: 17 + 7 us one row and 256 n at a time with a kernel for the ridge, 12 us).
+// F[m][n] = sum_z G[m][z] E[z][n] for MR rows m and the n of this workgroup (all of them, or one
+// of `parts` parts), and with ridge the rows' ridge, for which the workgroup has to hold every n.
+// (Workgroups of neighbouring numbers take the parts of the same rows: with a multiple of 8 of
+// them each XCD keeps to its parts of E, which then stay in its L2.)  An element of E serves MR
+// rows, and a row's maximum needs no second pass over F (1024 x 1024 x 24: 17 + 7 us one row and
+// 256 n at a time with a kernel for the ridge, 12 us).  UZ: loads in flight.
 template <int MR, int UZ>
 __global__ __launch_bounds__(1024) void k_dft_space(const double2 *__restrict__ G, const double2 *__restrict__ E,
                                                     int nz, int nw, int nk, double2 *__restrict__ F,

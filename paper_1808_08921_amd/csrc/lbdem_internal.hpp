@@ -47,7 +47,6 @@ constexpr double kRestRadius = 12.0;
 constexpr int kLinkComp = 6;
 // cached link-set sums per (particle, chunk): S (6, upper triangle), Qx (9, row-major), Wx (6)
 constexpr int kZComp = 21;
-constexpr int kEmpty = 0x7fffffff;
 // Link words of a fluid node x (two 64-bit words per node: lw[c] and lw[ncell_total + c]).
 // Word 0: bits 0-17 the directions e whose source x - c_e is inside a particle, bits 18-35
 // the low bit of the slot (0..3) of the particle owning that source, bits 36-48 and 49-61

@@ -261,19 +261,10 @@ __device__ __forceinline__ int wave_sum_i(int v)
     return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
            (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
 }
-// Minimum over the 64 lanes, returned to every lane.
-__device__ __forceinline__ int wave_min(int v)
-{
-    v = min(v, dpp_i<0xB1, 0xF>(v, v));
-    v = min(v, dpp_i<0x4E, 0xF>(v, v));
-    v = min(v, dpp_i<0x141, 0xF>(v, v));
-    v = min(v, dpp_i<0x140, 0xF>(v, v));
-    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
+// Minimum over the 64 lanes of non-negative values (their bit patterns order like the values),
+// returned to every lane.
 __device__ __forceinline__ double wave_min_d(double v)
 {
-    // values are non-negative here: the bit patterns order like the values
     long long b = __double_as_longlong(v);
     int hi = (int)(b >> 32);
     unsigned lo = (unsigned)b;
@@ -329,13 +320,6 @@ __device__ __forceinline__ const MemberDev *member_of_tile(const DevSet &s, int 
         else hi = mid - 1;
     }
     return s.mem + uni(lo);
-}
-
-__device__ __forceinline__ int wrap_axis(int c, int n, int bclo, int bchi, int &kind)
-{
-    if (c < 0) { kind = max(kind, bclo); return c + n; }
-    if (c >= n) { kind = max(kind, bchi); return c - n; }
-    return c;
 }
 
 // Density boundary on a z face: non-equilibrium bounce-back (Sec. 2.4) with zero
@@ -405,19 +389,12 @@ __device__ __forceinline__ void moments(const C (&f)[kQ], C &rho, C &jx, C &jy, 
     rho = r; jx = x; jy = y; jz = z;
 }
 
-// f^eq_d(rho, u), Eq. (BGKequili)
-template <typename C>
-__device__ __forceinline__ C feq(int d, C rho, C ux, C uy, C uz, C uu)
+// f^eq_d(rho, u), Eq. (BGKequili), in FP64
+__device__ __forceinline__ double feq(int d, double rho, double ux, double uy, double uz, double uu)
 {
-    const C cu = cdot(d, ux, uy, uz);
-    if constexpr (sizeof(C) == 8) {
-        const double cs2 = kCS2;
-        return kWd[d] * rho * (1.0 + cu / cs2 + (cu * cu) / (2.0 * cs2 * cs2) - uu / (2.0 * cs2));
-    } else {
-        return (C)kWd[d] * rho * (C(1) + C(3) * cu + C(4.5) * (cu * cu) - C(1.5) * uu);
-    }
+    const double cu = cdot(d, ux, uy, uz), cs2 = kCS2;
+    return kWd[d] * rho * (1.0 + cu / cs2 + (cu * cu) / (2.0 * cs2 * cs2) - uu / (2.0 * cs2));
 }
-
 // f^eq_d(rho, u) - w_d rho_f with rho = rho_f + drho, Eq. (BGKequili) written for the
 // deviation from the rest state: w_d (drho + rho (c.u / c_s^2 + (c.u)^2 / (2 c_s^4) - u.u /
 // (2 c_s^2))), with 1 / c_s^2 = 3 as exact factors 3, 9/2 and 3/2 and fused multiply-adds
@@ -983,7 +960,7 @@ __global__ __launch_bounds__(256) void k_refresh(DevSet s)
                         const double uu = u0 * u0 + u1 * u1 + u2 * u2;
                         S *CbS = reinterpret_cast<S *>(Cb);
                         for (int d = 0; d < kQ; ++d)
-                            st<P>(CbS, (unsigned)(d * nc + to), d, (typename Prec<P>::C)feq<double>(d, rb, u0, u1, u2, uu),
+                            st<P>(CbS, (unsigned)(d * nc + to), d, (typename Prec<P>::C)feq(d, rb, u0, u1, u2, uu),
                                   M->rho_f);
                         continue;
                     }
@@ -2325,7 +2302,7 @@ __global__ __launch_bounds__(64 * kMotionWaves) void k_motion(DevSet s, int mode
 // FUSED: one workgroup per particle, a wave per chunk and a ninth for p's contacts meanwhile
 // and its motion (motion_update) after the workgroup's barrier.  This saves the motion kernel's
 // launch and its loads, but a workgroup holds its place until the motion is done, so it pays
-// while every workgroup has a CU of its own (FCC packings, FP32, us for links and motion, fused
+// while every workgroup has a CU of its own, which a set's room for particles bounds (FCC packings, FP32, us for links and motion, fused
 // | apart: 256 particles 19 | 25, 384 28 | 28, 512 32 | 30, 768 41 | 34; 60 in a chain, FP64,
 // 14 | 19).  Otherwise a workgroup per four slabs, first the equatorial slabs of every
 // particle, which hold most of the entries, then the polar ones (in slab order the long waves
@@ -2539,8 +2516,9 @@ __global__ __launch_bounds__(256) void k_remap(DevSet s, int mode, int only)
     // each wave's queue of candidate nodes
     constexpr int kQueue = 256;
     __shared__ int qcell[kRemapWaves][kQueue];
-    // the step being completed: copied by the fluid kernel (mode 0); the counter itself is
-    // advanced here and read by no workgroup of this kernel
+    // the step being completed (mode 0), copied by the refresh kernel, or by the fluid kernel of a
+    // set that runs no refresh; the counter itself is advanced here and read by no workgroup of
+    // this kernel
     const long long t = (mode == 0) ? *s.tcopy : *s.tstep;
     const int par = (int)(t & 1);
     const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
@@ -3004,7 +2982,7 @@ __global__ __launch_bounds__(256) void k_fields(DevSet s, int m, double *out)
             const double uu = u0 * u0 + u1 * u1 + u2 * u2;
 #pragma unroll
             for (int d = 0; d < kQ; ++d)
-                st<P>(raw, d, d, (typename Prec<P>::C)feq<double>(d, rb, u0, u1, u2, uu), rho_ff);
+                st<P>(raw, d, d, (typename Prec<P>::C)feq(d, rb, u0, u1, u2, uu), rho_ff);
         }
 #pragma unroll
         for (int d = 0; d < kQ; ++d) {
@@ -3085,7 +3063,7 @@ __global__ __launch_bounds__(256) void k_expand(DevSet s)
                 }
                 const double uu = u0 * u0 + u1 * u1 + u2 * u2;
                 for (int d = 0; d < kQ; ++d)
-                    st<P>(A, (unsigned)(d * nc + z0 + c), d, (typename Prec<P>::C)feq<double>(d, rb, u0, u1, u2, uu), rho_ff);
+                    st<P>(A, (unsigned)(d * nc + z0 + c), d, (typename Prec<P>::C)feq(d, rb, u0, u1, u2, uu), rho_ff);
             }
         }
         __syncthreads();
